@@ -1,0 +1,354 @@
+"""Cases of the GPP reduction for timing and comparison, through the package's
+public entry points: the forward (sigma_fwd, sigma_fwd_noalloc, sigma_qp), the
+adjoint (sigma_bwd, and sigma with autograd) and the batched forward (Plan,
+sigma_batched).
+
+A case is a dict of plain values:
+  entry   the entry point: "fwd", "noalloc", "qp", "autograd", "bwd", "batched"
+  nb, nv, ng, np, nw   number_bands, nvband, ncouls, ngpown, nfreq
+  poles   share of wtilde planted within 1e-6 of a frequency
+  reuse   the program keeps its outputs and workspace from call to call
+          (otherwise each call allocates its own)
+and for "batched" instead of the sizes of one state:
+  states, nw, nb_lo, nb_hi, ng_lo, ng_hi, ng_unit, np_per (ngpown = ncouls //
+  np_per, at least 1), sizes (the seed of the states' sizes)
+
+Values follow the distributions of paper_2008_11326_amd.inputs, drawn on the
+GPU.
+"""
+import math
+import random
+
+import torch
+
+import paper_2008_11326_amd as gpp
+
+DEV = "cuda:0"
+F64, C128 = torch.float64, torch.complex128
+FLOP_PER_TERM = 21       # forward: fp64 operations of one Coulomb-hole or exchange term
+FLOP_PER_TERM_BWD = 42   # adjoint: the term again, and its share of four gradients
+# terms beyond which the plain evaluation below takes too long
+EXACT_TERMS, EXACT_TERMS_BWD = 1.2e11, 1.5e10
+
+
+def one(name, entry, nb, nv, ng, np_, nw, poles=0.0, reuse=False):
+    return {"name": name, "entry": entry, "nb": nb, "nv": nv, "ng": ng, "np": np_, "nw": nw,
+            "poles": poles, "reuse": reuse}
+
+
+def listed():
+    return [
+        # the smallest workload, one call as written in the README: latency,
+        # launches and the binding's own cost
+        one("fwd_small", "fwd", 32, 2, 512, 64, 3),
+        # a small odd-sized system at the paper's two frequencies, some
+        # wtilde next to a pole
+        one("fwd_ragged", "fwd", 61, 3, 777, 38, 2, poles=0.05),
+        # one quasiparticle state of a small system inside a loop over states
+        # that keeps its buffers
+        one("qp_state", "qp", 128, 2, 4096, 204, 3, reuse=True),
+        # a serving loop that may not allocate, five frequencies
+        one("noalloc_loop", "noalloc", 64, 2, 2048, 102, 5, reuse=True),
+        # a wide frequency scan of one state of a middle-sized system
+        one("fwd_scan8", "fwd", 256, 2, 8192, 409, 8),
+        # the Si-shaped share of one task
+        one("fwd_si", "fwd", 512, 2, 32768, 1638, 3, reuse=True),
+        # the larger system, 1 % near-poles: the benchmark's headline
+        one("fwd_large", "fwd", 1024, 4, 65536, 3276, 3, poles=0.01, reuse=True),
+        # forward and backward of the smallest workload through autograd: one
+        # step of a fit on a small model system
+        one("autograd_small", "autograd", 32, 2, 512, 64, 3),
+        # the adjoint workload, all four gradients
+        one("bwd_adjoint", "bwd", 256, 2, 16384, 819, 3, reuse=True),
+        # an odd-sized adjoint at five frequencies
+        one("bwd_ragged", "bwd", 101, 4, 3001, 150, 5),
+        # 256 states of a small system in one plan
+        {"name": "batched_small", "entry": "batched", "states": 256, "nw": 3, "nb_lo": 32,
+         "nb_hi": 128, "ng_lo": 4, "ng_hi": 16, "ng_unit": 256, "np_per": 20, "sizes": 5,
+         "reuse": True},
+        # 3000 tiny states (model systems, tests of a code that calls this one)
+        {"name": "batched_tiny", "entry": "batched", "states": 3000, "nw": 3, "nb_lo": 1,
+         "nb_hi": 6, "ng_lo": 1, "ng_hi": 100, "ng_unit": 1, "np_per": 20, "sizes": 31,
+         "reuse": True},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    if rng.random() < 0.2:
+        tiny = rng.random() < 0.5
+        return {"entry": "batched", "states": _log_int(rng, 8, 1000 if tiny else 128),
+                "nw": rng.choice((1, 2, 3, 3, 5)), "nb_lo": 1 if tiny else 20,
+                "nb_hi": rng.randint(4, 12) if tiny else rng.randint(40, 160),
+                "ng_lo": 1 if tiny else 3, "ng_hi": rng.randint(30, 150) if tiny else 12,
+                "ng_unit": 1 if tiny else rng.choice((100, 255, 256)),
+                "np_per": rng.choice((10, 20)), "sizes": rng.randrange(1 << 20), "reuse": True}
+    entry = rng.choice(("fwd", "fwd", "fwd", "noalloc", "qp", "autograd", "bwd", "bwd"))
+    nw = rng.choice((3, 5, 7)) if entry == "qp" else rng.choice((1, 2, 3, 3, 3, 4, 5, 6, 7, 8))
+    back = entry in ("autograd", "bwd")
+    nb = _log_int(rng, 12, 300 if back else 900)
+    nv = min(nb, rng.choice((0, 1, 2, 2, 3, 4, 8)))
+    ng = _log_int(rng, 200, 12000 if back else 24000)
+    np_ = max(1, int(ng / rng.uniform(10.0, 30.0)))
+    c = one("", entry, nb, nv, ng, np_, nw, rng.choice((0.0, 0.0, 0.01, 0.05)),
+            entry in ("noalloc", "qp") or rng.random() < 0.5)
+    del c["name"]
+    return c
+
+
+# ---- inputs ---------------------------------------------------------------
+
+def _uni(gen, shape, lo, hi):
+    return torch.rand(shape, generator=gen, dtype=F64, device=DEV) * (hi - lo) + lo
+
+
+def _cuni(gen, shape, lr, hr, li, hi):
+    return torch.complex(_uni(gen, shape, lr, hr), _uni(gen, shape, li, hi))
+
+
+def _inputs(case, gen):
+    nb, ng, np_, nw = case["nb"], case["ng"], case["np"], case["nw"]
+    e_n, e_lk = _uni(gen, (nb,), -1.0, 1.0), _uni(gen, (1,), -1.0, 1.0)
+    shift = (torch.arange(nw, dtype=F64, device=DEV) - (nw - 1) / 2.0) * 0.5
+    t = {"aqsmtemp": _cuni(gen, (nb, ng), -0.5, 0.5, -0.5, 0.5),
+         "aqsntemp": _cuni(gen, (nb, ng), -0.5, 0.5, -0.5, 0.5),
+         "I_eps_array": _cuni(gen, (np_, ng), -0.5, 0.5, -0.5, 0.5),
+         "wtilde_array": _cuni(gen, (np_, ng), 0.5, 2.0, -0.05, 0.05),
+         "vcoul": _uni(gen, (ng,), 0.1, 1.0),
+         "wx_array": ((e_lk - e_n)[None, :] + shift[:, None]).contiguous()}
+    k = int(round(case["poles"] * np_ * ng))
+    if k:
+        # every (1/share)-th pair, from a drawn offset, next to a drawn frequency
+        step = (np_ * ng) // k
+        first = int(torch.randint(step, (1,), generator=gen, device=DEV))
+        at = first + step * torch.arange(k, device=DEV)
+        pick = torch.randint(nw * nb, (k,), generator=gen, device=DEV)
+        t["wtilde_array"].view(-1)[at] = t["wx_array"].view(-1)[pick] + _cuni(
+            gen, (k,), -1e-6, 1e-6, -1e-6, 1e-6)
+    return t
+
+
+def _dims(case):
+    return case["nb"], case["nv"], case["ng"], case["np"], case["nw"]
+
+
+def _batch_dims(case):
+    r = random.Random(case["sizes"])
+    out = []
+    for _ in range(case["states"]):
+        nb = r.randint(case["nb_lo"], case["nb_hi"])
+        ng = case["ng_unit"] * r.randint(case["ng_lo"], case["ng_hi"])
+        out.append((nb, min(2, nb), ng, max(1, ng // case["np_per"]), case["nw"]))
+    return out
+
+
+def _batch_inputs(case, gen):
+    """The states' inputs, each array kind drawn in one piece and cut."""
+    dims = _batch_dims(case)
+    nw = case["nw"]
+    pad = lambda n: -(-n // 2) * 2  # real arrays start on 16 bytes, too
+    nbg, npg = [d[0] * d[2] for d in dims], [d[3] * d[2] for d in dims]
+    am = _cuni(gen, (sum(nbg),), -0.5, 0.5, -0.5, 0.5)
+    an = _cuni(gen, (sum(nbg),), -0.5, 0.5, -0.5, 0.5)
+    ie = _cuni(gen, (sum(npg),), -0.5, 0.5, -0.5, 0.5)
+    wt = _cuni(gen, (sum(npg),), 0.5, 2.0, -0.05, 0.05)
+    vc = _uni(gen, (sum(pad(d[2]) for d in dims),), 0.1, 1.0)
+    # wx of a state: nw rows of e_lk - e_n, shifted
+    base = _uni(gen, (sum(pad(nw * d[0]) for d in dims),), -1.0, 1.0)
+    shift = [(w - (nw - 1) / 2.0) * 0.5 for w in range(nw)]
+    add, e_lk = [], torch.rand(len(dims), generator=torch.Generator().manual_seed(
+        int(gen.initial_seed())), dtype=F64).tolist()
+    for d, e in zip(dims, e_lk):
+        row = [2.0 * e - 1.0 + s for s in shift for _ in range(d[0])]
+        add += row + [0.0] * (pad(nw * d[0]) - nw * d[0])
+    states, b, p, v, x = [], 0, 0, 0, 0
+    for d, n, q in zip(dims, nbg, npg):
+        nb, ng = d[0], d[2]
+        base[x:x + nw * nb].view(nw, nb)[1:] = base[x:x + nb]
+        states.append({"aqsmtemp": am[b:b + n].view(nb, ng), "aqsntemp": an[b:b + n].view(nb, ng),
+                       "I_eps_array": ie[p:p + q].view(d[3], ng),
+                       "wtilde_array": wt[p:p + q].view(d[3], ng), "vcoul": vc[v:v + ng],
+                       "wx_array": base[x:x + nw * nb].view(nw, nb)})
+        b, p, v, x = b + n, p + q, v + pad(ng), x + pad(nw * nb)
+    base.neg_().add_(torch.tensor(add, dtype=F64).to(DEV))
+    return dims, states
+
+
+def _gradients_of_the_loss(gen, nw):
+    z = torch.complex(torch.randn(2 * nw, generator=gen, dtype=F64, device=DEV),
+                      torch.randn(2 * nw, generator=gen, dtype=F64, device=DEV))
+    z = z / z.abs().square().sum().sqrt()
+    return z[:nw].clone(), z[nw:].clone()
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(int(seed))
+    entry, nw = case["entry"], case["nw"]
+    s = {"entry": entry, "reuse": case["reuse"], "out": None, "ws": None}
+    if entry == "batched":
+        dims, s["states"] = _batch_inputs(case, gen)
+        s["plan"] = gpp.Plan(dims)
+        s["out"] = tuple(torch.empty((len(dims), nw), dtype=C128, device=DEV) for _ in range(2))
+        s["ws"] = torch.empty(s["plan"].workspace_bytes, dtype=torch.uint8, device=DEV)
+        return s
+    t = _inputs(case, gen)
+    s["in"], s["nv"] = t, case["nv"]
+    if entry in ("autograd", "bwd"):
+        s["ga"], s["gs"] = _gradients_of_the_loss(gen, nw)
+    if entry == "autograd":
+        s["leaves"] = [t[k].requires_grad_() for k in
+                       ("aqsmtemp", "aqsntemp", "I_eps_array", "wtilde_array")]
+    if case["reuse"]:
+        if entry == "bwd":
+            s["ws"] = torch.empty(gpp.bwd_workspace_bytes(*_dims(case)), dtype=torch.uint8,
+                                  device=DEV)
+        else:
+            s["out"] = tuple(torch.empty(nw, dtype=C128, device=DEV) for _ in range(2))
+            if entry == "qp":
+                s["out"] += (torch.empty(6, dtype=F64, device=DEV),)
+            if entry != "noalloc":
+                s["ws"] = torch.empty(gpp.fwd_workspace_bytes(*_dims(case)), dtype=torch.uint8,
+                                      device=DEV)
+    elif entry == "noalloc":
+        s["out"] = tuple(torch.empty(nw, dtype=C128, device=DEV) for _ in range(2))
+    return s
+
+
+def run(s):
+    entry = s["entry"]
+    if entry == "fwd":
+        return gpp.sigma_fwd(**s["in"], nvband=s["nv"], out=s["out"], workspace=s["ws"])
+    if entry == "noalloc":
+        return gpp.sigma_fwd_noalloc(**s["in"], nvband=s["nv"], out=s["out"])
+    if entry == "qp":
+        return gpp.sigma_qp(**s["in"], nvband=s["nv"], freq_step=0.5, energy=0.25, vxc=-0.25,
+                            out=s["out"], workspace=s["ws"])
+    if entry == "bwd":
+        return gpp.sigma_bwd(**s["in"], nvband=s["nv"], grad_achtemp=s["ga"],
+                             grad_asxtemp=s["gs"], workspace=s["ws"])
+    if entry == "autograd":
+        ach, asx = gpp.sigma(**s["in"], nvband=s["nv"])
+        return (ach, asx) + torch.autograd.grad((ach, asx), s["leaves"], (s["ga"], s["gs"]))
+    return gpp.sigma_batched(s["plan"], s["states"], out=s["out"], workspace=s["ws"])
+
+
+# ---- work -----------------------------------------------------------------
+
+def _terms(d):
+    nb, nv, ng, np_, nw = d
+    return (nb + nv) * ng * np_ * nw
+
+
+def _read(d):
+    nb, _, ng, np_, nw = d
+    return 16 * (nb * np_ + nb * ng + 2 * np_ * ng) + 8 * (ng + nw * nb)
+
+
+def work(case):
+    entry = case["entry"]
+    if entry == "batched":
+        dims = _batch_dims(case)
+        return {"bytes": sum(_read(d) + 32 * d[4] for d in dims),
+                "flops": FLOP_PER_TERM * sum(_terms(d) for d in dims)}
+    d = _dims(case)
+    nb, _, ng, np_, nw = d
+    grads = 16 * (2 * nb * ng + 2 * np_ * ng)
+    w = {"bytes": _read(d) + 32 * nw, "flops": FLOP_PER_TERM * _terms(d)}
+    if entry == "bwd":
+        w = {"bytes": _read(d) + 32 * nw + grads, "flops": FLOP_PER_TERM_BWD * _terms(d)}
+    if entry == "autograd":
+        w = {"bytes": w["bytes"] + _read(d) + 32 * nw + grads,
+             "flops": (FLOP_PER_TERM + FLOP_PER_TERM_BWD) * _terms(d)}
+    return w
+
+
+# ---- plain evaluation in 64 bits ------------------------------------------
+
+def _plain(t, nv, nw, ga=None, gs=None):
+    """achtemp, asxtemp by torch's own complex arithmetic, and with ga, gs the
+    gradients of Re(conj(ga) achtemp + conj(gs) asxtemp) as well."""
+    am, an, ie, wt, vc, wx = (t[k].detach() for k in (
+        "aqsmtemp", "aqsntemp", "I_eps_array", "wtilde_array", "vcoul", "wx_array"))
+    nb, ng = an.shape
+    np_ = ie.shape[0]
+    ach, asx = (torch.zeros(nw, dtype=C128, device=DEV) for _ in range(2))
+    back = ga is not None
+    g = [torch.zeros_like(v) for v in (am, an, ie, wt)] if back else None
+    room = 4_000_000 if back else 24_000_000
+    pc = max(1, min(np_, room // ng))
+    nc = max(1, min(nb, room // (ng * pc)))
+    vc = vc.to(C128)
+    for p0 in range(0, np_, pc):
+        om, e = wt[p0:p0 + pc], ie[p0:p0 + pc]
+        wi2 = om.imag * om.imag
+        wtr = om.real * om.real + wi2
+        for n0 in range(0, nb, nc):
+            a, b = an[n0:n0 + nc], am[n0:n0 + nc, p0:p0 + pc]
+            m = a[:, None, :] * b.conj()[:, :, None]
+            occ = torch.arange(n0, min(nb, n0 + nc), device=DEV) < nv
+            if back:
+                ge, gw = torch.zeros_like(m), torch.zeros_like(m)
+            for w in range(nw):
+                x = wx[w, n0:n0 + nc, None, None]
+                dr = x - om.real
+                wd = dr * dr + wi2
+                is_a = (wd > 0.25) & (wtr < 250000.0 * wd)
+                d = torch.where(is_a, x - om, 1.0)
+                sch = torch.where(is_a, om / d, 0.0)
+                ach[w] += 0.5 * torch.sum(vc * e * m * sch)
+                if back:
+                    dsch = torch.where(is_a, x / (d * d), 0.0)
+                    k = 0.5 * ga[w]
+                    ge += k.conj() * sch  # conjugated throughout, once at the end
+                    gw += k.conj() * dsch
+                if occ.any():
+                    s = x + om
+                    is_b = ~is_a & (wtr > 1e-12 * wd)
+                    s = torch.where(is_a | is_b, s, 1.0)
+                    ssx = torch.where(is_a, om * om / (d * s), torch.where(is_b, -om / (2 * s), 0.0))
+                    ssx = ssx * occ[:, None, None]
+                    asx[w] += torch.sum(vc * e * m * ssx)
+                    if back:
+                        ds = torch.where(is_a, 2 * om * x * x / (d * s).square(),
+                                         torch.where(is_b, -x / (2 * s * s), 0.0))
+                        ge += gs[w].conj() * ssx
+                        gw += gs[w].conj() * ds * occ[:, None, None]
+            if back:
+                z = vc * e * ge
+                g[0][n0:n0 + nc, p0:p0 + pc] += torch.sum(a[:, None, :] * z, dim=2)
+                g[1][n0:n0 + nc] += torch.sum(b.conj()[:, :, None] * z, dim=1).conj()
+                g[2][p0:p0 + pc] += torch.sum(vc * m * ge, dim=0).conj()
+                g[3][p0:p0 + pc] += torch.sum(vc * e * m * gw, dim=0).conj()
+    return ach, asx, g
+
+
+def exact(case, seed):
+    entry, nw = case["entry"], case["nw"]
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(int(seed))
+    if entry == "batched":
+        dims, states = _batch_inputs(case, gen)
+        if sum(_terms(d) for d in dims) > EXACT_TERMS:
+            return None
+        got = [_plain(t, d[1], nw)[:2] for d, t in zip(dims, states)]
+        return torch.stack([a for a, _ in got]), torch.stack([x for _, x in got])
+    back = entry in ("autograd", "bwd")
+    if _terms(_dims(case)) > (EXACT_TERMS_BWD if back else EXACT_TERMS):
+        return None
+    t = _inputs(case, gen)
+    if not back:
+        ach, asx, _ = _plain(t, case["nv"], nw)
+        if entry != "qp":
+            return ach, asx
+        m = (nw - 1) // 2
+        sig = ach - asx
+        ds = (sig[m + 1] - sig[m - 1]) / 1.0
+        z = 1.0 / (1.0 - ds.real)
+        e_qp = 0.25 + z * (sig[m].real + 0.25)
+        return ach, asx, torch.stack([sig[m].real, sig[m].imag, ds.real, ds.imag, z, e_qp])
+    ach, asx, g = _plain(t, case["nv"], nw, *_gradients_of_the_loss(gen, nw))
+    return tuple(g) if entry == "bwd" else (ach, asx) + tuple(g)
