@@ -283,11 +283,12 @@ def _plain(t, nv, nw, ga=None, gs=None):
     nc = max(1, min(nb, room // (ng * pc)))
     vc = vc.to(C128)
     for p0 in range(0, np_, pc):
-        om, e = wt[p0:p0 + pc], ie[p0:p0 + pc]
+        p1 = min(np_, p0 + pc)
+        om, e = wt[p0:p1], ie[p0:p1]
         wi2 = om.imag * om.imag
         wtr = om.real * om.real + wi2
         for n0 in range(0, nb, nc):
-            a, b = an[n0:n0 + nc], am[n0:n0 + nc, p0:p0 + pc]
+            a, b = an[n0:n0 + nc], am[n0:n0 + nc, p0:p1]
             m = a[:, None, :] * b.conj()[:, :, None]
             occ = torch.arange(n0, min(nb, n0 + nc), device=DEV) < nv
             if back:
@@ -319,10 +320,10 @@ def _plain(t, nv, nw, ga=None, gs=None):
                         gw += gs[w].conj() * ds * occ[:, None, None]
             if back:
                 z = vc * e * ge
-                g[0][n0:n0 + nc, p0:p0 + pc] += torch.sum(a[:, None, :] * z, dim=2)
+                g[0][n0:n0 + nc, p0:p1] += torch.sum(a[:, None, :] * z, dim=2)
                 g[1][n0:n0 + nc] += torch.sum(b.conj()[:, :, None] * z, dim=1).conj()
-                g[2][p0:p0 + pc] += torch.sum(vc * m * ge, dim=0).conj()
-                g[3][p0:p0 + pc] += torch.sum(vc * e * m * gw, dim=0).conj()
+                g[2][p0:p1] += torch.sum(vc * m * ge, dim=0).conj()
+                g[3][p0:p1] += torch.sum(vc * e * m * gw, dim=0).conj()
     return ach, asx, g
 
 
