@@ -34,11 +34,16 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result", f"-I{INCLUDE}", f"-I{CSRC}",
 ]
+# The forward's tile loop asks for the next group's values ahead of its
+# arithmetic; with machine sinking on, the compiler moves those loads back
+# behind a branch, right before their use.
+EXTRA_FLAGS = {src: ["-mllvm", "-disable-machine-sink"]
+               for src in ("gpp_fwd.hip", "gpp_batched.hip")}
 
 
 def _compile(src: str, verbose: bool, objdir: str = OBJDIR, defines=()) -> str:
     obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *EXTRA_FLAGS.get(src, []), *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

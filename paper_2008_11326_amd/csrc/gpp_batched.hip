@@ -106,16 +106,10 @@ __device__ __forceinline__ void state_tile(const StateDesc &d, long local, int l
     const int npt = (d.np + C - 1) / C;
     const int gt = (int)(local / npt);
     const int pt = (int)(local - (long)gt * npt);
-    if (C == 1) {
-        fwd_tile_body<NW, BU>(d.nb, d.nv, 0, d.nb, d.ng, pt, gt, lane, as_global(d.aqsm),
-                              as_global(d.aqsn), as_global(d.ieps), as_global(d.wt),
-                              as_global(d.vcoul), as_global(d.wx), a, x);
-    } else {
-        fwd_tile_body_cols<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
-                                      as_global(d.aqsm), as_global(d.aqsn), as_global(d.ieps),
-                                      as_global(d.wt), as_global(d.vcoul), as_global(d.wx), a,
-                                      x);
-    }
+    fwd_tile_body<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
+                                  as_global(d.aqsm), as_global(d.aqsn), as_global(d.ieps),
+                                  as_global(d.wt), as_global(d.vcoul), as_global(d.wx), a,
+                                  x);
 }
 
 // Register caps: two-column tiles (up to three frequencies) at 3 waves per
@@ -253,7 +247,7 @@ batched_queue(const StateDesc *__restrict__ st, int nstates, long nchunks, int c
 }
 
 // Flat form (not persistent): one wave per tile of the plain forward's own
-// shape (fwd_cols(NW) G' columns x 64 rows, fwd_tile_body_cols), four
+// shape (fwd_cols(NW) G' columns x 64 rows, fwd_tile_body), four
 // consecutive tiles of one state per workgroup, each state's tiles padded to
 // whole workgroups.  Here chunk_begin is a state's first workgroup:
 // workgroup wg finds its state by binary search, and writes one partial row
@@ -302,16 +296,10 @@ batched_flat(const StateDesc *__restrict__ st, int nstates, double *__restrict__
     if (local < ntile) {
         int gt, pt, ck;
         tile_coords(local, npt, (d.ng + kWave - 1) / kWave, 1, gt, pt, ck);
-        if (C == 1) {
-            fwd_tile_body<NW, BU>(d.nb, d.nv, 0, d.nb, d.ng, pt, gt, lane, as_global(d.aqsm),
-                                  as_global(d.aqsn), as_global(d.ieps), as_global(d.wt),
-                                  as_global(d.vcoul), as_global(d.wx), ach, asx);
-        } else {
-            fwd_tile_body_cols<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
-                                          as_global(d.aqsm), as_global(d.aqsn),
-                                          as_global(d.ieps), as_global(d.wt),
-                                          as_global(d.vcoul), as_global(d.wx), ach, asx);
-        }
+        fwd_tile_body<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
+                                      as_global(d.aqsm), as_global(d.aqsn),
+                                      as_global(d.ieps), as_global(d.wt),
+                                      as_global(d.vcoul), as_global(d.wx), ach, asx);
     }
     // wave then workgroup sums in a fixed order (row layout as the other forms)
 #pragma unroll

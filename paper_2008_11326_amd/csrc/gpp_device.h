@@ -113,35 +113,69 @@ __device__ __forceinline__ double rcp_batch(double d) {
 }
 
 // Batch inversion: r[k] = 1/d[k] for K positive values from one reciprocal
-// of their product.  Prefix products c[k] = d[0]...d[k]; then R = 1/c[K-1]
-// and, walking back, r[k] = R c[k-1] and R <- R d[k].  Costs 3(K-1)
-// multiplies plus one rcp_batch instead of K reciprocals; each r[k] carries
-// the error of R plus at most 2K roundings.  The batch path needs every d[k] >= 2^-60 (so that no
-// prefix product, K <= 12, leaves the normal range at the bottom; callers
-// pass batch_ok = false for a lane without that bound) and c[K-1] < 2^1000
-// (an overflowed prefix stays infinite, so this also covers the middle
-// ones).  Other lanes take the one-by-one path; a zero there gives an
-// infinite or NaN reciprocal, which callers mask.
+// of their product.  The values go in two halves, each with its own prefix
+// products c[k]; with R = 1 / (product of all), R times the other half's
+// product is the reciprocal of a half's product, and walking a half back,
+// r[k] = R c[k-1] and R <- R d[k].  Two halves cost the same 3(K-1)
+// multiplies as one run over all K, with half the serial chain.  Each r[k]
+// carries the error of R plus at most 2K roundings.  The batch path needs
+// every d[k] >= 2^-60 (so that no product of up to 12 leaves the normal
+// range at the bottom; callers pass batch_ok = false for a lane without that
+// bound) and a total product below 2^1000 (an overflowed prefix stays
+// infinite, so this also covers the prefixes).  batch_prefix forms the prefix
+// products and returns the total, batch_back the r[k]; where a lane of the
+// wave fails one of the bounds (batch_misses, one scalar test), every lane
+// inverts one by one instead (one_by_one); a zero there gives an infinite or
+// NaN reciprocal, which callers mask.
+template <int K>
+__device__ __forceinline__ double batch_prefix(const double (&d)[K], double (&c)[K]) {
+    static_assert(K <= 12, "the 2^-60 lane bound keeps products of at most 12 factors normal");
+    constexpr int H = (K + 1) / 2;  // the first half's length
+    c[0] = d[0];
+    if constexpr (K > 1) c[H] = d[H];
+#pragma unroll
+    for (int k = 1; k < H; ++k) {  // one step of each half
+        c[k] = c[k - 1] * d[k];
+        if (H + k < K) c[H + k] = c[H + k - 1] * d[H + k];
+    }
+    return K > 1 ? c[H - 1] * c[K - 1] : c[0];
+}
+template <int K>
+__device__ __forceinline__ void batch_back(const double (&d)[K], const double (&c)[K], double all,
+                                           double (&r)[K]) {
+    constexpr int H = (K + 1) / 2;
+    const double R = rcp_batch(all);
+    double ra = K > 1 ? R * c[K - 1] : R, rb = R * c[H - 1];
+#pragma unroll
+    for (int k = H - 1; k > 0; --k) {
+        if (H + k < K) {
+            r[H + k] = rb * c[H + k - 1];
+            rb = rb * d[H + k];
+        }
+        r[k] = ra * c[k - 1];
+        ra = ra * d[k];
+    }
+    r[0] = ra;
+    if constexpr (K > 1) r[H] = rb;
+}
+// The lanes whose batch of product `all` may not be used; narrow = the lanes
+// (as a wave mask) with a denominator that may be below 2^-60.
+__device__ __forceinline__ uint64_t batch_misses(double all, uint64_t narrow) {
+    return __builtin_amdgcn_ballot_w64(!(all < 0x1p1000)) | narrow;
+}
+template <int K>
+__device__ __forceinline__ void one_by_one(const double (&d)[K], double (&r)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) r[k] = rcp_nr2(d[k]);
+}
 template <int K>
 __device__ __forceinline__ void batch_reciprocal(const double (&d)[K], double (&r)[K],
                                                  bool batch_ok = true) {
-    static_assert(K <= 12, "the 2^-60 lane bound keeps products of at most 12 factors normal");
     double c[K];
-    c[0] = d[0];
-#pragma unroll
-    for (int k = 1; k < K; ++k) c[k] = c[k - 1] * d[k];
-    if (__builtin_expect(batch_ok && c[K - 1] < 0x1p1000, 1)) {
-        double R = rcp_batch(c[K - 1]);
-#pragma unroll
-        for (int k = K - 1; k > 0; --k) {
-            r[k] = R * c[k - 1];
-            R = R * d[k];
-        }
-        r[0] = R;
-    } else {
-#pragma unroll
-        for (int k = 0; k < K; ++k) r[k] = rcp_nr2(d[k]);
-    }
+    const double all = batch_prefix<K>(d, c);
+    batch_back<K>(d, c, all, r);
+    if (__builtin_expect(batch_misses(all, __builtin_amdgcn_ballot_w64(!batch_ok)) != 0, 0))
+        one_by_one<K>(d, r);
 }
 
 // How the hot loops apply the branch-A test to a term.  2: the compare

@@ -78,16 +78,10 @@ fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_ban
         tile_coords(tile, npt, (ng + kWave - 1) / kWave, nchunk, gt, pt, ck);
         const int n_lo = ck * chunk_bands;
         const int n_hi = nb - n_lo < chunk_bands ? nb : n_lo + chunk_bands;
-        if (C == 1) {
-            fwd_tile_body<NW, BU>(nb, nv, n_lo, n_hi, ng, pt, gt, lane, as_global(aqsm),
-                                  as_global(aqsn), as_global(ieps), as_global(wt),
-                                  as_global(vcoul), as_global(wx), ach, asx);
-        } else {
-            fwd_tile_body_cols<NW, BU, C>(nb, nv, n_lo, n_hi, ng, np, C * pt, gt, lane,
-                                          as_global(aqsm), as_global(aqsn), as_global(ieps),
-                                          as_global(wt), as_global(vcoul), as_global(wx), ach,
-                                          asx);
-        }
+        fwd_tile_body<NW, BU, C>(nb, nv, n_lo, n_hi, ng, np, C * pt, gt, lane,
+                                      as_global(aqsm), as_global(aqsn), as_global(ieps),
+                                      as_global(wt), as_global(vcoul), as_global(wx), ach,
+                                      asx);
     }
 
     // wave then workgroup reduction in a fixed order; partial row layout

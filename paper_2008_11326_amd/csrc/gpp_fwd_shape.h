@@ -42,7 +42,7 @@ static_assert(fwd_shapes_fit(), "a forward tile's batch inversion holds at most 
 // spills) 9.5 % and 5.1 % faster than at 130 and 144 (3).  nfreq 1 capped
 // for 6 waves and nfreq 6 for 4 ran 0.9 % and 16 % slower.
 #ifndef GPP_FWD_MIN_WAVES
-#define GPP_FWD_MIN_WAVES 1, 1, 1, 5, 1, 1, 4, 4
+#define GPP_FWD_MIN_WAVES 1, 3, 3, 5, 1, 1, 4, 4
 #endif
 constexpr int kFwdMinWaves[8] = {GPP_FWD_MIN_WAVES};
 constexpr int fwd_min_waves(int nw) { return kFwdMinWaves[nw - 1]; }

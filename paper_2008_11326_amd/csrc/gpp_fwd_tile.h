@@ -6,12 +6,6 @@
 
 #include "gpp_device.h"
 
-// 1: the columns of a multi-column tile share one batch inversion per band
-// group; 0: one inversion per column.
-#ifndef GPP_FWD_JOINT_INV
-#define GPP_FWD_JOINT_INV 1
-#endif
-
 namespace gpp {
 
 // Column tiles per block of the tile walk: 0 walks each g-tile through all
@@ -61,23 +55,6 @@ __device__ inline void tile_coords(long tile, int npt, int gtiles, int nchunk, i
     ck = __builtin_amdgcn_readfirstlane(ck);
 }
 
-// CH-only accumulation for BU consecutive unoccupied bands starting at n.
-// aqsntemp[n][g] is read through a buffer descriptor for the row (scalar
-// registers) plus the lane's 32-bit byte offset, so the per-band address
-// arithmetic stays on the scalar unit.  The denominators go into the batch
-// inversion unclamped: every one is at least (Im om)^2, and a lane with
-// (Im om)^2 below kMinUnclampedWi2 (wide == false) inverts one by one; a
-// masked term's reciprocal (possibly infinite or NaN there) never reaches
-// the sums (ch_term).
-// The group's aqsntemp values of this lane (one per band).
-template <int BU>
-__device__ __forceinline__ void load_an(int n, int ng, gptr<double2> aqsn, uint32_t goff,
-                                        cplx (&an)[BU])
-{
-#pragma unroll
-    for (int u = 0; u < BU; ++u) an[u] = load_row_elem(aqsn + (size_t)(n + u) * ng, ng, goff);
-}
-
 // an conj(am) for a lane's aqsntemp value and a wave-uniform aqsmtemp
 // value; the sign sits on the uniform factor, so it folds into an operand
 // modifier instead of costing a vector instruction.
@@ -86,144 +63,116 @@ __device__ __forceinline__ cplx qm_of(cplx an, cplx am) {
     return cmake(fma(an.re, am.re, an.im * am.im), fma(an.im, am.re, an.re * nai));
 }
 
-// One Coulomb-hole term: P1 += r x qm and P2 += r qm when the term is on
-// branch A (isA).  With GPP_EXEC_MASK the test is the wave's execution mask
-// around the accumulation, laid out as the common case so that no skip
-// branch is emitted; otherwise the reciprocal is cleared with mask_keep.
-__device__ __forceinline__ void ch_term(bool isA, double r, double x, cplx qm, cplx &P1,
-                                        cplx &P2) {
-#if GPP_EXEC_MASK
-    if (__builtin_expect(isA, 1)) {
-        const double rx = r * x;
-        P1.re = fma(rx, qm.re, P1.re);
-        P1.im = fma(rx, qm.im, P1.im);
-        P2.re = fma(r, qm.re, P2.re);
-        P2.im = fma(r, qm.im, P2.im);
-    }
-#else
-    const double re = mask_keep(isA, r);
-    const double rx = re * x;
-    P1.re = fma(rx, qm.re, P1.re);
-    P1.im = fma(rx, qm.im, P1.im);
-    P2.re = fma(re, qm.re, P2.re);
-    P2.im = fma(re, qm.im, P2.im);
-#endif
-}
-
-// ch_term on the denominator d against the branch-A threshold thr.  With
-// GPP_EXEC_MASK == 2 the compare writes the execution mask itself
-// (v_cmpx), so the term's five vector instructions wait on one vector
-// result instead of a compare, a scalar mask update and the exec write;
-// the mask is restored before the block ends.
-__device__ __forceinline__ void ch_term_dt(double d, double thr, double r, double x, cplx qm,
-                                           cplx &P1, cplx &P2) {
-#if GPP_EXEC_MASK == 2
-    unsigned long long saved;
+// One Coulomb-hole term with denominator d and reciprocal r: P1 += r x qm
+// and P2 += r qm where d > thr (branch A).  The compare writes the wave's
+// execution mask (v_cmpx) around the accumulation, so a masked term adds
+// nothing and no select is spent; the mask goes back to all 64 lanes, which
+// every caller has active (the tile bodies run whole waves).
+__device__ __forceinline__ void ch_term(double d, double thr, double r, double x, cplx qm,
+                                        cplx &P1, cplx &P2) {
     double rx;
     // Not volatile: the block touches no memory and restores exec, and a
     // volatile block would count as a possible store, which keeps the
     // compiler from turning later wave-uniform loads into scalar loads.
-    asm(
-        "s_mov_b64 %[sv], exec\n\t"
-        "v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+    asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
         "v_mul_f64 %[rx], %[r], %[x]\n\t"
         "v_fma_f64 %[p2r], %[r], %[qr], %[p2r]\n\t"
         "v_fma_f64 %[p2i], %[r], %[qi], %[p2i]\n\t"
         "v_fma_f64 %[p1r], %[rx], %[qr], %[p1r]\n\t"
         "v_fma_f64 %[p1i], %[rx], %[qi], %[p1i]\n\t"
-        "s_mov_b64 exec, %[sv]"
-        : [sv] "=&s"(saved), [rx] "=&v"(rx), [p1r] "+v"(P1.re), [p1i] "+v"(P1.im),
-          [p2r] "+v"(P2.re), [p2i] "+v"(P2.im)
+        "s_mov_b64 exec, -1"
+        : [rx] "=&v"(rx), [p1r] "+v"(P1.re), [p1i] "+v"(P1.im), [p2r] "+v"(P2.re),
+          [p2i] "+v"(P2.im)
         : [d] "v"(d), [thr] "v"(thr), [r] "v"(r), [x] "s"(x), [qr] "v"(qm.re), [qi] "v"(qm.im)
         : "vcc");
-#else
-    ch_term(d > thr, r, x, qm, P1, P2);
-#endif
 }
 
-template <int NW, int BU>
-__device__ __forceinline__ void ch_group_an(int n, int nb, int ng, const cplx (&an)[BU],
-                                            gptr<double2> am_col, gptr<double> wx, double a,
-                                            double wi2, double thr, bool wide, cplx (&P1)[NW],
-                                            cplx (&P2)[NW])
-{
-    constexpr int K = BU * NW;
-    cplx qm[BU];
-    double xs[K], d[K], r[K];
-#pragma unroll
-    for (int u = 0; u < BU; ++u) {
-        qm[u] = qm_of(an[u], cload(am_col + (size_t)(n + u) * ng));
-#pragma unroll
-        for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double dr = xs[k] - a;
-        d[k] = fma(dr, dr, wi2);
-    }
-    batch_reciprocal<K>(d, r, wide);
-#pragma unroll
-    for (int u = 0; u < BU; ++u)
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const int k = u * NW + w;
-            ch_term_dt(d[k], thr, r[k], xs[k], qm[u], P1[w], P2[w]);
-        }
-}
-
-// As ch_group_an for NC columns at once: the BU*NW*NC denominators of the
-// group share one batch inversion, which takes NC-1 fewer hardware
-// reciprocals and Newton steps for NC-1 more multiplies per link of the
-// prefix chain.  wide must hold for every column of the lane.
+// Coulomb-hole sums of NC columns over the whole groups of BU unoccupied
+// bands in [n, n_hi); returns the first band left over.  The BU*NW*NC
+// denominators of a group share one batch inversion; they go in unclamped:
+// every one is at least (Im om)^2, and where a lane has a column with
+// (Im om)^2 below kMinUnclampedWi2 (the wave mask `narrow`) the wave inverts
+// one by one; a masked term's reciprocal (possibly infinite or NaN there)
+// never reaches the sums (ch_term).
+// Loads run ahead of their use, so that no wait sits in front of a group's
+// arithmetic: the frequencies of the next group are asked for together with
+// this group's aqsmtemp values, which are needed only after the reciprocals;
+// the next group's aqsntemp rows are asked for once this group's have gone
+// into the products.  aqsntemp[n][g] is read through a buffer descriptor of
+// the row (scalar registers) plus the lane's 32-bit byte offset, so the
+// address arithmetic stays on the scalar unit.
+// With the loads ahead and the inversion in two halves (gpp_device.h), against
+// loads waited for in front of each group's arithmetic: 8192 rows x 409
+// columns x 256 bands at nfreq 8 2.82 -> 2.72 ms; 4096 x 204 x 128 at nfreq 3
+// 1.8 % faster; 32768 x 1638 x 512 unchanged and 65536 x 3276 x 1024 0.7 %
+// faster, as those sit at the part's power limit (a register-only loop of the
+// same instructions reaches 4.3e10 wave-terms per second, these 3.95e10).
 template <int NW, int BU, int NC>
-__device__ __forceinline__ void ch_group_cols(int n, int nb, int ng, const cplx (&an)[BU],
-                                              gptr<double2> aqsm, const int (&pc)[NC],
-                                              gptr<double> wx, const double (&a)[NC],
-                                              const double (&wi2)[NC], const double (&thr)[NC],
-                                              bool wide, cplx (&P1)[NC][NW],
-                                              cplx (&P2)[NC][NW])
+__device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<double2> aqsn,
+                                        uint32_t goff, gptr<double2> aqsm, const int (&pc)[NC],
+                                        gptr<double> wx, const double (&a)[NC],
+                                        const double (&wi2)[NC], const double (&thr)[NC],
+                                        uint64_t narrow, cplx (&P1)[NC][NW], cplx (&P2)[NC][NW])
 {
     constexpr int KB = BU * NW;  // terms of one column
     constexpr int K = NC * KB;
-    double xs[KB], d[K], r[K];
-    cplx qm[NC][BU];
+    if (n + BU > n_hi) return n;
+    cplx an[BU];
+    double xs[KB];
 #pragma unroll
     for (int u = 0; u < BU; ++u) {
+        an[u] = load_row_elem(aqsn + (size_t)(n + u) * ng, ng, goff);
 #pragma unroll
         for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
+    }
+    for (;;) {
+        // the last group asks for its own values again
+        const int nx = n + 2 * BU <= n_hi ? n + BU : n;
+        cplx am[NC][BU];
+        double xn[KB];
+#pragma unroll
+        for (int u = 0; u < BU; ++u) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) am[c][u] = cload(aqsm + pc[c] + (size_t)(n + u) * ng);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) xn[u * NW + w] = wx[(size_t)w * nb + nx + u];
+        }
+        double d[K], r[K];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                const double dr = xs[k] - a[c];
+                d[c * KB + k] = fma(dr, dr, wi2[c]);
+            }
+        }
+        double c[K];
+        const double all = batch_prefix<K>(d, c);
+        batch_back<K>(d, c, all, r);
+        if (__builtin_expect(batch_misses(all, narrow) != 0, 0)) one_by_one<K>(d, r);
+        cplx qm[NC][BU];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            qm[c][u] = qm_of(an[u], cload(aqsm + pc[c] + (size_t)(n + u) * ng));
-    }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-#pragma unroll
-        for (int k = 0; k < KB; ++k) {
-            const double dr = xs[k] - a[c];
-            d[c * KB + k] = fma(dr, dr, wi2[c]);
-        }
-    }
-    batch_reciprocal<K>(d, r, wide);
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
+            for (int u = 0; u < BU; ++u) qm[c][u] = qm_of(an[u], am[c][u]);
 #pragma unroll
         for (int u = 0; u < BU; ++u)
+            an[u] = load_row_elem(aqsn + (size_t)(nx + u) * ng, ng, goff);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const int k = c * KB + u * NW + w;
-                ch_term_dt(d[k], thr[c], r[k], xs[u * NW + w], qm[c][u], P1[c][w], P2[c][w]);
-            }
-}
-
-template <int NW, int BU>
-__device__ __forceinline__ void ch_group(int n, int nb, int ng, gptr<double2> aqsn,
-                                         uint32_t goff, gptr<double2> am_col,
-                                         gptr<double> wx, double a, double wi2, double thr,
-                                         bool wide, cplx (&P1)[NW], cplx (&P2)[NW])
-{
-    cplx an[BU];
-    load_an<BU>(n, ng, aqsn, goff, an);
-    ch_group_an<NW, BU>(n, nb, ng, an, am_col, wx, a, wi2, thr, wide, P1, P2);
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int u = 0; u < BU; ++u)
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const int k = u * NW + w;
+                    ch_term(d[c * KB + k], thr[c], r[c * KB + k], xs[k], qm[c][u], P1[c][w],
+                            P2[c][w]);
+                }
+        if (nx == n) return n + BU;
+        n = nx;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) xs[k] = xn[k];
+    }
 }
 
 // Frequencies W0 .. W0+G-1 of one occupied band (see occupied_bands).
@@ -322,81 +271,17 @@ __device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng,
     }
 }
 
-// One tile: lane g = gt*64 + lane of column p, bands n_lo <= n < n_hi.  On
-// return ach[w] holds this lane's Coulomb-hole contribution (still to be
-// summed over the wave) and asx[w] the wave's screened-exchange total
-// (wave-uniform).  Must be called by all 64 lanes of a wave together (wave
-// reductions inside).
-template <int NW, int BU>
-__device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi, int ng, int p,
-                                              int gt, int lane,
-                                              gptr<double2> aqsm, gptr<double2> aqsn,
-                                              gptr<double2> ieps, gptr<double2> wt,
-                                              gptr<double> vcoul, gptr<double> wx,
-                                              cplx (&ach)[NW], cplx (&asx)[NW])
-{
-    const int g = gt * kWave + lane;
-    const bool valid = g < ng;
-    const int gc = valid ? g : ng - 1;  // clamped, contribution zeroed
-
-    const cplx om = cload(wt + (size_t)p * ng + gc);
-    const double a = om.re, b = om.im;
-    const double wi2 = b * b;
-    const double wtr = fma(a, a, wi2);
-    const double thr = branch_a_threshold(wtr);
-
-    cplx P1[NW], P2[NW], SX[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) P1[w] = P2[w] = SX[w] = cmake(0.0, 0.0);
-
-    const gptr<double2> an_col = aqsn + gc;
-    const gptr<double2> am_col = aqsm + p;
-    const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
-    const cplx e = cload(ieps + (size_t)p * ng + gc);
-    const double v = valid ? vcoul[gc] : 0.0;
-    const cplx ev = cscale(v, e);
-
-    // occupied bands: screened exchange (SX) and Coulomb hole (CH)
-    const int occ_hi = nv < n_hi ? nv : n_hi;
-    occupied_bands<NW>(n_lo, occ_hi, nb, ng, an_col, am_col, wx, om, wi2, wtr, thr, P1, P2, SX);
-    // The exchange sums are finished here and reduced over the wave into
-    // scalar registers, so they hold no vector registers in the hot loop.
-    if (occ_hi > n_lo) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const cplx t = cmul(ev, SX[w]);
-            asx[w] = cmake(wave_sum_uniform(t.re), wave_sum_uniform(t.im));
-        }
-    } else {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) asx[w] = cmake(0.0, 0.0);
-    }
-
-    // unoccupied bands: CH only -- the hot loop
-    const bool wide = wi2 >= kMinUnclampedWi2;
-    int n = nv > n_lo ? nv : n_lo;
-    for (; n + BU <= n_hi; n += BU)
-        ch_group<NW, BU>(n, nb, ng, aqsn, goff, am_col, wx, a, wi2, thr, wide, P1, P2);
-    for (; n < n_hi; ++n)
-        ch_group<NW, 1>(n, nb, ng, aqsn, goff, am_col, wx, a, wi2, thr, wide, P1, P2);
-
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        // S = om P1 - wtr P2
-        cplx S = cmul(om, P1[w]);
-        S.re = fma(-wtr, P2[w].re, S.re);
-        S.im = fma(-wtr, P2[w].im, S.im);
-        ach[w] = cscale(0.5, cmul(ev, S));
-    }
-}
-
 // NC consecutive G' columns p0 .. p0+NC-1 of one 64-row tile per wave,
 // bands n_lo <= n < n_hi: each aqsntemp element a lane loads serves all of
 // them, which divides the vector-memory traffic of the hot loop by NC.
-// Columns at or beyond np repeat p0 and their contribution is dropped.
-// Outputs as fwd_tile_body, for the NC columns together.
+// Columns at or beyond np repeat p0 and their contribution is dropped.  On
+// return ach[w] holds this lane's Coulomb-hole contribution of the columns
+// (still to be summed over the wave) and asx[w] the wave's screened-exchange
+// total (wave-uniform).  All 64 lanes of the wave must call it together
+// (wave reductions and full execution masks inside); lane l takes row
+// g = gt*64 + l.
 template <int NW, int BU, int NC>
-__device__ __forceinline__ void fwd_tile_body_cols(int nb, int nv, int n_lo, int n_hi, int ng,
+__device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi, int ng,
                                                    int np, int p0, int gt, int lane,
                                                    gptr<double2> aqsm,
                                                    gptr<double2> aqsn, gptr<double2> ieps,
@@ -457,43 +342,17 @@ __device__ __forceinline__ void fwd_tile_body_cols(int nb, int nv, int n_lo, int
         for (int w = 0; w < NW; ++w) asx[w] = cmake(0.0, 0.0);
     }
 
-    // unoccupied bands: CH only
-    int n = nv > n_lo ? nv : n_lo;
-#if GPP_FWD_JOINT_INV
+    // unoccupied bands: CH only, whole groups, then band by band
     bool wide_all = true;
 #pragma unroll
     for (int c = 0; c < NC; ++c) wide_all = wide_all && wide[c];
-    for (; n + BU <= n_hi; n += BU) {
-        cplx an[BU];
-        load_an<BU>(n, ng, aqsn, goff, an);
-        ch_group_cols<NW, BU, NC>(n, nb, ng, an, aqsm, pc, wx, a, wi2, thr, wide_all, P1, P2);
-    }
-    for (; n < n_hi; ++n) {
-        cplx an[1];
-        load_an<1>(n, ng, aqsn, goff, an);
-        ch_group_cols<NW, 1, NC>(n, nb, ng, an, aqsm, pc, wx, a, wi2, thr, wide_all, P1, P2);
-    }
-#else
-    for (; n + BU <= n_hi; n += BU) {
-        cplx an[BU];
-        load_an<BU>(n, ng, aqsn, goff, an);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            ch_group_an<NW, BU>(n, nb, ng, an, aqsm + pc[c], wx, a[c], wi2[c], thr[c], wide[c],
-                                P1[c], P2[c]);
-            // one column's reciprocal chain at a time (register pressure)
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    for (; n < n_hi; ++n) {
-        cplx an[1];
-        load_an<1>(n, ng, aqsn, goff, an);
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            ch_group_an<NW, 1>(n, nb, ng, an, aqsm + pc[c], wx, a[c], wi2[c], thr[c], wide[c],
-                               P1[c], P2[c]);
-    }
-#endif
+    const uint64_t narrow = __builtin_amdgcn_ballot_w64(!wide_all);
+    int n = nv > n_lo ? nv : n_lo;
+    n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, P1,
+                             P2);
+    if constexpr (BU > 1)
+        ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, P1,
+                            P2);
 
 #pragma unroll
     for (int w = 0; w < NW; ++w) ach[w] = cmake(0.0, 0.0);
