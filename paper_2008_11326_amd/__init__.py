@@ -2,7 +2,8 @@
 
 The computation runs in hand-written HIP kernels for gfx950 (libgpp.so,
 include/gpp.h).  This module only marshals torch CUDA tensors (device
-memory and the current stream) into that ABI.
+memory and the current stream) into that ABI: the plain case natively
+(csrc/gpp_binding.cpp), everything it declines through the checks here.
 
     ach, asx = sigma_fwd(aqsmtemp, aqsntemp, I_eps_array, wtilde_array,
                          vcoul, wx_array, nvband)
@@ -85,6 +86,13 @@ def _prepare(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array,
     return dims, ins, dev
 
 
+def _done(r, func):
+    """A native call's results, or the error of the status it returned."""
+    if type(r) is not tuple:
+        _lib.check(r, func)
+    return r
+
+
 def fwd_workspace_bytes(number_bands, nvband, ncouls, ngpown, nfreq) -> int:
     d = _lib.dims_struct(number_bands, nvband, ncouls, ngpown, nfreq)
     return int(_lib.load().gpp_sigma_fwd_workspace(C.byref(d)))
@@ -97,6 +105,10 @@ def sigma_fwd(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array,
     `out` may be a pair of preallocated complex128 [nfreq] tensors and
     `workspace` a uint8 tensor of at least fwd_workspace_bytes(...) bytes;
     `stream` defaults to torch's current stream on the inputs' device."""
+    r = _lib.native().fwd(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array, nvband,
+                          out, workspace, stream)
+    if r is not None:
+        return _done(r, "gpp_sigma_fwd")
     torch = _torch()
     lib = _lib.load()
     dims, ins, dev = _prepare(aqsmtemp, aqsntemp, I_eps_array, wtilde_array,
@@ -127,6 +139,10 @@ def sigma_fwd_noalloc(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_a
     """sigma_fwd through gpp_sigma_fwd_noalloc, which allocates nothing: its
     workspace is a fixed array inside the library (include/gpp.h).  `out`
     must be a pair of preallocated complex128 [nfreq] tensors."""
+    r = _lib.native().fwd_noalloc(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array,
+                                  nvband, out, stream)
+    if r is not None:
+        return _done(r, "gpp_sigma_fwd_noalloc")
     torch = _torch()
     lib = _lib.load()
     dims, ins, dev = _prepare(aqsmtemp, aqsntemp, I_eps_array, wtilde_array,
@@ -150,6 +166,10 @@ def sigma_qp(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array,
     returns (achtemp, asxtemp, qp) with qp a float64 [6] tensor holding
     Sigma(E) re/im, dSigma/dE re/im, Z and E_qp (include/gpp.h).  The nfreq
     (odd) frequencies are energy + (w - (nfreq-1)/2) freq_step."""
+    r = _lib.native().qp(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array, nvband,
+                         freq_step, energy, vxc, out, workspace, stream)
+    if r is not None:
+        return _done(r, "gpp_sigma_qp")
     torch = _torch()
     lib = _lib.load()
     dims, ins, dev = _prepare(aqsmtemp, aqsntemp, I_eps_array, wtilde_array,
@@ -191,6 +211,10 @@ def sigma_bwd(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array,
     grad_wtilde_array), each a complex128 tensor shaped like its input or
     None where `want` is False.  Gradients follow PyTorch's convention
     dL/dRe z + i dL/dIm z for L = sum Re(conj(g) * output)."""
+    r = _lib.native().bwd(aqsmtemp, aqsntemp, I_eps_array, wtilde_array, vcoul, wx_array, nvband,
+                          grad_achtemp, grad_asxtemp, want, workspace, stream)
+    if r is not None:
+        return _done(r, "gpp_sigma_bwd")
     torch = _torch()
     lib = _lib.load()
     dims, ins, dev = _prepare(aqsmtemp, aqsntemp, I_eps_array, wtilde_array,
@@ -285,7 +309,12 @@ class Plan:
         _lib.check(lib.gpp_plan_create(len(self.dims), arr, C.byref(handle)),
                    "gpp_plan_create")
         self._h = handle
+        self._sizes = arr  # what the native call compares the states with
         self.workspace_bytes = int(lib.gpp_plan_workspace(handle))
+
+    def _native_args(self):
+        return (self._h.value if self._h else 0, C.addressof(self._sizes), len(self._sizes),
+                self.workspace_bytes)
 
     def info(self) -> dict:
         inf = _lib.GppPlanInfo()
@@ -313,6 +342,9 @@ def sigma_batched(plan: Plan, states, *, out=None, workspace=None, stream=None):
     """achtemp, asxtemp (complex128 [nstates, nfreq]) for every state via
     gpp_sigma_batched.  `states` is a sequence of dicts (or 6-tuples) of
     CUDA tensors in sigma_fwd's layouts, matching the plan's sizes."""
+    r = _lib.native().batched(*plan._native_args(), states, out, workspace, stream)
+    if r is not None:
+        return _done(r, "gpp_sigma_batched")
     torch = _torch()
     lib = _lib.load()
     if len(states) != len(plan.dims):

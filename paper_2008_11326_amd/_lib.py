@@ -1,8 +1,8 @@
 """ctypes binding of libgpp.so (declared in include/gpp.h).
 
 Argument marshalling only: every step of the computation runs in the HIP
-library.  If the library is not built the import of any entry point fails
-loudly; there is no fallback.
+library.  If the library (or the native side of the binding, _binding.so) is
+not built the import of any entry point fails loudly; there is no fallback.
 """
 from __future__ import annotations
 
@@ -114,6 +114,28 @@ def load():
         fn.argtypes = args
     _lib = lib
     return lib
+
+
+_native = None
+# in the order _binding.bind takes them
+_NATIVE_ENTRIES = ("gpp_sigma_fwd_workspace", "gpp_sigma_fwd", "gpp_sigma_fwd_noalloc",
+                   "gpp_sigma_qp", "gpp_sigma_bwd_workspace", "gpp_sigma_bwd",
+                   "gpp_sigma_batched")
+
+
+def native():
+    """The native side of the binding (csrc/gpp_binding.cpp), bound to the
+    library load() returns."""
+    global _native
+    if _native is not None and _lib is not None:
+        return _native
+    lib = load()
+    import torch
+    from . import _binding
+    _binding.bind(*[C.cast(getattr(lib, n), C.c_void_p).value for n in _NATIVE_ENTRIES],
+                  torch.nn.Parameter)
+    _native = _binding
+    return _native
 
 
 def check(status: int, func: str):
