@@ -79,37 +79,37 @@ __device__ __forceinline__ int find_state(const StateDesc *__restrict__ st, int 
 // Write the wave's running sums (wave-uniform values) into partial row
 // `slot` and clear them.
 template <int NW>
-__device__ __forceinline__ void flush_state(long slot, int lane, cplx (&ach)[NW], cplx (&asx)[NW],
+__device__ __forceinline__ void flush_state(long slot, int lane, RunningSink<NW> &sums,
                                             double *__restrict__ partials)
 {
     if (lane == 0) {
         double *dst = partials + (size_t)slot * (4 * NW);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            dst[4 * w + 0] = ach[w].re;
-            dst[4 * w + 1] = ach[w].im;
-            dst[4 * w + 2] = asx[w].re;
-            dst[4 * w + 3] = asx[w].im;
+            dst[4 * w + 0] = sums.ach[w].re;
+            dst[4 * w + 1] = sums.ach[w].im;
+            dst[4 * w + 2] = sums.asx[w].re;
+            dst[4 * w + 3] = sums.asx[w].im;
         }
     }
-#pragma unroll
-    for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
+    sums.clear();
 }
 
 // The forward work of one tile of state d (its local tile index), as in
 // the plain forward: one or two G' columns x 64 G rows.
 template <int NW, int BU>
 __device__ __forceinline__ void state_tile(const StateDesc &d, long local, int lane,
-                                           cplx (&a)[NW], cplx (&x)[NW])
+                                           RunningSink<NW> &sums)
 {
     constexpr int C = bat_cols(NW);
     const int npt = (d.np + C - 1) / C;
-    const int gt = (int)(local / npt);
+    int gt;
+    if (local < (1L << 31)) gt = (int)((uint32_t)local / (uint32_t)npt);
+    else gt = (int)(local / npt);
     const int pt = (int)(local - (long)gt * npt);
-    fwd_tile_body<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
-                                  as_global(d.aqsm), as_global(d.aqsn), as_global(d.ieps),
-                                  as_global(d.wt), as_global(d.vcoul), as_global(d.wx), a,
-                                  x);
+    fwd_tile_body<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane, as_global(d.aqsm),
+                             as_global(d.aqsn), as_global(d.ieps), as_global(d.wt),
+                             as_global(d.vcoul), as_global(d.wx), sums);
 }
 
 // Register caps: two-column tiles (up to three frequencies) at 3 waves per
@@ -143,36 +143,26 @@ batched_persistent(const StateDesc *__restrict__ st, int nstates, long total_til
     // running sums of the current state, kept wave-uniform (scalar
     // registers): each tile's contribution is summed over the wave as soon
     // as the tile is done, so no vector registers live across tiles
-    cplx ach[NW], asx[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
+    RunningSink<NW> sums;
+    sums.clear();
 
     int s = 0;        // schedule position of the state holding tile t
     long first = -1;  // the wave's first tile of state s (-1: none yet)
     for (long t = t0; t < t_end; t += step) {
         if (t >= st[s + 1].tile_begin) {  // st[nstates].tile_begin == total_tiles
             if (first >= 0)
-                flush_state<NW>(static_slot(st, s, first, xcd_chunks, xcd, per, rem), lane, ach,
-                                asx, partials);
+                flush_state<NW>(static_slot(st, s, first, xcd_chunks, xcd, per, rem), lane, sums,
+                                partials);
             first = -1;
             // the states in between hold none of this wave's tiles
             s = find_state<false>(st, s + 1, nstates, t);
         }
         if (first < 0) first = t;
         const StateDesc d = st[s];
-        cplx a[NW], x[NW];
-        state_tile<NW, BU>(d, t - d.tile_begin, lane, a, x);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            ach[w].re = to_uniform(ach[w].re + wave_sum(a[w].re));
-            ach[w].im = to_uniform(ach[w].im + wave_sum(a[w].im));
-            asx[w].re = to_uniform(asx[w].re + x[w].re);  // x: already wave totals
-            asx[w].im = to_uniform(asx[w].im + x[w].im);
-        }
+        state_tile<NW, BU>(d, t - d.tile_begin, lane, sums);
     }
     if (first >= 0)
-        flush_state<NW>(static_slot(st, s, first, xcd_chunks, xcd, per, rem), lane, ach, asx,
-                        partials);
+        flush_state<NW>(static_slot(st, s, first, xcd_chunks, xcd, per, rem), lane, sums, partials);
 }
 
 // Work-queue form: waves take chunks of chunk_tiles consecutive tiles (never
@@ -219,30 +209,10 @@ batched_queue(const StateDesc *__restrict__ st, int nstates, long nchunks, int c
         const long t0 = d.tile_begin + (c - d.chunk_begin) * chunk_tiles;
         const long tmax = st[s + 1].tile_begin;
         const long t1 = t0 + chunk_tiles < tmax ? t0 + chunk_tiles : tmax;
-        cplx ach[NW], asx[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
-        for (long t = t0; t < t1; ++t) {
-            cplx a[NW], x[NW];
-            state_tile<NW, BU>(d, t - d.tile_begin, lane, a, x);
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                ach[w].re = to_uniform(ach[w].re + wave_sum(a[w].re));
-                ach[w].im = to_uniform(ach[w].im + wave_sum(a[w].im));
-                asx[w].re = to_uniform(asx[w].re + x[w].re);
-                asx[w].im = to_uniform(asx[w].im + x[w].im);
-            }
-        }
-        if (lane == 0) {
-            double *dst = partials + (size_t)c * (4 * NW);
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                dst[4 * w + 0] = ach[w].re;
-                dst[4 * w + 1] = ach[w].im;
-                dst[4 * w + 2] = asx[w].re;
-                dst[4 * w + 3] = asx[w].im;
-            }
-        }
+        RunningSink<NW> sums;
+        sums.clear();
+        for (long t = t0; t < t1; ++t) state_tile<NW, BU>(d, t - d.tile_begin, lane, sums);
+        flush_state<NW>(c, lane, sums, partials);
     }
 }
 
@@ -290,28 +260,16 @@ batched_flat(const StateDesc *__restrict__ st, int nstates, double *__restrict__
     const long ntile = (long)((d.ng + kWave - 1) / kWave) * npt;
     const long local = (wg - d.chunk_begin) * kBatWaves + wid;
 
-    cplx ach[NW], asx[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
+    if (lane < 4 * NW) red[wid][lane] = 0.0;  // the tile may write only some of it
     if (local < ntile) {
         int gt, pt, ck;
         tile_coords(local, npt, (d.ng + kWave - 1) / kWave, 1, gt, pt, ck);
+        RowSink<NW> sink{red[wid], lane};
         fwd_tile_body<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
-                                      as_global(d.aqsm), as_global(d.aqsn),
-                                      as_global(d.ieps), as_global(d.wt),
-                                      as_global(d.vcoul), as_global(d.wx), ach, asx);
+                                 as_global(d.aqsm), as_global(d.aqsn), as_global(d.ieps),
+                                 as_global(d.wt), as_global(d.vcoul), as_global(d.wx), sink);
     }
-    // wave then workgroup sums in a fixed order (row layout as the other forms)
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const double v0 = wave_sum(ach[w].re), v1 = wave_sum(ach[w].im);
-        if (lane == 0) {
-            red[wid][4 * w + 0] = v0;
-            red[wid][4 * w + 1] = v1;
-            red[wid][4 * w + 2] = asx[w].re;  // already wave totals
-            red[wid][4 * w + 3] = asx[w].im;
-        }
-    }
+    // workgroup sums in a fixed order (row layout as the other forms)
     __syncthreads();
     if (threadIdx.x < 4 * NW) {
         double s = 0.0;
@@ -335,27 +293,12 @@ batched_reduce_chunks(const StateDesc *__restrict__ st, const double *__restrict
                       double2 *__restrict__ ach, double2 *__restrict__ asx)
 {
     constexpr int R = 4 * NW;
-    __shared__ double red[4][R];
+    __shared__ double lds[256];
     const int k = blockIdx.x;
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     const long c0 = st[k].chunk_begin, c1 = st[k + 1].chunk_begin;
     const int s = st[k].out_index;
-    double acc[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) acc[j] = 0.0;
-    for (long c = c0 + threadIdx.x; c < c1; c += 256) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) acc[j] += partials[(size_t)c * R + j];
-    }
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const double v = wave_sum(acc[j]);
-        if (lane == 0) red[wid][j] = v;
-    }
-    __syncthreads();
+    const double v = column_sums<R, 256>(partials, c0, c1, lds);
     if (threadIdx.x < R) {
-        const double v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] +
-                         red[3][threadIdx.x];
         const int w = threadIdx.x / 4, c = threadIdx.x % 4;
         double *dst = reinterpret_cast<double *>(c < 2 ? ach + (size_t)s * NW + w
                                                        : asx + (size_t)s * NW + w);

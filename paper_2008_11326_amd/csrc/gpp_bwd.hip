@@ -128,26 +128,6 @@ __global__ void bwd_prepare(int nb, int nw, const double *__restrict__ wx,
     }
 }
 
-// Lane exchange inside a row of 16 lanes (DPP), both halves of a double.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    // every source lane of the controls used here exists, so no lane keeps
-    // an old value (bound_ctrl only matters for lanes outside the row)
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-
-// Sum over each aligned group of 8 lanes; every lane of the group gets it.
-__device__ __forceinline__ double octet_sum(double v)
-{
-    v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]: lane ^ 1
-    v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]: lane ^ 2
-    v += dpp_f64<0x141>(v);  // row_half_mirror: lane i <-> 7 - i within 8
-    return v;
-}
-
 // Order this wave's LDS writes before its later LDS reads (and the reverse)
 // when lanes exchange data through LDS without a workgroup barrier.
 __device__ __forceinline__ void wave_lds_sync()

@@ -225,10 +225,75 @@ __device__ inline bool branch_b_holds(double wtr, double wdiffr) {
     return wtr > kTolZero * wdiffr;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+// Lane exchange inside a row of 16 lanes (DPP), both halves of a double.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    // every source lane of the controls used here exists, so no lane keeps
+    // an old value (bound_ctrl only matters for lanes outside the row)
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over each aligned group of 8 lanes; every lane of the group gets it.
+__device__ __forceinline__ double octet_sum(double v)
+{
+    v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]: lane ^ 1
+    v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]: lane ^ 2
+    v += dpp_f64<0x141>(v);  // row_half_mirror: lane i <-> 7 - i within 8
     return v;
+}
+// Sum over each row of 16 lanes; every lane of the row gets it.
+__device__ __forceinline__ double row_sum(double v)
+{
+    v = octet_sum(v);
+    return v + dpp_f64<0x140>(v);  // row_mirror: lane i <-> 15 - i within 16
+}
+
+// a + b after a's upper 32 lanes and b's lower 32 have changed places: lanes
+// 0-31 get the two halves of a added up, lanes 32-63 those of b.
+__device__ __forceinline__ double add_halves(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// The same between a's odd rows of 16 lanes and b's even ones: rows 0 and 2
+// get a's rows 0 + 1 and 2 + 3, rows 1 and 3 those of b.
+__device__ __forceinline__ double add_rows(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Wave total of v in every lane.
+__device__ __forceinline__ double wave_sum(double v) {
+    v = add_halves(v, v);
+    return row_sum(add_rows(v, v));
+}
+
+// Wave totals of M values (M even): calls put(i, total of v[i]) for each, on
+// one lane each.  The first two steps fold two values into one register
+// instead of exchanging each value with itself (permlane swaps), so that
+// only M/4 registers go through the row sums: 63 vector instructions for 12
+// values, against 18 per value one at a time, or 6 LDS round trips each with
+// __shfl_xor.  Row q of register j ends up with value 4 j + {0, 2, 1, 3}[q].
+template <int M, typename F>
+__device__ __forceinline__ void wave_totals(const double (&v)[M], int lane, F put) {
+    static_assert(M % 2 == 0, "values go in pairs");
+    constexpr int H = M / 2, R = (H + 1) / 2;
+    double h[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k) h[k] = add_halves(v[2 * k], v[2 * k + 1]);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const double t = row_sum(add_rows(h[2 * j], h[2 * j + 1 < H ? 2 * j + 1 : 2 * j]));
+        const int q = lane / 16;
+        const int i = 4 * j + (q == 1 ? 2 : q == 2 ? 1 : q);
+        if (lane % 16 == 0 && i < M) put(i, t);
+    }
 }
 
 // Element at byte offset `off` of a complex row of `len` elements whose
@@ -252,9 +317,6 @@ __device__ __forceinline__ double to_uniform(double t) {
     return __hiloint2double(hi, lo);
 }
 
-// Wave total of v, returned as a wave-uniform (scalar-register) value.
-__device__ __forceinline__ double wave_sum_uniform(double v) { return to_uniform(wave_sum(v)); }
-
 // Map a hardware workgroup id to a logical one so that each of the 8 XCDs
 // (which receive workgroups round-robin) walks a contiguous logical range
 // and its private L2 sees neighbouring tiles.  A bijection on [0, n).
@@ -262,6 +324,50 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t n) {
     const uint32_t kXcd = 8;
     uint32_t x = b % kXcd, i = b / kXcd, per = n / kXcd, rem = n % kXcd;
     return x * per + (x < rem ? x : rem) + i;
+}
+
+// Column sums of the rows [lo, hi) of W doubles by a workgroup of T threads,
+// in a fixed order: thread t adds column t % W of every (T / W)-th row, eight
+// loads in flight, then the T / W row lanes are added through LDS (T doubles)
+// in two steps.  Thread t < W returns column t's sum.
+template <int W, int T>
+__device__ __forceinline__ double column_sums(const double *__restrict__ rows, long lo, long hi,
+                                              double *lds)
+{
+    constexpr int R = T / W, G = R < 8 ? R : 8;
+    static_assert(R >= 1, "a row lane per column at least");
+    const int t = threadIdx.x;
+    double s = 0.0;
+    if (t < R * W) {
+        constexpr long step = R * W;
+        const long end = hi * W;
+        long i = lo * W + t;
+        double a[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] = 0.0;
+        for (; i + 7 * step < end; i += 8 * step) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] += rows[i + k * step];
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+            if (i + k * step < end) a[k] += rows[i + k * step];
+        s = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+        lds[t] = s;
+    }
+    __syncthreads();
+    if (t < G * W) {
+        s = lds[t];
+        for (int k = t + G * W; k < R * W; k += G * W) s += lds[k];
+    }
+    __syncthreads();
+    if (t < G * W) lds[t] = s;
+    __syncthreads();
+    if (t < W) {
+#pragma unroll
+        for (int k = 1; k < G; ++k) s += lds[t + k * W];
+    }
+    return s;
 }
 
 }  // namespace gpp

@@ -37,72 +37,82 @@
 
 namespace gpp {
 
-constexpr int kFwdWaves = 4;
-constexpr int kFwdThreads = kFwdWaves * kWave;
+constexpr int kFwdWaves = 4;      // waves per workgroup of the long form
+constexpr int kSplitWaves = 16;   // and of the split form
+constexpr long kCUs = 256;        // compute units of the MI355X
+constexpr int kRedThreads = 256;  // first reduction stage
+constexpr long kRedBlocks = 512;
+constexpr int kFinalThreads = 1024;
+
 // G' columns per wave tile and bands per batch-inverted group (K = columns
 // x bands x nfreq reciprocals from one hardware reciprocal) come from
 // fwd_cols and fwd_bands, and a cap on VGPRs through a minimum number of
-// waves per SIMD from fwd_min_waves (gpp_internal.h), all chosen by
+// waves per SIMD from fwd_min_waves (gpp_fwd_shape.h), all chosen by
 // measurement on MI355X.  At nfreq 3, two columns per wave let each
-// aqsntemp load serve both: 153 VGPRs when measured, 156 with the
-// divide-free exchange term (3 waves per SIMD either way) with 2-band
-// groups, 2.8-3.1 % faster than one column with 3-band groups (105 VGPRs,
-// 4 waves); three columns need about 200 VGPRs (2 waves) and measured
-// 3-30 % slower.
-constexpr int kRedThreads = 256;
-constexpr long kRedBlocks = 512;  // first reduction stage
+// aqsntemp load serve both: 159 VGPRs (3 waves per SIMD) with 2-band groups,
+// 2.8-3.1 % faster than one column with 3-band groups (4 waves); three
+// columns with 1-band groups at 3 waves measured 6 % slower and four at 2
+// waves 10 % slower, two with 1-band groups at 4 waves 7 % slower.
 
-template <int NW, int BU>
-__global__ void __launch_bounds__(kFwdThreads)
-__attribute__((amdgpu_waves_per_eu(fwd_min_waves(NW))))
-fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_bands,
+// Bands [n_lo, n_hi) of a tile's band chunk for one of 2^shift waves that
+// share the tile.  An occupied band counts as kOccupiedCost others; the cuts
+// between unoccupied bands fall on whole groups of BU.
+template <int BU>
+__device__ __forceinline__ int split_at(int k, int shift, int lo, int occ, int hi)
+{
+    const int cost = hi - lo + (kOccupiedCost - 1) * occ;
+    const int at = (int)(((long)cost * k) >> shift);
+    if (at >= cost) return hi;
+    if (at < kOccupiedCost * occ) return lo + at / kOccupiedCost;
+    return lo + occ + (at - kOccupiedCost * occ) / BU * BU;
+}
+
+// WAVES waves per workgroup, 2^shift of them on one tile (its bands split
+// between them), one partial row per workgroup.  Long grids run 4 waves and
+// shift 0; short ones the split form, 16 waves (fwd_geometry).
+template <int NW, int BU, int C, int WAVES, int MIN_WAVES>
+__global__ void __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(MIN_WAVES)))
+fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_bands, int shift,
           const double2 *__restrict__ aqsm, const double2 *__restrict__ aqsn,
           const double2 *__restrict__ ieps, const double2 *__restrict__ wt,
           const double *__restrict__ vcoul, const double *__restrict__ wx,
           double *__restrict__ partials)
 {
-    __shared__ double red[kFwdWaves][4 * NW];
+    __shared__ double red[WAVES][4 * NW];
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const long tile = (long)xcd_remap(blockIdx.x, gridDim.x) * kFwdWaves + wid;
+    const long wave = (long)xcd_remap(blockIdx.x, gridDim.x) * WAVES + wid;
+    const long tile = WAVES > kFwdWaves ? wave >> shift : wave;
 
-    cplx ach[NW], asx[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
-
+    if (lane < 4 * NW) red[wid][lane] = 0.0;  // the tile may write only some of it
     if (tile < ntiles) {
         // consecutive tiles share a g-tile (and so the same aqsntemp rows)
-        constexpr int C = fwd_cols(NW);
         const int npt = (np + C - 1) / C;  // column tiles per g-tile
         int gt, pt, ck;
         tile_coords(tile, npt, (ng + kWave - 1) / kWave, nchunk, gt, pt, ck);
-        const int n_lo = ck * chunk_bands;
-        const int n_hi = nb - n_lo < chunk_bands ? nb : n_lo + chunk_bands;
-        fwd_tile_body<NW, BU, C>(nb, nv, n_lo, n_hi, ng, np, C * pt, gt, lane,
-                                      as_global(aqsm), as_global(aqsn), as_global(ieps),
-                                      as_global(wt), as_global(vcoul), as_global(wx), ach,
-                                      asx);
+        int n_lo = ck * chunk_bands;
+        int n_hi = nb - n_lo < chunk_bands ? nb : n_lo + chunk_bands;
+        if (WAVES > kFwdWaves) {
+            const int k = (int)wave & ((1 << shift) - 1);
+            const int occ = nv < n_hi ? (nv > n_lo ? nv - n_lo : 0) : n_hi - n_lo;
+            const int lo = n_lo, hi = n_hi;
+            n_lo = split_at<BU>(k, shift, lo, occ, hi);
+            n_hi = split_at<BU>(k + 1, shift, lo, occ, hi);
+        }
+        RowSink<NW> sink{red[wid], lane};
+        if (n_lo < n_hi)
+            fwd_tile_body<NW, BU, C>(nb, nv, n_lo, n_hi, ng, np, C * pt, gt, lane, as_global(aqsm),
+                                     as_global(aqsn), as_global(ieps), as_global(wt),
+                                     as_global(vcoul), as_global(wx), sink);
     }
 
-    // wave then workgroup reduction in a fixed order; partial row layout
+    // the workgroup's row, the waves' rows added in a fixed order; row layout
     // [4 w + 0..3] = achtemp[w].re, .im, asxtemp[w].re, .im
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        // asx[] already holds wave totals (or zeros)
-        const double v0 = wave_sum(ach[w].re), v1 = wave_sum(ach[w].im);
-        const double v2 = asx[w].re, v3 = asx[w].im;
-        if (lane == 0) {
-            red[wid][4 * w + 0] = v0;
-            red[wid][4 * w + 1] = v1;
-            red[wid][4 * w + 2] = v2;
-            red[wid][4 * w + 3] = v3;
-        }
-    }
     __syncthreads();
     if (threadIdx.x < 4 * NW) {
         double s = 0.0;
 #pragma unroll
-        for (int k = 0; k < kFwdWaves; ++k) s += red[k][threadIdx.x];
+        for (int k = 0; k < WAVES; ++k) s += red[k][threadIdx.x];
         partials[(size_t)blockIdx.x * 4 * NW + threadIdx.x] = s;
     }
 }
@@ -136,52 +146,34 @@ __device__ inline void qp_epilogue(const double *fin, const QpArgs &qp)
     }
 }
 
-// Sum rows of W doubles: block b takes rows [b*chunk, (b+1)*chunk), thread
-// t rows t, t+256, ... of it (coalesced: neighbouring threads read
-// neighbouring rows), then a fixed wave/workgroup tree.  With final set,
-// writes the result as achtemp/asxtemp instead of a row, and with qp.out
-// set also the quasiparticle quantities (qp_epilogue).
-template <int NW>
-__global__ void __launch_bounds__(kRedThreads)
+// Column sums of the partial rows: block b adds rows [b*chunk, (b+1)*chunk)
+// into one row of `out`.  With FINAL, one block adds all of them and writes
+// achtemp/asxtemp instead, and with qp.out set also the quasiparticle
+// quantities (qp_epilogue).
+template <int NW, int T, bool FINAL>
+__global__ void __launch_bounds__(T)
 reduce_rows(const double *__restrict__ in, long nrows, long chunk, double *__restrict__ out,
-            double2 *__restrict__ ach, double2 *__restrict__ asx, int final_stage, QpArgs qp)
+            double2 *__restrict__ ach, double2 *__restrict__ asx, QpArgs qp)
 {
     constexpr int W = 4 * NW;
-    __shared__ double red[kRedThreads / kWave][W];
-    __shared__ double fin[W];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    __shared__ double lds[T];
     const long lo = (long)blockIdx.x * chunk;
     const long hi = lo + chunk < nrows ? lo + chunk : nrows;
-    double acc[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) acc[j] = 0.0;
-    for (long i = lo + threadIdx.x; i < hi; i += kRedThreads) {
-        const double *row = in + (size_t)i * W;
-#pragma unroll
-        for (int j = 0; j < W; ++j) acc[j] += row[j];
+    const double s = column_sums<W, T>(in, lo, hi, lds);
+    if constexpr (!FINAL) {
+        if (threadIdx.x < W) out[(size_t)blockIdx.x * W + threadIdx.x] = s;
+        return;
     }
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const double v = wave_sum(acc[j]);
-        if (lane == 0) red[wid][j] = v;
-    }
-    __syncthreads();
+    __syncthreads();  // lds is read above, written below
     if (threadIdx.x < W) {
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < kRedThreads / kWave; ++k) s += red[k][threadIdx.x];
-        if (!final_stage) {
-            out[(size_t)blockIdx.x * W + threadIdx.x] = s;
-        } else {
-            const int w = threadIdx.x / 4, c = threadIdx.x % 4;
-            double *dst = reinterpret_cast<double *>(c < 2 ? ach + w : asx + w);
-            dst[c & 1] = s;
-            fin[threadIdx.x] = s;
-        }
+        const int w = threadIdx.x / 4, c = threadIdx.x % 4;
+        double *dst = reinterpret_cast<double *>(c < 2 ? ach + w : asx + w);
+        dst[c & 1] = s;
+        lds[threadIdx.x] = s;
     }
-    if (final_stage && qp.out) {  // uniform: kernel arguments
+    if (qp.out) {  // uniform: a kernel argument
         __syncthreads();
-        if (threadIdx.x == 0) qp_epilogue<NW>(fin, qp);
+        if (threadIdx.x == 0) qp_epilogue<NW>(lds, qp);
     }
 }
 
@@ -216,6 +208,11 @@ static hipError_t launch_fill_zero(int nw, double2 *a, double2 *b, const QpArgs 
     return hipGetLastError();
 }
 
+// Partial rows that one workgroup of kFinalThreads adds by itself: up to 24
+// loads per thread.  More rows go through a first stage of kRedBlocks
+// workgroups, whose launch costs as much as about that many loads.
+static bool one_stage(int nw, long rows) { return rows * 4 * nw <= 24L * kFinalThreads; }
+
 FwdGeometry fwd_geometry(const Dims32 &d)
 {
     FwdGeometry geo{};
@@ -224,14 +221,43 @@ FwdGeometry fwd_geometry(const Dims32 &d)
     const int cols = fwd_cols(d.nw);
     fwd_band_chunks(d.nb, d.nw, geo.nchunk, geo.chunk_bands);
     geo.ntiles = gtiles * ((d.np + cols - 1) / cols) * geo.nchunk;
+    geo.waves = kFwdWaves;
     geo.nblocks = (geo.ntiles + kFwdWaves - 1) / kFwdWaves;
-    geo.red_blocks = geo.nblocks < kRedBlocks ? geo.nblocks : kRedBlocks;
-    geo.red_chunk = (geo.nblocks + geo.red_blocks - 1) / geo.red_blocks;
+    const long long_rows = geo.nblocks;
+    if (geo.ntiles < kSplitBelow) {
+        // the split form: enough waves per tile to fill the GPU
+        geo.waves = kSplitWaves;
+        while (geo.shift < 3 && (geo.ntiles << geo.shift) < kSplitWaves * kCUs) ++geo.shift;
+        geo.nblocks = ((geo.ntiles << geo.shift) + kSplitWaves - 1) / kSplitWaves;
+    }
+    const bool one = one_stage(d.nw, geo.nblocks);
+    geo.red_blocks = one ? 0 : geo.nblocks < kRedBlocks ? geo.nblocks : kRedBlocks;
+    geo.red_chunk = one ? 0 : (geo.nblocks + geo.red_blocks - 1) / geo.red_blocks;
+    // sized for the long form and its first stage: 2^3 waves per tile and 16
+    // per workgroup make at most twice its rows, and then no first stage
     const size_t row = 4 * sizeof(double) * d.nw;
-    geo.partial_bytes = (size_t)geo.nblocks * row;
-    geo.stage_bytes = (size_t)geo.red_blocks * row;
-    geo.workspace_bytes = geo.partial_bytes + geo.stage_bytes;
+    const long stage_rows = long_rows < kRedBlocks ? long_rows : kRedBlocks;
+    geo.workspace_bytes = (size_t)(long_rows + stage_rows) * row;
     return geo;
+}
+
+template <int NW>
+static hipError_t launch_reduce_nw(const double *partials, long rows, long red_blocks,
+                                   long red_chunk, double *stage, double2 *ach, double2 *asx,
+                                   hipStream_t st, const QpArgs &qp)
+{
+    if (red_blocks > 0) {
+        hipLaunchKernelGGL((reduce_rows<NW, kRedThreads, false>), dim3((unsigned)red_blocks),
+                           dim3(kRedThreads), 0, st, partials, rows, red_chunk, stage, nullptr,
+                           nullptr, QpArgs());
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        partials = stage;
+        rows = red_blocks;
+    }
+    hipLaunchKernelGGL((reduce_rows<NW, kFinalThreads, true>), dim3(1), dim3(kFinalThreads), 0, st,
+                       partials, rows, rows, nullptr, ach, asx, qp);
+    return hipGetLastError();
 }
 
 template <int NW>
@@ -241,19 +267,23 @@ static hipError_t launch_fwd_nw(const Dims32 &d, const FwdGeometry &geo, const D
 {
     double *partials = ws;
     double *stage = ws + (size_t)geo.nblocks * 4 * NW;
-    constexpr int BU = fwd_bands(NW);
-    hipLaunchKernelGGL((fwd_tiles<NW, BU>), dim3((unsigned)geo.nblocks),
-                       dim3(kFwdThreads), 0, st, d.nb, d.nv, d.ng, d.np, geo.ntiles, geo.nchunk,
-                       geo.chunk_bands, in.aqsm, in.aqsn, in.ieps, in.wt, in.vcoul, in.wx,
-                       partials);
-    hipError_t e = hipGetLastError();
+    const dim3 grid((unsigned)geo.nblocks), block((unsigned)(geo.waves * kWave));
+    if (geo.waves == kFwdWaves)
+        hipLaunchKernelGGL((fwd_tiles<NW, fwd_bands(NW), fwd_cols(NW), kFwdWaves,
+                                      fwd_min_waves(NW)>),
+                           grid, block, 0, st, d.nb, d.nv, d.ng, d.np, geo.ntiles, geo.nchunk,
+                           geo.chunk_bands, 0, in.aqsm, in.aqsn, in.ieps, in.wt, in.vcoul, in.wx,
+                           partials);
+    else
+        hipLaunchKernelGGL((fwd_tiles<NW, split_bands(NW), fwd_cols(NW), kSplitWaves,
+                                      kSplitWaves / 4>),
+                           grid, block, 0, st, d.nb, d.nv, d.ng, d.np, geo.ntiles, geo.nchunk,
+                           geo.chunk_bands, geo.shift, in.aqsm, in.aqsn, in.ieps, in.wt, in.vcoul,
+                           in.wx, partials);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_rows<NW>, dim3((unsigned)geo.red_blocks), dim3(kRedThreads), 0,
-                       st, partials, geo.nblocks, geo.red_chunk, stage, ach, asx, 0, QpArgs());
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_rows<NW>, dim3(1), dim3(kRedThreads), 0, st, stage,
-                       geo.red_blocks, geo.red_blocks, nullptr, ach, asx, 1, qp);
-    return hipGetLastError();
+    return launch_reduce_nw<NW>(partials, geo.nblocks, geo.red_blocks, geo.red_chunk, stage, ach,
+                                asx, st, qp);
 }
 
 size_t reduce_stage_bytes(int nw, long nrows)
@@ -262,34 +292,21 @@ size_t reduce_stage_bytes(int nw, long nrows)
     return (size_t)blocks * 4 * sizeof(double) * nw;
 }
 
-template <int NW>
-static hipError_t launch_reduce_nw(const double *partials, long nrows, double *stage,
-                                   double2 *ach, double2 *asx, hipStream_t st)
-{
-    const long blocks = nrows < kRedBlocks ? nrows : kRedBlocks;
-    const long chunk = (nrows + blocks - 1) / blocks;
-    hipLaunchKernelGGL(reduce_rows<NW>, dim3((unsigned)blocks), dim3(kRedThreads), 0, st,
-                       partials, nrows, chunk, stage, ach, asx, 0, QpArgs());
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_rows<NW>, dim3(1), dim3(kRedThreads), 0, st, stage, blocks,
-                       blocks, nullptr, ach, asx, 1, QpArgs());
-    return hipGetLastError();
-}
-
 hipError_t launch_reduce_partials(int nw, const double *partials, long nrows, double *stage,
                                   double2 *ach, double2 *asx, hipStream_t st)
 {
     if (nrows <= 0) return launch_fill_zero(nw, ach, asx, QpArgs(), st);
+    const long blocks = one_stage(nw, nrows) ? 0 : nrows < kRedBlocks ? nrows : kRedBlocks;
+    const long chunk = blocks ? (nrows + blocks - 1) / blocks : 0;
     switch (nw) {
-    case 1: return launch_reduce_nw<1>(partials, nrows, stage, ach, asx, st);
-    case 2: return launch_reduce_nw<2>(partials, nrows, stage, ach, asx, st);
-    case 3: return launch_reduce_nw<3>(partials, nrows, stage, ach, asx, st);
-    case 4: return launch_reduce_nw<4>(partials, nrows, stage, ach, asx, st);
-    case 5: return launch_reduce_nw<5>(partials, nrows, stage, ach, asx, st);
-    case 6: return launch_reduce_nw<6>(partials, nrows, stage, ach, asx, st);
-    case 7: return launch_reduce_nw<7>(partials, nrows, stage, ach, asx, st);
-    case 8: return launch_reduce_nw<8>(partials, nrows, stage, ach, asx, st);
+    case 1: return launch_reduce_nw<1>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 2: return launch_reduce_nw<2>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 3: return launch_reduce_nw<3>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 4: return launch_reduce_nw<4>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 5: return launch_reduce_nw<5>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 6: return launch_reduce_nw<6>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 7: return launch_reduce_nw<7>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
+    case 8: return launch_reduce_nw<8>(partials, nrows, blocks, chunk, stage, ach, asx, st, QpArgs());
     default: return hipErrorInvalidValue;
     }
 }

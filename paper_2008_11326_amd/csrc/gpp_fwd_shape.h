@@ -72,4 +72,18 @@ inline void fwd_band_chunks(int nb, int nw, int &nchunk, int &chunk_bands)
     nchunk = (nb + cb - 1) / cb;
 }
 
+// The split form of the forward's tile kernel, for grids of fewer than
+// kSplitBelow tiles (gpp_fwd.hip).  Bands per batch-inverted group there: a
+// 16-wave workgroup holds its waves to 128 VGPRs.
+#ifndef GPP_FWD_SPLIT_BELOW
+#define GPP_FWD_SPLIT_BELOW 2048
+#endif
+constexpr long kSplitBelow = GPP_FWD_SPLIT_BELOW;
+#ifndef GPP_FWD_SPLIT_BANDS
+#define GPP_FWD_SPLIT_BANDS 4, 1, 1, 2, 2, 1, 1, 1
+#endif
+constexpr int kSplitBands[8] = {GPP_FWD_SPLIT_BANDS};
+constexpr int split_bands(int nw) { return kSplitBands[nw - 1]; }
+constexpr int kOccupiedCost = 3;  // an occupied band's cost in unoccupied ones
+
 }  // namespace gpp

@@ -8,9 +8,8 @@
 
 namespace gpp {
 
-// Column tiles per block of the tile walk: 0 walks each g-tile through all
-// column tiles in turn; Q > 0 walks blocks of Q column tiles through all
-// g-tiles, so that the block's aqsmtemp columns (Q * cols * 16 bytes per
+// Column tiles per block of the tile walk: blocks of Q column tiles go
+// through all g-tiles, so that the block's aqsmtemp columns (Q * cols * 16 bytes per
 // band: 2 MB at 128 two-column tiles and 512 bands, half an XCD's L2) stay
 // in the L2 while the g-tiles' aqsntemp rows stream past, each row fetched
 // once per block.  Measured with band chunks of 512 on MI355X: Q = 128
@@ -28,28 +27,32 @@ namespace gpp {
 // are wave-uniform and made scalar explicitly, since the divisions run on
 // the vector unit and a column index left in vector registers would turn
 // the tile's aqsmtemp loads into vector loads.
-__device__ inline void tile_coords(long tile, int npt, int gtiles, int nchunk, int &gt, int &pt,
-                                   int &ck)
+template <typename Int>
+__device__ __forceinline__ void tile_coords_in(Int tile, int npt, int gtiles, int nchunk, int &gt,
+                                               int &pt, int &ck)
 {
-#if GPP_FWD_COL_BLOCK > 0
     constexpr int Q = GPP_FWD_COL_BLOCK;
-    const long per = (long)Q * gtiles * nchunk;
+    const Int per = (Int)Q * (Int)gtiles * (Int)nchunk;
     const int c = (int)(tile / per);
-    long r = tile - (long)c * per;
+    Int r = tile - (Int)c * per;
     const int c0 = c * Q;
     const int qc = npt - c0 < Q ? npt - c0 : Q;  // the last block may be short
-    const long per_chunk = (long)qc * gtiles;
+    const Int per_chunk = (Int)qc * (Int)gtiles;
     ck = (int)(r / per_chunk);
-    r -= (long)ck * per_chunk;
-    gt = (int)(r / qc);
-    pt = c0 + (int)(r - (long)gt * qc);
-#else
-    const long per_chunk = (long)gtiles * npt;
-    ck = (int)(tile / per_chunk);
-    const long r = tile - (long)ck * per_chunk;
-    gt = (int)(r / npt);
-    pt = (int)(r - (long)gt * npt);
-#endif
+    r -= (Int)ck * per_chunk;
+    gt = (int)(r / (Int)qc);
+    pt = c0 + (int)(r - (Int)gt * (Int)qc);
+}
+// In 32 bits wherever a block of tiles and the tile index fit (a 64-bit
+// division costs about a hundred instructions, three of them as much as the
+// band loop of a few bands).
+__device__ __forceinline__ void tile_coords(long tile, int npt, int gtiles, int nchunk, int &gt,
+                                            int &pt, int &ck)
+{
+    if (tile < (1L << 31) && (long)GPP_FWD_COL_BLOCK * gtiles * nchunk < (1L << 31))
+        tile_coords_in<uint32_t>((uint32_t)tile, npt, gtiles, nchunk, gt, pt, ck);
+    else
+        tile_coords_in<long>(tile, npt, gtiles, nchunk, gt, pt, ck);
     gt = __builtin_amdgcn_readfirstlane(gt);
     pt = __builtin_amdgcn_readfirstlane(pt);
     ck = __builtin_amdgcn_readfirstlane(ck);
@@ -271,23 +274,55 @@ __device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng,
     }
 }
 
+// Where a tile's sums go.  hole() takes the lanes' Coulomb-hole parts (2 NW
+// values per lane), exchange() the screened-exchange ones; either may be
+// called or not, at most once.
+//
+// A row of 4 NW wave totals in LDS, achtemp re, im, asxtemp re, im per
+// frequency, so that no total stays in registers over the band loop.
+template <int NW>
+struct RowSink {
+    double *row;
+    int lane;
+    __device__ __forceinline__ void hole(const double (&v)[2 * NW]) const {
+        wave_totals<2 * NW>(v, lane, [&](int i, double t) { row[i + (i & ~1)] = t; });
+    }
+    __device__ __forceinline__ void exchange(const double (&v)[2 * NW]) const {
+        wave_totals<2 * NW>(v, lane, [&](int i, double t) { row[i + (i & ~1) + 2] = t; });
+    }
+};
+// Running sums of a persistent wave, in scalar registers.
+template <int NW>
+struct RunningSink {
+    cplx ach[NW], asx[NW];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
+    }
+    __device__ __forceinline__ void hole(const double (&v)[2 * NW]) { add(ach, v); }
+    __device__ __forceinline__ void exchange(const double (&v)[2 * NW]) { add(asx, v); }
+    __device__ __forceinline__ void add(cplx (&to)[NW], const double (&v)[2 * NW]) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            to[w].re = to_uniform(to[w].re + wave_sum(v[2 * w]));
+            to[w].im = to_uniform(to[w].im + wave_sum(v[2 * w + 1]));
+        }
+    }
+};
+
 // NC consecutive G' columns p0 .. p0+NC-1 of one 64-row tile per wave,
 // bands n_lo <= n < n_hi: each aqsntemp element a lane loads serves all of
 // them, which divides the vector-memory traffic of the hot loop by NC.
-// Columns at or beyond np repeat p0 and their contribution is dropped.  On
-// return ach[w] holds this lane's Coulomb-hole contribution of the columns
-// (still to be summed over the wave) and asx[w] the wave's screened-exchange
-// total (wave-uniform).  All 64 lanes of the wave must call it together
-// (wave reductions and full execution masks inside); lane l takes row
-// g = gt*64 + l.
-template <int NW, int BU, int NC>
-__device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi, int ng,
-                                                   int np, int p0, int gt, int lane,
-                                                   gptr<double2> aqsm,
-                                                   gptr<double2> aqsn, gptr<double2> ieps,
-                                                   gptr<double2> wt, gptr<double> vcoul,
-                                                   gptr<double> wx, cplx (&ach)[NW],
-                                                   cplx (&asx)[NW])
+// Columns at or beyond np repeat p0 and their contribution is dropped.  The
+// sums go to the sink, the exchange ones only where the bands hold occupied
+// ones.  All 64 lanes of the wave must call it together (wave reductions and
+// full execution masks inside); lane l takes row g = gt*64 + l.
+template <int NW, int BU, int NC, typename Sink>
+__device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi, int ng, int np,
+                                              int p0, int gt, int lane, gptr<double2> aqsm,
+                                              gptr<double2> aqsn, gptr<double2> ieps,
+                                              gptr<double2> wt, gptr<double> vcoul,
+                                              gptr<double> wx, Sink &sink)
 {
     const int g = gt * kWave + lane;
     const bool valid = g < ng;
@@ -316,7 +351,7 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     const double v = valid ? vcoul[gc] : 0.0;
 
     // occupied bands, column by column; the exchange sums of all columns
-    // are reduced over the wave into scalar registers before the hot loop
+    // leave for the sink before the hot loop
     const int occ_hi = nv < n_hi ? nv : n_hi;
     if (occ_hi > n_lo) {
         cplx sx[NW];
@@ -334,12 +369,13 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
 #pragma unroll
             for (int w = 0; w < NW; ++w) cmac(sx[w], ev, SX[w]);
         }
+        double v2[2 * NW];
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
-            asx[w] = cmake(wave_sum_uniform(sx[w].re), wave_sum_uniform(sx[w].im));
-    } else {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) asx[w] = cmake(0.0, 0.0);
+        for (int w = 0; w < NW; ++w) {
+            v2[2 * w] = sx[w].re;
+            v2[2 * w + 1] = sx[w].im;
+        }
+        sink.exchange(v2);
     }
 
     // unoccupied bands: CH only, whole groups, then band by band
@@ -354,8 +390,9 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
         ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, P1,
                             P2);
 
+    double v2[2 * NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) ach[w] = cmake(0.0, 0.0);
+    for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const double vc = has[c] ? v : 0.0;
@@ -368,9 +405,11 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
             S.re = fma(-wtr, P2[c][w].re, S.re);
             S.im = fma(-wtr, P2[c][w].im, S.im);
             const cplx t = cscale(0.5, cmul(ev, S));
-            ach[w] = cadd(ach[w], t);
+            v2[2 * w] += t.re;
+            v2[2 * w + 1] += t.im;
         }
     }
+    sink.hole(v2);
 }
 
 }  // namespace gpp

@@ -24,10 +24,12 @@ struct FwdGeometry {
     long ntiles = 0;      // g-tiles x column tiles x band chunks, one per wave
     int nchunk = 1;       // band chunks (fwd_band_chunks)
     int chunk_bands = 0;  // bands per chunk (the last may be shorter)
-    long nblocks = 0;     // tile-kernel workgroups of 4 waves (one partial each)
-    long red_blocks = 0;  // first reduction stage workgroups
+    int waves = 4;        // waves per tile-kernel workgroup (16: the split form)
+    int shift = 0;        // split form: 2^shift waves share a tile's bands
+    long nblocks = 0;     // tile-kernel workgroups (one partial row each)
+    long red_blocks = 0;  // first reduction stage workgroups, 0 for none
     long red_chunk = 0;   // partial rows per first-stage workgroup
-    size_t partial_bytes = 0, stage_bytes = 0, workspace_bytes = 0;
+    size_t workspace_bytes = 0;
 };
 
 struct BwdGeometry {
