@@ -60,18 +60,26 @@ __device__ __forceinline__ long static_slot(const StateDesc *__restrict__ st, in
 }
 
 // The schedule position k in [lo, nstates) of the state holding item v of
-// the list (a tile, or a queue chunk when CHUNK), given that state lo starts
-// at or before v: the last k with start(k) <= v, so empty states are never
-// returned.  st[nstates] is the sentinel holding the total, which v is below.
+// the list (a tile, or a queue chunk, flat workgroup or slot when CHUNK),
+// given that state lo starts at or before v: the last k with start(k) <= v,
+// so empty states are never returned.  st[nstates] is the sentinel holding
+// the total, which v is below.  All 64 lanes search together: each looks at
+// one of 64 evenly spaced states, so that 256 states take two dependent
+// loads instead of the eight of a bisection.
 template <bool CHUNK>
 __device__ __forceinline__ int find_state(const StateDesc *__restrict__ st, int lo, int nstates,
                                           long v)
 {
-    int hi = nstates;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if ((CHUNK ? st[mid].chunk_begin : st[mid].tile_begin) <= v) lo = mid;
-        else hi = mid;
+    const int lane = threadIdx.x & (kWave - 1);
+    int n = nstates - lo;  // candidates lo .. lo + n - 1
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const int i = lane * step;
+        const bool at_or_before =
+            i < n && (CHUNK ? st[lo + i].chunk_begin : st[lo + i].tile_begin) <= v;
+        const int last = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(at_or_before));
+        lo += last * step;
+        n = n - last * step < step ? n - last * step : step;
     }
     return lo;
 }
@@ -220,7 +228,7 @@ batched_queue(const StateDesc *__restrict__ st, int nstates, long nchunks, int c
 // shape (fwd_cols(NW) G' columns x 64 rows, fwd_tile_body), four
 // consecutive tiles of one state per workgroup, each state's tiles padded to
 // whole workgroups.  Here chunk_begin is a state's first workgroup:
-// workgroup wg finds its state by binary search, and writes one partial row
+// workgroup wg finds its state (find_state), and writes one partial row
 // (zeros past the state's last tile), which batched_reduce_chunks adds per
 // state in a fixed order.  With no loop state to carry it keeps the plain
 // forward's registers and two-column tiles.
@@ -246,14 +254,7 @@ batched_flat(const StateDesc *__restrict__ st, int nstates, double *__restrict__
         const long r = b - sb * span;
         wg = sb * span + (r % kXcdCount) * kFlatRun + r / kXcdCount;
     }
-    // st[lo].chunk_begin <= wg < st[hi].chunk_begin; st[nstates] is the
-    // sentinel holding the total, so the state found owns wg
-    int lo = 0, hi = nstates;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (st[mid].chunk_begin <= wg) lo = mid;
-        else hi = mid;
-    }
+    const int lo = find_state<true>(st, 0, nstates, wg);
     const StateDesc d = st[lo];
     constexpr int C = fwd_cols(NW);
     const int npt = (d.np + C - 1) / C;

@@ -221,6 +221,16 @@ FwdGeometry fwd_geometry(const Dims32 &d)
     const int cols = fwd_cols(d.nw);
     fwd_band_chunks(d.nb, d.nw, geo.nchunk, geo.chunk_bands);
     geo.ntiles = gtiles * ((d.np + cols - 1) / cols) * geo.nchunk;
+    if (geo.ntiles >= kSplitBelow) {
+        const int m = fwd_fine_chunks(geo.ntiles, geo.chunk_bands, kCUs);
+        if (m > 1) {
+            const int bu = fwd_bands(d.nw);
+            const long tiles = geo.ntiles / geo.nchunk;
+            geo.chunk_bands = ((geo.chunk_bands + m - 1) / m + bu - 1) / bu * bu;
+            geo.nchunk = (d.nb + geo.chunk_bands - 1) / geo.chunk_bands;
+            geo.ntiles = tiles * geo.nchunk;
+        }
+    }
     geo.waves = kFwdWaves;
     geo.nblocks = (geo.ntiles + kFwdWaves - 1) / kFwdWaves;
     const long long_rows = geo.nblocks;

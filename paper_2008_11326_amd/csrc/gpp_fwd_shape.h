@@ -72,6 +72,31 @@ inline void fwd_band_chunks(int nb, int nw, int &nchunk, int &chunk_bands)
     nchunk = (nb + cb - 1) / cb;
 }
 
+// Above kSplitBelow tiles but with few workgroups per compute unit, the
+// last of them leave much of the GPU idle: finer band chunks even that out,
+// until a tile's fixed part (set-up, epilogue: worth kTileBands bands) costs
+// more.  The chunk count in [1, kMaxFineChunks] with the least work on the
+// fullest compute unit, at most 1/64 less than with fewer chunks counting as
+// equal.  Measured at 128 bands x 4096 rows x 204 columns, nfreq 3 (1632
+// workgroups of 4 tiles): 156.0 us in one chunk, 150.8 in two, 165.4 in
+// four; 64 x 2048 x 102 at nfreq 5 (816): 47.3, 45.8 and 50.6.
+constexpr int kTileBands = 7;
+constexpr int kMaxFineChunks = 4;
+inline int fwd_fine_chunks(long tiles, int bands, int cus)
+{
+    int best = 1;
+    double least = 0.0;
+    for (int m = 1; m <= kMaxFineChunks; ++m) {
+        const long per_cu = ((tiles * m + 3) / 4 + cus - 1) / cus;
+        const double cost = (double)per_cu * ((double)bands / m + kTileBands);
+        if (m == 1 || cost < least * (1.0 - 1.0 / 64)) {
+            best = m;
+            least = cost;
+        }
+    }
+    return best;
+}
+
 // The split form of the forward's tile kernel, for grids of fewer than
 // kSplitBelow tiles (gpp_fwd.hip).  Bands per batch-inverted group there: a
 // 16-wave workgroup holds its waves to 128 VGPRs.

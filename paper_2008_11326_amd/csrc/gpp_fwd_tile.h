@@ -329,26 +329,31 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     const int gc = valid ? g : ng - 1;  // clamped, contribution zeroed
 
     int pc[NC];
-    bool has[NC];
-    cplx om[NC];
+    cplx om[NC], ev[NC];
     double a[NC], wi2[NC], thr[NC];
-    bool wide[NC];
     cplx P1[NC][NW], P2[NC][NW];
+    // every column's loads before the first value is used: one wait for all
+    // of them, also for e, which the sums need only at the end
+    const double v = valid ? vcoul[gc] : 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        has[c] = p0 + c < np;
-        pc[c] = has[c] ? p0 + c : p0;
+        pc[c] = p0 + c < np ? p0 + c : p0;
         om[c] = cload(wt + (size_t)pc[c] * ng + gc);
+        ev[c] = cload(ieps + (size_t)pc[c] * ng + gc);
+    }
+    bool wide_all = true;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        ev[c] = cscale(p0 + c < np ? v : 0.0, ev[c]);
         a[c] = om[c].re;
         wi2[c] = om[c].im * om[c].im;
         thr[c] = branch_a_threshold(fma(a[c], a[c], wi2[c]));
-        wide[c] = wi2[c] >= kMinUnclampedWi2;
+        wide_all = wide_all && wi2[c] >= kMinUnclampedWi2;
 #pragma unroll
         for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
     }
     const gptr<double2> an_col = aqsn + gc;
     const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
-    const double v = valid ? vcoul[gc] : 0.0;
 
     // occupied bands, column by column; the exchange sums of all columns
     // leave for the sink before the hot loop
@@ -364,10 +369,8 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
             for (int w = 0; w < NW; ++w) SX[w] = cmake(0.0, 0.0);
             occupied_bands<NW>(n_lo, occ_hi, nb, ng, an_col, aqsm + pc[c], wx, om[c], wi2[c],
                                fma(a[c], a[c], wi2[c]), thr[c], P1[c], P2[c], SX);
-            const double vc = has[c] ? v : 0.0;
-            const cplx ev = cscale(vc, cload(ieps + (size_t)pc[c] * ng + gc));
 #pragma unroll
-            for (int w = 0; w < NW; ++w) cmac(sx[w], ev, SX[w]);
+            for (int w = 0; w < NW; ++w) cmac(sx[w], ev[c], SX[w]);
         }
         double v2[2 * NW];
 #pragma unroll
@@ -379,9 +382,6 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     }
 
     // unoccupied bands: CH only, whole groups, then band by band
-    bool wide_all = true;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) wide_all = wide_all && wide[c];
     const uint64_t narrow = __builtin_amdgcn_ballot_w64(!wide_all);
     int n = nv > n_lo ? nv : n_lo;
     n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, P1,
@@ -395,8 +395,6 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const double vc = has[c] ? v : 0.0;
-        const cplx ev = cscale(vc, cload(ieps + (size_t)pc[c] * ng + gc));
         const double wtr = fma(a[c], a[c], wi2[c]);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
@@ -404,7 +402,7 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
             cplx S = cmul(om[c], P1[c][w]);
             S.re = fma(-wtr, P2[c][w].re, S.re);
             S.im = fma(-wtr, P2[c][w].im, S.im);
-            const cplx t = cscale(0.5, cmul(ev, S));
+            const cplx t = cscale(0.5, cmul(ev[c], S));
             v2[2 * w] += t.re;
             v2[2 * w + 1] += t.im;
         }
