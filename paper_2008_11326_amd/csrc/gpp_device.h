@@ -44,6 +44,33 @@ __device__ __forceinline__ gptr<T> as_global(const T *p) {
     return (gptr<T>)p;
 }
 
+// A running wave-uniform address (scalar registers) of read-only data.  Its
+// loads are scalar loads whatever else the kernel writes (constant address
+// space); the empty asm in advance() keeps the compiler from folding the
+// running addresses of a loop back into one index, whose products and sums
+// per load then stand in front of every load.
+struct Walker {
+    uint64_t at;
+    __device__ __forceinline__ void start(uint64_t a) {
+        at = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32 |
+             (unsigned)__builtin_amdgcn_readfirstlane((int)a);
+    }
+    __device__ __forceinline__ void advance(long bytes) {
+        at += bytes;
+        asm("" : "+s"(at));
+    }
+    // the real value `i` doubles further on
+    __device__ __forceinline__ double real(int i) const {
+        return ((const __attribute__((address_space(4))) double *)at)[i];
+    }
+    // the complex value `bytes` further on
+    __device__ __forceinline__ cplx complex(uint32_t bytes) const {
+        typedef double pair __attribute__((ext_vector_type(2)));
+        const pair v = *(const __attribute__((address_space(4))) pair *)(at + bytes);
+        return {v.x, v.y};
+    }
+};
+
 __device__ __forceinline__ cplx cmake(double re, double im) { return {re, im}; }
 __device__ __forceinline__ cplx cload(const double2 *p) {
     double2 v = *p;
@@ -209,7 +236,7 @@ __device__ __forceinline__ double next_down(double t) {
 // specification for every wdiffr >= 0.  fl(kLimitOne * d) is monotone in
 // d, so {d : wtr < fl(kLimitOne * d)} = {d >= T}; A is then
 // d > kLimitTwo && d >= T, i.e. d > max(kLimitTwo, pred(T)).
-__device__ inline double branch_a_threshold(double wtr) {
+__device__ inline double threshold_search(double wtr) {
 #pragma clang fp contract(off)
     if (wtr < kFastWtr) return kLimitTwo;
     if (!(wtr <= 1.0e300)) return __builtin_inf();  // NaN/huge: never A
@@ -218,6 +245,12 @@ __device__ inline double branch_a_threshold(double wtr) {
     for (int i = 0; i < 64 && (kLimitOne * next_down(t) > wtr); ++i) t = next_down(t);
     double p = next_down(t);
     return p > kLimitTwo ? p : kLimitTwo;
+}
+// The search only where a lane of the wave needs it (one scalar branch).
+__device__ __forceinline__ double branch_a_threshold(double wtr) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(wtr < kFastWtr)) != 0, 0))
+        return threshold_search(wtr);
+    return kLimitTwo;
 }
 
 __device__ inline bool branch_b_holds(double wtr, double wdiffr) {
@@ -315,6 +348,17 @@ __device__ __forceinline__ double to_uniform(double t) {
     const int lo = __builtin_amdgcn_readfirstlane(__double2loint(t));
     const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(t));
     return __hiloint2double(hi, lo);
+}
+
+// The same for the row `row_off` bytes further on (a scalar register) than
+// the 64-bit row address `at`.  The callers' offsets are those of existing
+// elements, so the descriptor sets no bound.
+__device__ __forceinline__ cplx load_elem_at(uint64_t at, uint32_t row_off, uint32_t off) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)at, (short)0, -1,
+                                                                        0x00020000);
+    const double2 v = __builtin_bit_cast(
+        double2, __builtin_amdgcn_raw_buffer_load_b128(rs, off, row_off, 0));
+    return {v.x, v.y};
 }
 
 // Map a hardware workgroup id to a logical one so that each of the 8 XCDs

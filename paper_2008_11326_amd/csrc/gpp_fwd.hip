@@ -96,8 +96,9 @@ fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_ban
             const int k = (int)wave & ((1 << shift) - 1);
             const int occ = nv < n_hi ? (nv > n_lo ? nv - n_lo : 0) : n_hi - n_lo;
             const int lo = n_lo, hi = n_hi;
-            n_lo = split_at<BU>(k, shift, lo, occ, hi);
-            n_hi = split_at<BU>(k + 1, shift, lo, occ, hi);
+            // wave-uniform, and told so: the divisions run on the vector unit
+            n_lo = __builtin_amdgcn_readfirstlane(split_at<BU>(k, shift, lo, occ, hi));
+            n_hi = __builtin_amdgcn_readfirstlane(split_at<BU>(k + 1, shift, lo, occ, hi));
         }
         RowSink<NW> sink{red[wid], lane};
         if (n_lo < n_hi)

@@ -90,13 +90,43 @@ __device__ __forceinline__ void ch_term(double d, double thr, double r, double x
         : "vcc");
 }
 
+// What BU consecutive bands bring into a group: a lane's aqsntemp values and
+// the frequencies x (wave-uniform).  Bands at or beyond nb repeat the last
+// one.
+template <int NW, int BU>
+struct BandGroup {
+    cplx an[BU];
+    double xs[BU * NW];
+    // An empty use of the values: whatever was asked for up to them has
+    // arrived here (loads return in order), so that a loop behind this point
+    // does not start every round with a wait for its own loads.  Not volatile
+    // (see ch_term).
+    __device__ __forceinline__ void arrived() {
+#pragma unroll
+        for (int u = 0; u < BU; ++u) asm("" : "+v"(an[u].re), "+v"(an[u].im));
+#pragma unroll
+        for (int k = 0; k < BU * NW; ++k) asm("" : "+s"(xs[k]));
+    }
+    __device__ __forceinline__ void load_first(int n, int nb, int ng, gptr<double2> aqsn,
+                                               uint32_t goff, gptr<double> wx) {
+#pragma unroll
+        for (int u = 0; u < BU; ++u) {
+            const int m = n + u < nb ? n + u : nb - 1;
+            an[u] = load_row_elem(aqsn + (size_t)m * ng, ng, goff);
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+                xs[u * NW + w] = Walker{(uint64_t)(wx + (size_t)w * nb + m)}.real(0);
+        }
+    }
+};
+
 // Coulomb-hole sums of NC columns over the whole groups of BU unoccupied
-// bands in [n, n_hi); returns the first band left over.  The BU*NW*NC
-// denominators of a group share one batch inversion; they go in unclamped:
-// every one is at least (Im om)^2, and where a lane has a column with
-// (Im om)^2 below kMinUnclampedWi2 (the wave mask `narrow`) the wave inverts
-// one by one; a masked term's reciprocal (possibly infinite or NaN there)
-// never reaches the sums (ch_term).
+// bands in [n, n_hi), the first of them loaded in `cur`; returns the first
+// band left over.  The BU*NW*NC denominators of a group share one batch
+// inversion; they go in unclamped: every one is at least (Im om)^2, and where
+// a lane has a column with (Im om)^2 below kMinUnclampedWi2 (the wave mask
+// `narrow`) the wave inverts one by one; a masked term's reciprocal (possibly
+// infinite or NaN there) never reaches the sums (ch_term).
 // Loads run ahead of their use, so that no wait sits in front of a group's
 // arithmetic: the frequencies of the next group are asked for together with
 // this group's aqsmtemp values, which are needed only after the reciprocals;
@@ -104,42 +134,56 @@ __device__ __forceinline__ void ch_term(double d, double thr, double r, double x
 // into the products.  aqsntemp[n][g] is read through a buffer descriptor of
 // the row (scalar registers) plus the lane's 32-bit byte offset, so the
 // address arithmetic stays on the scalar unit.
-// With the loads ahead and the inversion in two halves (gpp_device.h), against
-// loads waited for in front of each group's arithmetic: 8192 rows x 409
-// columns x 256 bands at nfreq 8 2.82 -> 2.72 ms; 4096 x 204 x 128 at nfreq 3
-// 1.8 % faster; 32768 x 1638 x 512 unchanged and 65536 x 3276 x 1024 0.7 %
-// faster, as those sit at the part's power limit (a register-only loop of the
-// same instructions reaches 4.3e10 wave-terms per second, these 3.95e10).
+// Measured on MI355X against loads waited for in front of each group's
+// arithmetic, one chain for the inversion and addresses formed per load: 512
+// bands x 32768 rows x 1638 columns 33.1 -> 31.7 ms (3.97e10 -> 4.1e10
+// wave-terms per second; a register-only loop of the same instructions
+// reaches 4.3e10 at the part's power limit), 256 states of 32-128 bands
+// 10.7 -> 10.2 ms; of that the running addresses 2.0 and 2.6 %.
 template <int NW, int BU, int NC>
 __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<double2> aqsn,
                                         uint32_t goff, gptr<double2> aqsm, const int (&pc)[NC],
                                         gptr<double> wx, const double (&a)[NC],
                                         const double (&wi2)[NC], const double (&thr)[NC],
-                                        uint64_t narrow, cplx (&P1)[NC][NW], cplx (&P2)[NC][NW])
+                                        uint64_t narrow, BandGroup<NW, BU> &cur,
+                                        cplx (&P1)[NC][NW], cplx (&P2)[NC][NW])
 {
     constexpr int KB = BU * NW;  // terms of one column
     constexpr int K = NC * KB;
-    if (n + BU > n_hi) return n;
-    cplx an[BU];
-    double xs[KB];
+    int left = (n_hi - n) / BU;
+    if (left <= 0) return n;
+    n += left * BU;
+    cplx (&an)[BU] = cur.an;
+    double (&xs)[KB] = cur.xs;
+    const uint32_t row_bytes = (uint32_t)ng * (uint32_t)sizeof(double2);
+    const long step = (long)BU * row_bytes;
+    uint64_t rows = (uint64_t)(aqsn + (size_t)(n - left * BU) * ng);
+    Walker am_at[NC], x_at[NW];
 #pragma unroll
-    for (int u = 0; u < BU; ++u) {
-        an[u] = load_row_elem(aqsn + (size_t)(n + u) * ng, ng, goff);
+    for (int c = 0; c < NC; ++c)
+        am_at[c].start((uint64_t)(aqsm + pc[c] + (size_t)(n - left * BU) * ng));
+    // the last group asks for its own frequencies and rows again
+    int more = left > 1 ? BU : 0;  // bands to the next group
 #pragma unroll
-        for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
-    }
+    for (int w = 0; w < NW; ++w)
+        x_at[w].start((uint64_t)(wx + (size_t)w * nb + (n - left * BU) + more));
+    cur.arrived();
     for (;;) {
-        // the last group asks for its own values again
-        const int nx = n + 2 * BU <= n_hi ? n + BU : n;
         cplx am[NC][BU];
         double xn[KB];
 #pragma unroll
         for (int u = 0; u < BU; ++u) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) am[c][u] = cload(aqsm + pc[c] + (size_t)(n + u) * ng);
+            for (int c = 0; c < NC; ++c) am[c][u] = am_at[c].complex(u * row_bytes);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) xn[u * NW + w] = wx[(size_t)w * nb + nx + u];
+            for (int w = 0; w < NW; ++w) xn[u * NW + w] = x_at[w].real(u);
         }
+        rows += more ? step : 0;
+        more = left > 2 ? BU : 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) am_at[c].advance(step);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) x_at[w].advance(more * (long)sizeof(double));
         double d[K], r[K];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -159,8 +203,7 @@ __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<do
 #pragma unroll
             for (int u = 0; u < BU; ++u) qm[c][u] = qm_of(an[u], am[c][u]);
 #pragma unroll
-        for (int u = 0; u < BU; ++u)
-            an[u] = load_row_elem(aqsn + (size_t)(nx + u) * ng, ng, goff);
+        for (int u = 0; u < BU; ++u) an[u] = load_elem_at(rows, u * row_bytes, goff);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -171,8 +214,7 @@ __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<do
                     ch_term(d[c * KB + k], thr[c], r[c * KB + k], xs[k], qm[c][u], P1[c][w],
                             P2[c][w]);
                 }
-        if (nx == n) return n + BU;
-        n = nx;
+        if (--left == 0) return n;
 #pragma unroll
         for (int k = 0; k < KB; ++k) xs[k] = xn[k];
     }
@@ -180,7 +222,7 @@ __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<do
 
 // Frequencies W0 .. W0+G-1 of one occupied band (see occupied_bands).
 template <int NW, int W0, int G>
-__device__ __forceinline__ void occupied_freqs(int n, int nb, gptr<double> wx, double a, double b,
+__device__ __forceinline__ void occupied_freqs(const double (&x)[NW], double a, double b,
                                                double wi2, double wtr, double thr, bool wide,
                                                cplx om2, cplx qm, cplx (&P1)[NW],
                                                cplx (&P2)[NW], cplx (&SX)[NW])
@@ -188,7 +230,7 @@ __device__ __forceinline__ void occupied_freqs(int n, int nb, gptr<double> wx, d
     double xs[G], wd[G], ws[G], r[G], rs[G];
 #pragma unroll
     for (int k = 0; k < G; ++k) {
-        xs[k] = wx[(size_t)(W0 + k) * nb + n];
+        xs[k] = x[W0 + k];
         const double dr = xs[k] - a, sp = xs[k] + a;
         wd[k] = fma(dr, dr, wi2);  // |x - om|^2, the branch's wdiffr
         ws[k] = fma(sp, sp, wi2);  // |x + om|^2
@@ -203,18 +245,17 @@ __device__ __forceinline__ void occupied_freqs(int n, int nb, gptr<double> wx, d
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int w = W0 + k;
-        const double x = xs[k];
-        const double dr = x - a, sp = x + a;
+        const double dr = xs[k] - a, sp = xs[k] + a;
         const bool isA = wd[k] > thr;
         const double rc = isA ? r[k] : 0.0;
-        const double rx = rc * x;
+        const double rx = rc * xs[k];
         P1[w].re = fma(rx, qm.re, P1[w].re);
         P1[w].im = fma(rx, qm.im, P1[w].im);
         P2[w].re = fma(rc, qm.re, P2[w].re);
         P2[w].im = fma(rc, qm.im, P2[w].im);
         // both branches' values carry rs: A = r om^2 conj(d s), B = -om conj(s) / 2
         const cplx na = cscale(r[k], cmul(om2, cmake(fma(dr, sp, wi2), om2.im)));
-        const cplx nb2 = cmake(-0.5 * fma(a, sp, wi2), -0.5 * (b * x));
+        const cplx nb2 = cmake(-0.5 * fma(a, sp, wi2), -0.5 * (b * xs[k]));
         const bool isB = branch_b_holds(wtr, wd[k]);
         cplx t;
         t.re = rs[k] * (isA ? na.re : (isB ? nb2.re : 0.0));
@@ -232,20 +273,35 @@ __device__ __forceinline__ void occupied_freqs(int n, int nb, gptr<double> wx, d
 constexpr int occ_group(int nw) { return GPP_OCC_GROUP ? GPP_OCC_GROUP : (nw <= 3 ? nw : 1); }
 
 template <int NW, int W0>
-__device__ __forceinline__ void occupied_groups(int n, int nb, gptr<double> wx, double a, double b,
+__device__ __forceinline__ void occupied_groups(const double (&x)[NW], double a, double b,
                                                 double wi2, double wtr, double thr, bool wide,
                                                 cplx om2, cplx qm, cplx (&P1)[NW],
                                                 cplx (&P2)[NW], cplx (&SX)[NW])
 {
     constexpr int G = NW - W0 < occ_group(NW) ? NW - W0 : occ_group(NW);
-    occupied_freqs<NW, W0, G>(n, nb, wx, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
+    occupied_freqs<NW, W0, G>(x, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
     if constexpr (W0 + G < NW)
-        occupied_groups<NW, W0 + G>(n, nb, wx, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
+        occupied_groups<NW, W0 + G>(x, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
 }
 
-// Occupied bands n0 <= n < n1 (all below nvband) of one lane and one
-// column: Coulomb-hole terms into P1/P2 and screened-exchange terms
-// (ssx / e) into SX.  With d = x - om and s = x + om, the exchange term is
+// One occupied band's values for one column.
+template <int NW>
+struct OccupiedBand {
+    cplx an, am;
+    double x[NW];
+    __device__ __forceinline__ void load(int n, int nb, int ng, gptr<double2> aqsn, uint32_t goff,
+                                         gptr<double2> am_col, gptr<double> wx) {
+        an = load_row_elem(aqsn + (size_t)n * ng, ng, goff);
+        am = cload(am_col + (size_t)n * ng);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) x[w] = wx[(size_t)w * nb + n];
+    }
+};
+
+// Occupied bands n0 <= n < n1 (all below nvband) of one lane and one column,
+// band n0 loaded in `cur`: Coulomb-hole terms into P1/P2 and
+// screened-exchange terms (ssx / e) into SX.  With d = x - om and s = x + om,
+// the exchange term is
 //   A:  om^2 / (d s) = om^2 conj(d s) r rs,     r = 1/|d|^2, rs = 1/|s|^2
 //   B:  -om / (2 s)  = -om conj(s) rs / 2
 // where d s = x^2 - om^2 has real part fma(Re d, Re s, (Im om)^2) (both
@@ -255,22 +311,29 @@ __device__ __forceinline__ void occupied_groups(int n, int nb, gptr<double> wx, 
 // batch inversions per group of frequencies (both are at least
 // (Im om)^2, like the hot loop's denominators); the branch picks each
 // term's value by selects, so a value computed for another branch never
-// reaches the sums.
+// reaches the sums.  The next band (after the last, the next column's first)
+// loads while this one computes: with few bands per wave each exposed load
+// would be a visible part of its time.  (Loading the first group and the first
+// occupied band at the tile's start as well cost more registers than it won:
+// 61 bands x 777 rows x 38 columns at nfreq 2 ran 18.5 instead of 15.7 us.)
 template <int NW>
-__device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng,
-                                               gptr<double2> an_col, gptr<double2> am_col,
-                                               gptr<double> wx, cplx om, double wi2, double wtr,
-                                               double thr, cplx (&P1)[NW], cplx (&P2)[NW],
-                                               cplx (&SX)[NW])
+__device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng, gptr<double2> aqsn,
+                                               uint32_t goff, gptr<double2> am_col,
+                                               gptr<double2> am_next, gptr<double> wx, cplx om,
+                                               double wi2, double thr, OccupiedBand<NW> &cur,
+                                               cplx (&P1)[NW], cplx (&P2)[NW], cplx (&SX)[NW])
 {
     const double a = om.re, b = om.im;
+    const double wtr = fma(a, a, wi2);
     const cplx om2 = cmake(fma(a, a, -wi2), 2.0 * a * b);  // om^2
     const bool wide = wi2 >= kMinUnclampedWi2;
     for (int n = n0; n < n1; ++n) {
-        const cplx an = cload(an_col + (size_t)n * ng);
-        const cplx am = cload(am_col + (size_t)n * ng);
-        const cplx qm = cmul_conj(an, am);
-        occupied_groups<NW, 0>(n, nb, wx, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
+        const bool more = n + 1 < n1;
+        OccupiedBand<NW> next;
+        next.load(more ? n + 1 : n0, nb, ng, aqsn, goff, more ? am_col : am_next, wx);
+        occupied_groups<NW, 0>(cur.x, a, b, wi2, wtr, thr, wide, om2, cmul_conj(cur.an, cur.am),
+                               P1, P2, SX);
+        cur = next;
     }
 }
 
@@ -332,8 +395,11 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     cplx om[NC], ev[NC];
     double a[NC], wi2[NC], thr[NC];
     cplx P1[NC][NW], P2[NC][NW];
-    // every column's loads before the first value is used: one wait for all
-    // of them, also for e, which the sums need only at the end
+    const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
+    const int occ_hi = nv < n_hi ? nv : n_hi;
+    int n = nv > n_lo ? nv : n_lo;
+    // every column's loads before the first value is used, also e, which the
+    // sums need only at the end: one wait for all of them
     const double v = valid ? vcoul[gc] : 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -352,43 +418,47 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
 #pragma unroll
         for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
     }
-    const gptr<double2> an_col = aqsn + gc;
-    const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
 
-    // occupied bands, column by column; the exchange sums of all columns
-    // leave for the sink before the hot loop
-    const int occ_hi = nv < n_hi ? nv : n_hi;
+    // occupied bands; their exchange sums leave for the sink before the hot
+    // loop
     if (occ_hi > n_lo) {
-        cplx sx[NW];
+        OccupiedBand<NW> occ;
+        occ.load(n_lo, nb, ng, aqsn, goff, aqsm + pc[0], wx);
+        double v2[2 * NW];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sx[w] = cmake(0.0, 0.0);
+        for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             cplx SX[NW];
 #pragma unroll
             for (int w = 0; w < NW; ++w) SX[w] = cmake(0.0, 0.0);
-            occupied_bands<NW>(n_lo, occ_hi, nb, ng, an_col, aqsm + pc[c], wx, om[c], wi2[c],
-                               fma(a[c], a[c], wi2[c]), thr[c], P1[c], P2[c], SX);
+            occupied_bands<NW>(n_lo, occ_hi, nb, ng, aqsn, goff, aqsm + pc[c],
+                               aqsm + pc[c + 1 < NC ? c + 1 : c], wx, om[c], wi2[c], thr[c], occ,
+                               P1[c], P2[c], SX);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) cmac(sx[w], ev[c], SX[w]);
-        }
-        double v2[2 * NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            v2[2 * w] = sx[w].re;
-            v2[2 * w + 1] = sx[w].im;
+            for (int w = 0; w < NW; ++w) {
+                const cplx t = cmul(ev[c], SX[w]);
+                v2[2 * w] += t.re;
+                v2[2 * w + 1] += t.im;
+            }
         }
         sink.exchange(v2);
     }
 
     // unoccupied bands: CH only, whole groups, then band by band
     const uint64_t narrow = __builtin_amdgcn_ballot_w64(!wide_all);
-    int n = nv > n_lo ? nv : n_lo;
-    n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, P1,
-                             P2);
-    if constexpr (BU > 1)
-        ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, P1,
-                            P2);
+    BandGroup<NW, BU> first;
+    first.load_first(n, nb, ng, aqsn, goff, wx);
+    n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, first,
+                             P1, P2);
+    if constexpr (BU > 1) {
+        if (n < n_hi) {
+            BandGroup<NW, 1> rest;
+            rest.load_first(n, nb, ng, aqsn, goff, wx);
+            ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow,
+                                rest, P1, P2);
+        }
+    }
 
     double v2[2 * NW];
 #pragma unroll
