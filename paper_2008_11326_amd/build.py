@@ -38,11 +38,11 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result", f"-I{INCLUDE}", f"-I{CSRC}",
 ]
-# The forward's tile loop asks for the next group's values ahead of its
+# The tile loops ask for the next group's values ahead of their
 # arithmetic; with machine sinking on, the compiler moves those loads back
 # behind a branch, right before their use.
 EXTRA_FLAGS = {src: ["-mllvm", "-disable-machine-sink"]
-               for src in ("gpp_fwd.hip", "gpp_batched.hip")}
+               for src in ("gpp_fwd.hip", "gpp_batched.hip", "gpp_bwd.hip")}
 
 
 def _compile(src: str, verbose: bool, objdir: str = OBJDIR, defines=()) -> str:

@@ -20,8 +20,8 @@
 //
 // Kernels.  bwd_pairs (lane = g, wave-uniform p, bands serial) writes
 // dwtilde and dI_eps.  K and L are linear in ga/2, so over unoccupied bands
-// (with at most four frequencies) the lane never forms them: it keeps four
-// sums per frequency over the bands, weighted by conj(M),
+// the lane never forms them: it keeps four sums per frequency over the bands,
+// weighted by conj(M),
 //   A2_w = sum_n conj(M) r,           B1_w = sum_n conj(M) x r,
 //   B2_w = sum_n conj(M) x r^2,       B3_w = sum_n conj(M) x (x - Re om) r^2
 // (r the reciprocal of |x - om|^2 on branch-A terms, which add nothing
@@ -29,7 +29,7 @@
 // branch A, |x - om|^2 r = 1,
 //   sum_n conj(M) K = sum_w ga_w/2 (B1_w - om A2_w),
 //   sum_n conj(M) L = sum_w ga_w/2 (B1_w - 2 (Im om)^2 B2_w - 2i Im om B3_w).
-// Occupied bands, a ragged tail and more frequencies form K and L per band.
+// Occupied bands form K and L per band.
 // bwd_bands (lane = g; a workgroup of four waves owns kBandTile bands and
 // 256 consecutive rows, 64 per wave, and walks a range of G' columns)
 // forms vcoul conj(e) Z per term, adds aqsmtemp[n][p] times it into
@@ -40,6 +40,7 @@
 // 256-row block; reduce_am sums the partials in a fixed order and zero-fills
 // columns >= ngpown.  No atomics: results are bitwise reproducible.
 #include "gpp_device.h"
+#include "gpp_fwd_tile.h"
 #include "gpp_internal.h"
 
 namespace gpp {
@@ -47,36 +48,27 @@ namespace gpp {
 constexpr int kBwdWaves = 4;
 constexpr int kBwdThreads = kBwdWaves * kWave;
 constexpr int kRowsPerBlock = kBwdWaves * kWave;  // g rows per workgroup (both kernels)
-// Bands per batch-inverted group of the per-band forms: 3, or 1 with more
-// than four frequencies, so that a group never holds more than 12
-// denominators (the range for which batch_reciprocal's (Im om)^2 >= 2^-60
-// lane test keeps every prefix product normal).
-constexpr int bwd_group(int nw) { return nw <= 4 ? 3 : 1; }
-// The pairs kernel's band-sum form: frequencies it takes, and bands per
-// batch-inverted group there (at most 12 / 4 = 3).
-constexpr int kPairsSumsMaxNW = 4;
+// Bands per batch-inverted group of the pairs kernel's band sums (at most 12
+// denominators) and the minimum waves per SIMD the compiler must allow (a
+// register cap; the four sums take 16 VGPRs per frequency), for nfreq 1 to 8.
 #ifndef GPP_BWD_PAIRS_GROUP
-#define GPP_BWD_PAIRS_GROUP 2
+#define GPP_BWD_PAIRS_GROUP 4, 3, 2, 2, 1, 1, 1, 1
 #endif
-constexpr int kPairsGroup = GPP_BWD_PAIRS_GROUP;
-static_assert(kPairsGroup * kPairsSumsMaxNW <= 12, "pairs groups hold at most 12 denominators");
-constexpr int kOctet = 8;                          // lanes that share one row sum
-// Minimum waves per SIMD the compiler must allow (register cap): pairs with
-// at most three frequencies (128 VGPRs; more frequencies take 3 waves, as
-// their band sums need more registers), and the bands kernel without and
-// with the daqsmtemp sums.  Bands per bands-kernel workgroup: four, so
-// that the daqsmtemp slab of two columns fills the 8 rows an octet of
-// lanes reduces.  Measured on MI355X at the adjoint workload's sizes
-// against three bands at 5 and 4 waves: the kernel with daqsmtemp 4.5 %
-// faster at nfreq 3 (7.39 against 7.74 ms; at 4 waves, with four bands,
-// it spilled and ran 28 % slower), without daqsmtemp 3 % faster at nfreq 3
-// and 2-2.5x faster at nfreq 4 and 8, where three bands at 5 waves spilled;
-// the whole adjoint 1 % and 5 % faster at nfreq 3 and 4, 1-2 % slower at
-// nfreq 5 and 8.
+constexpr int kPairsGroup[8] = {GPP_BWD_PAIRS_GROUP};
+constexpr int pairs_group(int nw) { return kPairsGroup[nw - 1]; }
 #ifndef GPP_BWD_PAIRS_WAVES
-#define GPP_BWD_PAIRS_WAVES 4
+#define GPP_BWD_PAIRS_WAVES 4, 4, 4, 3, 3, 3, 2, 2
 #endif
-constexpr int pairs_waves(int nw) { return nw <= 3 ? GPP_BWD_PAIRS_WAVES : 3; }
+constexpr int kPairsWaves[8] = {GPP_BWD_PAIRS_WAVES};
+constexpr int pairs_waves(int nw) { return kPairsWaves[nw - 1]; }
+constexpr int kOctet = 8;                          // lanes that share one row sum, and slab rows
+// The same cap of the bands kernel without and with the daqsmtemp sums.
+// Bands per bands-kernel workgroup: four, so that the daqsmtemp slab of two
+// columns fills the 8 rows an octet of lanes reduces.  Measured on MI355X at
+// the adjoint workload's sizes against three bands at 5 and 4 waves: the
+// kernel with daqsmtemp 4.5 % faster at nfreq 3 (at 4 waves, with four bands,
+// it spilled and ran 28 % slower), without daqsmtemp 3 % faster at nfreq 3
+// and 2-2.5x faster at nfreq 4 and 8, where three bands at 5 waves spilled.
 #ifndef GPP_BWD_BANDS_WAVES
 #define GPP_BWD_BANDS_WAVES 4
 #endif
@@ -98,34 +90,32 @@ constexpr int kBandsRounds = GPP_BWD_BANDS_ROUNDS;
 constexpr int kMinSegCols = 64;
 // Bands per batch-inverted group of the bands kernel: the largest divisor
 // of the band tile whose group holds at most 12 denominators.
-constexpr int bands_group(int nw)
+constexpr int bands_group(int nw, int bt)
 {
-    for (int g = kBandTile; g > 1; --g)
-        if (kBandTile % g == 0 && g * nw <= 12) return g;
+    for (int g = bt; g > 1; --g)
+        if (bt % g == 0 && g * nw <= 12) return g;
     return 1;
 }
-// daqsmtemp sums of the bands kernel: the slab holds the terms of two G'
-// columns (kBandTile rows each); every kAmCols columns (even) the four
-// waves' row sums are added and written.
-constexpr int kSlabRows = 2 * kBandTile;
+// Short grids of the bands kernel (fewer than kBandsShortBelow waves of the
+// long form) take kShortTile bands per workgroup and kShortRanges waves per
+// row tile, each on its own part of the column segment.
+constexpr int kShortTile = 2;
+constexpr int kShortRanges = 4;
+#ifndef GPP_BWD_SHORT_BELOW
+#define GPP_BWD_SHORT_BELOW 8192
+#endif
+constexpr long kBandsShortBelow = GPP_BWD_SHORT_BELOW;
+// daqsmtemp sums of the bands kernel: the slab holds the terms of 8 / BT G'
+// columns (BT rows each); every kAmCols columns the row tiles' sums are added
+// and written.
 constexpr int kAmCols = 16;
-constexpr int kAmRows = kBandTile * kAmCols;
-static_assert(kSlabRows <= kOctet && kAmCols % 2 == 0, "slab layout");
 
-// Upstream gradient scaled for the kernels: gh[w] = ga[w]/2 and
-// xgh[w][n] = wx[w][n] ga[w]/2, written once by bwd_prepare.
-__global__ void bwd_prepare(int nb, int nw, const double *__restrict__ wx,
-                            const double2 *__restrict__ ga, double2 *__restrict__ gh,
-                            double2 *__restrict__ xgh)
+// The upstream gradient scaled for the kernels, gh = ga/2 (wave-uniform; the
+// halving is exact, so x gh rounds as x ga / 2 does).
+__device__ __forceinline__ cplx half_of(const double2 *__restrict__ ga, int w)
 {
-    // 64-bit: nfreq x number_bands passes 2^31 from 2^28 bands on
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nw) gh[i] = make_double2(0.5 * ga[i].x, 0.5 * ga[i].y);
-    if (i < (long)nw * nb) {
-        const int w = (int)(i / nb);
-        const double x = wx[i];
-        xgh[i] = make_double2(0.5 * x * ga[w].x, 0.5 * x * ga[w].y);
-    }
+    const cplx g = cload(ga + w);
+    return cmake(0.5 * g.re, 0.5 * g.im);
 }
 
 // Order this wave's LDS writes before its later LDS reads (and the reverse)
@@ -175,8 +165,7 @@ __device__ inline void sx_sigma_delta(double x, double a, double b, double wi2, 
 // batch-inverted reciprocals over the BU*NW terms, masked to branch A.
 template <int NW, int BU, bool WANT_L>
 __device__ __forceinline__ void ch_bands_kl(int n, int nb, const double *__restrict__ wx,
-                                            const double2 *__restrict__ gh,
-                                            const double2 *__restrict__ xgh, double a, double b,
+                                            const double2 *__restrict__ ga, double a, double b,
                                             double wi2, double thr, bool wide, cplx (&K)[BU],
                                             cplx (&L)[BU])
 {
@@ -203,8 +192,9 @@ __device__ __forceinline__ void ch_bands_kl(int n, int nb, const double *__restr
             const int k = u * NW + w;
             const double re = mask_keep(isA[k], r[k]);
             const cplx uu = cmake(drs[k] * re, -b * re);  // conj(1/(x - om))
-            cmac(K[u], cload(gh + w), uu);
-            if (WANT_L) cmac(L[u], cload(xgh + (size_t)w * nb + n + u), cmul(uu, uu));
+            const cplx gh = half_of(ga, w);
+            cmac(K[u], gh, uu);
+            if (WANT_L) cmac(L[u], cscale(xs[k], gh), cmul(uu, uu));
         }
     }
 }
@@ -255,15 +245,12 @@ __device__ __forceinline__ PairState load_pair(const double2 *wt, const double2 
 // One branch-A term of the pairs kernel's band sums: A2 += cM r,
 // B1 += cM x r, B2 += cM x r^2, B3 += cM x dr r^2 (dr = x - Re om), with
 // the compare d > thr as the execution mask (a term off branch A adds
-// nothing, whatever its reciprocal).
+// nothing, whatever its reciprocal), all 64 lanes active before and after.
 __device__ __forceinline__ void pairs_term(double d, double thr, double r, double x, double dr,
                                            cplx cm, cplx &A2, cplx &B1, cplx &B2, cplx &B3)
 {
-#if GPP_EXEC_MASK == 2
-    unsigned long long saved;
     double xr, xr2, xdr2;
-    asm("s_mov_b64 %[sv], exec\n\t"
-        "v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+    asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
         "v_mul_f64 %[xr], %[r], %[x]\n\t"
         "v_fma_f64 %[a2r], %[r], %[cr], %[a2r]\n\t"
         "v_fma_f64 %[a2i], %[r], %[ci], %[a2i]\n\t"
@@ -275,117 +262,106 @@ __device__ __forceinline__ void pairs_term(double d, double thr, double r, doubl
         "v_fma_f64 %[b2i], %[xr2], %[ci], %[b2i]\n\t"
         "v_fma_f64 %[b3r], %[xdr2], %[cr], %[b3r]\n\t"
         "v_fma_f64 %[b3i], %[xdr2], %[ci], %[b3i]\n\t"
-        "s_mov_b64 exec, %[sv]"
-        : [sv] "=&s"(saved), [xr] "=&v"(xr), [xr2] "=&v"(xr2), [xdr2] "=&v"(xdr2),
+        "s_mov_b64 exec, -1"
+        : [xr] "=&v"(xr), [xr2] "=&v"(xr2), [xdr2] "=&v"(xdr2),
           [a2r] "+v"(A2.re), [a2i] "+v"(A2.im), [b1r] "+v"(B1.re), [b1i] "+v"(B1.im),
           [b2r] "+v"(B2.re), [b2i] "+v"(B2.im), [b3r] "+v"(B3.re), [b3i] "+v"(B3.im)
         : [d] "v"(d), [thr] "v"(thr), [r] "v"(r), [x] "s"(x), [dr] "v"(dr), [cr] "v"(cm.re),
           [ci] "v"(cm.im)
         : "vcc");
-#else
-    const double rm = mask_keep(d > thr, r);
-    const double xr = rm * x, xr2 = xr * rm, xdr2 = xr2 * dr;
-    A2.re = fma(rm, cm.re, A2.re);
-    A2.im = fma(rm, cm.im, A2.im);
-    B1.re = fma(xr, cm.re, B1.re);
-    B1.im = fma(xr, cm.im, B1.im);
-    B2.re = fma(xr2, cm.re, B2.re);
-    B2.im = fma(xr2, cm.im, B2.im);
-    B3.re = fma(xdr2, cm.re, B3.re);
-    B3.im = fma(xdr2, cm.im, B3.im);
-#endif
 }
 
-// G unoccupied bands n .. n+G-1 of one lane into the band sums: one batch
-// inversion over the G*NW denominators, then pairs_term per term.
+// The band sums of one lane over the whole groups of G unoccupied bands in
+// [n, nb): one batch inversion over a group's G*NW denominators, then
+// pairs_term per term; returns the first band left over.  Loads run ahead
+// and addresses run along as in the forward's loop (ch_bands).
 template <int NW, int G>
-__device__ __forceinline__ void pairs_sums_group(int n, int nb, int ng, gptr<double2> aqsn,
-                                                 uint32_t goff, gptr<double2> am_col,
-                                                 gptr<double> wx, const PairState &ps,
-                                                 cplx (&A2)[NW], cplx (&B1)[NW],
-                                                 cplx (&B2)[NW], cplx (&B3)[NW])
+__device__ __forceinline__ int pairs_bands(int n, int nb, int ng, gptr<double2> aqsn,
+                                           uint32_t goff, gptr<double2> am_col, gptr<double> wx,
+                                           const PairState &ps, cplx (&A2)[NW], cplx (&B1)[NW],
+                                           cplx (&B2)[NW], cplx (&B3)[NW])
 {
     constexpr int Kt = G * NW;
-    double xs[Kt], drs[Kt], dc[Kt], r[Kt];
-    // the group's aqsntemp and aqsmtemp loads go first, so that their
-    // latency overlaps the reciprocal chain
-    cplx an[G], am[G];
+    static_assert(Kt <= 12, "a group holds at most 12 denominators");
+    int left = (nb - n) / G;
+    if (left <= 0) return n;
+    const uint64_t narrow = __builtin_amdgcn_ballot_w64(!ps.wide);
+    const uint32_t row_bytes = (uint32_t)ng * (uint32_t)sizeof(double2);
+    const long step = (long)G * row_bytes;
+    BandGroup<NW, G> cur;
+    cur.load_first(n, nb, ng, aqsn, goff, wx);
+    uint64_t rows = (uint64_t)(aqsn + (size_t)n * ng);
+    Walker am_at, x_at[NW];
+    am_at.start((uint64_t)(am_col + (size_t)n * ng));
+    int more = left > 1 ? G : 0;  // bands to the next group; the last repeats
 #pragma unroll
-    for (int u = 0; u < G; ++u) {
-        an[u] = load_row_elem(aqsn + (size_t)(n + u) * ng, ng, goff);
-        am[u] = cload(am_col + (size_t)(n + u) * ng);
-    }
+    for (int w = 0; w < NW; ++w) x_at[w].start((uint64_t)(wx + (size_t)w * nb + n + more));
+    n += left * G;
+    cur.arrived();
+    for (;;) {
+        cplx am[G];
+        double xn[Kt];
 #pragma unroll
-    for (int u = 0; u < G; ++u)
+        for (int u = 0; u < G; ++u) {
+            am[u] = am_at.complex(u * row_bytes);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
-#pragma unroll
-    for (int k = 0; k < Kt; ++k) {
-        drs[k] = xs[k] - ps.a;
-        dc[k] = fma(drs[k], drs[k], ps.wi2);  // unclamped: see batch_reciprocal
-    }
-    batch_reciprocal<Kt>(dc, r, ps.wide);
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-        const cplx cM = cmul_conj(am[u], an[u]);  // conj(M) = conj(an) am
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const int k = u * NW + w;
-            pairs_term(dc[k], ps.thr, r[k], xs[k], drs[k], cM, A2[w], B1[w], B2[w], B3[w]);
+            for (int w = 0; w < NW; ++w) xn[u * NW + w] = x_at[w].real(u);
         }
+        rows += more ? step : 0;
+        more = left > 2 ? G : 0;
+        am_at.advance(step);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) x_at[w].advance(more * (long)sizeof(double));
+        double drs[Kt], d[Kt], c[Kt], r[Kt];
+#pragma unroll
+        for (int k = 0; k < Kt; ++k) {
+            drs[k] = cur.xs[k] - ps.a;
+            d[k] = fma(drs[k], drs[k], ps.wi2);  // unclamped: see batch_prefix
+        }
+        const double all = batch_prefix<Kt>(d, c);
+        batch_back<Kt>(d, c, all, r);
+        if (__builtin_expect(batch_misses(all, narrow) != 0, 0)) one_by_one<Kt>(d, r);
+        cplx cM[G];
+#pragma unroll
+        for (int u = 0; u < G; ++u) cM[u] = cmul_conj(am[u], cur.an[u]);  // conj(an) am
+#pragma unroll
+        for (int u = 0; u < G; ++u) cur.an[u] = load_elem_at(rows, u * row_bytes, goff);
+#pragma unroll
+        for (int u = 0; u < G; ++u)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int k = u * NW + w;
+                pairs_term(d[k], ps.thr, r[k], cur.xs[k], drs[k], cM[u], A2[w], B1[w], B2[w],
+                           B3[w]);
+            }
+        if (--left == 0) return n;
+#pragma unroll
+        for (int k = 0; k < Kt; ++k) cur.xs[k] = xn[k];
     }
 }
 
-// Bands [n, n_end) of one lane in the per-band form: K and L (and, for
-// occupied bands, KS and LS) per band, then Ge += conj(M) Z and
-// Gw += conj(M) W.
+// Occupied bands [0, nocc) of one lane: K and L (Coulomb hole) and KS and LS
+// (exchange) per band, then Ge += conj(M) Z and Gw += conj(M) W.
 template <int NW>
-__device__ __forceinline__ void pairs_per_band(int n, int n_end, int nb, int nv, int ng,
+__device__ __forceinline__ void pairs_occupied(int nocc, int nb, int ng,
                                                const double2 *__restrict__ aqsn,
                                                const double2 *__restrict__ am_col,
                                                const double *__restrict__ wx,
-                                               const double2 *__restrict__ gh,
-                                               const double2 *__restrict__ xgh,
+                                               const double2 *__restrict__ ga,
                                                const double2 *__restrict__ gs,
                                                const PairState &ps, uint32_t goff, cplx &Ge,
                                                cplx &Gw)
 {
-    constexpr int G = bwd_group(NW);
     const cplx cw = cmake(ps.om.re, -ps.om.im);  // conj(om)
-    while (n < n_end) {
-        // bands n .. n+cnt-1 form one batch-inverted group
-        const bool occ = n < nv;
-        const int cnt = (!occ && n + G <= n_end) ? G : 1;
-        cplx K[G], L[G];
-        if (cnt == G) {
-            ch_bands_kl<NW, G, true>(n, nb, wx, gh, xgh, ps.a, ps.b, ps.wi2, ps.thr, ps.wide, K,
-                                     L);
-        } else {
-            cplx K1[1], L1[1];
-            ch_bands_kl<NW, 1, true>(n, nb, wx, gh, xgh, ps.a, ps.b, ps.wi2, ps.thr, ps.wide, K1,
-                                     L1);
-            K[0] = K1[0];
-            L[0] = L1[0];
-        }
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            if (u >= cnt) break;  // wave-uniform
-            const int nn = n + u;
-            cplx Z = cmul(cw, K[u]);
-            cplx W = L[u];
-            if (nn < nv) {
-                cplx KS, LS;
-                sx_band_kl<NW>(nn, nb, wx, gs, ps.a, ps.b, ps.wi2, ps.wtr, ps.thr, KS, LS);
-                Z = cadd(Z, KS);
-                W = cadd(W, LS);
-            }
-            const cplx an = load_row_elem(as_global(aqsn) + (size_t)nn * ng, ng, goff);
-            const cplx am = cload(am_col + (size_t)nn * ng);
-            const cplx cM = cmul_conj(am, an);  // conj(M) = conj(an) am
-            cmac(Ge, cM, Z);
-            cmac(Gw, cM, W);
-        }
-        n += cnt;
+    for (int n = 0; n < nocc; ++n) {
+        cplx K[1], L[1], KS, LS;
+        ch_bands_kl<NW, 1, true>(n, nb, wx, ga, ps.a, ps.b, ps.wi2, ps.thr, ps.wide, K, L);
+        sx_band_kl<NW>(n, nb, wx, gs, ps.a, ps.b, ps.wi2, ps.wtr, ps.thr, KS, LS);
+        const cplx an = load_row_elem(as_global(aqsn) + (size_t)n * ng, ng, goff);
+        const cplx am = cload(am_col + (size_t)n * ng);
+        const cplx cM = cmul_conj(am, an);  // conj(M) = conj(an) am
+        cmac(Ge, cM, cadd(cmul(cw, K[0]), KS));
+        cmac(Gw, cM, cadd(L[0], LS));
     }
 }
 
@@ -398,9 +374,9 @@ __attribute__((amdgpu_waves_per_eu(pairs_waves(NW))))
 bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restrict__ aqsm,
           const double2 *__restrict__ aqsn, const double2 *__restrict__ ieps,
           const double2 *__restrict__ wt, const double *__restrict__ vcoul,
-          const double *__restrict__ wx, const double2 *__restrict__ gh,
-          const double2 *__restrict__ xgh, const double2 *__restrict__ gs,
-          double2 *__restrict__ grad_wt, double2 *__restrict__ grad_ieps)
+          const double *__restrict__ wx, const double2 *__restrict__ ga,
+          const double2 *__restrict__ gs, double2 *__restrict__ grad_wt,
+          double2 *__restrict__ grad_ieps)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -416,35 +392,31 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
     const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
 
     cplx Ge = cmake(0.0, 0.0), Gw = cmake(0.0, 0.0);
-    // occupied bands
     const int nocc = nv < nb ? nv : nb;
-    pairs_per_band<NW>(0, nocc, nb, nv, ng, aqsn, am_col, wx, gh, xgh, gs, ps, goff, Ge, Gw);
+    pairs_occupied<NW>(nocc, nb, ng, aqsn, am_col, wx, ga, gs, ps, goff, Ge, Gw);
+    cplx A2[NW], B1[NW], B2[NW], B3[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) A2[w] = B1[w] = B2[w] = B3[w] = cmake(0.0, 0.0);
     int n = nocc;
-    if constexpr (NW <= kPairsSumsMaxNW) {
-        cplx A2[NW], B1[NW], B2[NW], B3[NW];
+    n = pairs_bands<NW, pairs_group(NW)>(n, nb, ng, as_global(aqsn), goff, as_global(am_col),
+                                         as_global(wx), ps, A2, B1, B2, B3);
+    if constexpr (pairs_group(NW) > 1)
+        pairs_bands<NW, 1>(n, nb, ng, as_global(aqsn), goff, as_global(am_col), as_global(wx), ps,
+                           A2, B1, B2, B3);
+    // sum_n conj(M) K and sum_n conj(M) L from the band sums
+    cplx SK = cmake(0.0, 0.0), SL = cmake(0.0, 0.0);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) A2[w] = B1[w] = B2[w] = B3[w] = cmake(0.0, 0.0);
-        for (; n + kPairsGroup <= nb; n += kPairsGroup)
-            pairs_sums_group<NW, kPairsGroup>(opaque_uniform(n), nb, ng, as_global(aqsn), goff,
-                                              as_global(am_col), as_global(wx), ps, A2, B1, B2,
-                                              B3);
-        // sum_n conj(M) K and sum_n conj(M) L from the band sums
-        cplx SK = cmake(0.0, 0.0), SL = cmake(0.0, 0.0);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const cplx h = cload(gh + w);
-            const cplx k = cadd(B1[w], cmul(cmake(-ps.a, -ps.b), A2[w]));  // B1 - om A2
-            // B1 - 2 (Im om)^2 B2 - 2i (Im om) B3
-            const cplx l = cmake(fma(ps.b2, B3[w].im, fma(-ps.wi2x2, B2[w].re, B1[w].re)),
-                                 fma(-ps.b2, B3[w].re, fma(-ps.wi2x2, B2[w].im, B1[w].im)));
-            cmac(SK, h, k);
-            cmac(SL, h, l);
-        }
-        cmac(Ge, cmake(ps.om.re, -ps.om.im), SK);
-        Gw = cadd(Gw, SL);
+    for (int w = 0; w < NW; ++w) {
+        const cplx h = half_of(ga, w);
+        const cplx k = cadd(B1[w], cmul(cmake(-ps.a, -ps.b), A2[w]));  // B1 - om A2
+        // B1 - 2 (Im om)^2 B2 - 2i (Im om) B3
+        const cplx l = cmake(fma(ps.b2, B3[w].im, fma(-ps.wi2x2, B2[w].re, B1[w].re)),
+                             fma(-ps.b2, B3[w].re, fma(-ps.wi2x2, B2[w].im, B1[w].im)));
+        cmac(SK, h, k);
+        cmac(SL, h, l);
     }
-    // a ragged tail, or every unoccupied band with more frequencies
-    pairs_per_band<NW>(n, nb, nb, nv, ng, aqsn, am_col, wx, gh, xgh, gs, ps, goff, Ge, Gw);
+    cmac(Ge, cmake(ps.om.re, -ps.om.im), SK);
+    Gw = cadd(Gw, SL);
 
     if (valid) {
         const double v = vcoul[g];
@@ -461,226 +433,277 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
 }
 
 // ---- bands kernel: daqsntemp and the daqsmtemp partials -------------------
-// LDS of one bands workgroup's daqsmtemp sums: each wave's slab of
-// per-lane terms (kBandTile bands x two G' columns) and the waves' row sums
-// of up to kAmCols columns.
+// LDS of the daqsmtemp sums of four waves (the row tiles of 256 rows): each
+// wave's slab of per-lane terms (8 rows: BT bands x 8 / BT columns) and the
+// waves' row sums of up to kAmCols columns.  A row is 8 entries (128 bytes)
+// longer than the wave, see am_column_done.
+template <int BT>
 struct AmStage {
-    double2 slab[kBwdWaves][kSlabRows][kWave];
-    double2 red[kBwdWaves][kAmRows];
+    double2 slab[kBwdWaves][kOctet][kWave + kOctet];
+    double2 red[kBwdWaves][BT * kAmCols];
 };
 
-// Where a bands workgroup's daqsmtemp sums go: the slab row of band u at
-// column p is ((p - p_lo) % 2) kBandTile + u; `chunk` is the first column of
-// the rows waiting in red.
+// Where a wave's daqsmtemp terms go.  `first` is the first column whose sums
+// wait in red.
+template <int BT>
 struct AmCtx {
-    AmStage *st;
+    AmStage<BT> *st;
     double2 *part;  // am_part: [256-row block][nb][np]
-    int wid, lane, gblk, n0, nb, np, p_lo, p_hi, chunk;
+    int wid, lane, gblk, n0, nb, np, first;
 };
 
 // This lane's daqsmtemp term of band u at column p: an conj(vcoul conj(e) Z).
-__device__ __forceinline__ void am_put(AmCtx &a, int p, int u, cplx an, cplx vz)
+template <int BT>
+__device__ __forceinline__ void am_put(AmCtx<BT> &a, int p, int u, cplx an, cplx vz)
 {
+    constexpr int C = kOctet / BT;
     const cplx t = cmul_conj(an, vz);
-    a.st->slab[a.wid][((p - a.p_lo) & 1) * kBandTile + u][a.lane] = make_double2(t.re, t.im);
+    a.st->slab[a.wid][((p - a.first) % C) * BT + u][a.lane] = make_double2(t.re, t.im);
 }
 
-// After column p: when the slab is full (two columns) or p is the range's
-// last column, add each slab row over the wave (lane (tj, tk) adds the
-// entries tk, tk + 8, ..., tk + 56 of row tj, then the octet adds its 8
+// After column p: when the slab is full (8 / BT columns) or p is the last of
+// the columns up to `end`, add each slab row over the wave (lane (tj, tk) adds
+// the entries tk, tk + 8, ..., tk + 56 of row tj, then the octet adds its 8
 // sums) into red.  An octet thus reads 128 contiguous bytes at a time, and
-// the rows start at staggered offsets ((i + tj) mod 8), so that the two
-// octets the LDS serves per clock fall in different halves of its banks:
-// measured on gfx950 (gpp_mb_lds patterns 2 and 1), such a 16-byte read
-// takes 4 LDS cycles with no bank conflict, against 8 cycles (4 of them
-// conflict stalls) when each lane reads 8 consecutive entries.  Every
-// kAmCols columns, and at the end, add red over the four waves and write
-// the partials.  Every wave of the workgroup calls this for the same
-// columns.
-__device__ __forceinline__ void am_column_done(AmCtx &a, int p)
+// the row length shifts row tj by tj * 128 bytes, so that the two octets the
+// LDS serves per clock fall in different halves of its banks: measured on
+// gfx950 (gpp_mb_lds patterns 2 and 1), such a 16-byte read takes 4 LDS
+// cycles with no bank conflict, against 8 cycles (4 of them conflict stalls)
+// when each lane reads 8 consecutive entries.  With the shift in the row
+// length the eight reads share one address register.
+template <int BT>
+__device__ __forceinline__ void am_column_done(AmCtx<BT> &a, int p, int end)
 {
-    const int c = (p - a.p_lo) & 1;
-    const bool last = p + 1 == a.p_hi;
-    if (c == 1 || last) {
-        const int rows = (c + 1) * kBandTile;
-        const int base = (p - c - a.chunk) * kBandTile;
-        wave_lds_sync();
-        const int tj = a.lane >> 3, tk = a.lane & (kOctet - 1);
-        double sr = 0.0, si = 0.0;
-        if (tj < rows) {
+    constexpr int C = kOctet / BT;
+    const int c = (p - a.first) % C;
+    if (c + 1 < C && p + 1 < end) return;
+    const int rows = (c + 1) * BT;
+    wave_lds_sync();
+    const int tj = a.lane >> 3, tk = a.lane & (kOctet - 1);
+    double sr = 0.0, si = 0.0;
+    if (tj < rows) {
 #pragma unroll
-            for (int i = 0; i < kOctet; ++i) {
-                const double2 v = a.st->slab[a.wid][tj][tk + kOctet * ((i + tj) & (kOctet - 1))];
-                sr += v.x;
-                si += v.y;
-            }
+        for (int i = 0; i < kOctet; ++i) {
+            const double2 v = a.st->slab[a.wid][tj][tk + kOctet * i];
+            sr += v.x;
+            si += v.y;
         }
-        sr = octet_sum(sr);
-        si = octet_sum(si);
-        if (tk == 0 && tj < rows) a.st->red[a.wid][base + tj] = make_double2(sr, si);
-        wave_lds_sync();
     }
-    if (p + 1 - a.chunk == kAmCols || last) {
-        __syncthreads();
-        const int rows = (p + 1 - a.chunk) * kBandTile;
-        const int t = threadIdx.x;
-        if (t < 2 * rows) {
-            const int j = t >> 1, comp = t & 1;
-            double s = 0.0;
-#pragma unroll
-            for (int k = 0; k < kBwdWaves; ++k) {
-                const double2 v = a.st->red[k][j];
-                s += comp ? v.y : v.x;
-            }
-            const int col = a.chunk + j / kBandTile, n = a.n0 + j % kBandTile;
-            if (n < a.nb)
-                reinterpret_cast<double *>(a.part + ((size_t)a.gblk * a.nb + n) * a.np + col)[comp] = s;
-        }
-        __syncthreads();
-        a.chunk = p + 1;
-    }
+    sr = octet_sum(sr);
+    si = octet_sum(si);
+    if (tk == 0 && tj < rows) a.st->red[a.wid][(p - c - a.first) * BT + tj] = make_double2(sr, si);
+    wave_lds_sync();
 }
 
-// Fast form of one workgroup's p loop: every band n0 .. n0+kBandTile-1 is
-// unoccupied and below nb.  With u_w = (x_w - om) r_w (r_w the masked
-// reciprocal of |x_w - om|^2),
-//   K = sum_w gh_w u_w = S - om R,  S = sum_w xgh_w r_w,  R = sum_w gh_w r_w,
-// so vcoul conj(e) Z = vcoul conj(e) conj(om) K = c1 S - c2 R with the
-// per-pair constants c1 = vcoul conj(e om) and c2 = vcoul conj(e) |om|^2.
-template <int NW, bool AM>
-__device__ __forceinline__ void bands_fast(int nb, int ng, int n0, int gc, double vc,
-                                           gptr<double2> aqsm, gptr<double2> ieps,
-                                           gptr<double2> wt, gptr<double> wx,
-                                           gptr<double2> gh, gptr<double2> xgh,
-                                           const cplx (&an)[kBandTile], AmCtx &amc,
-                                           cplx (&acc)[kBandTile])
+// Adds the row tiles' sums of the columns [a.first, end) and writes them;
+// every wave of the workgroup calls it.
+template <int BT>
+__device__ __forceinline__ void am_flush(AmCtx<BT> &a, int end)
 {
-    constexpr int G = bands_group(NW);
-    constexpr int Kt = G * NW;
-    const int p_lo = amc.p_lo, p_hi = amc.p_hi;
-    // om and e of the next column are loaded one iteration ahead, so their
-    // latency overlaps this column's arithmetic
-    cplx om_next = cload(wt + (size_t)p_lo * ng + gc), e_next = cload(ieps + (size_t)p_lo * ng + gc);
-    for (int p = p_lo; p < p_hi; ++p) {
-        const int nfirst = opaque_uniform(n0);  // reload x and xgh per p
-        const cplx om = om_next, e = e_next;
-        const int pn = p + 1 < p_hi ? p + 1 : p;
-        om_next = cload(wt + (size_t)pn * ng + gc);
-        e_next = cload(ieps + (size_t)pn * ng + gc);
-        const double a = om.re, b = om.im;
-        const double wi2 = b * b;
-        const double wtr = fma(a, a, wi2);
-        const double thr = branch_a_threshold(wtr);
-        const bool wide = wi2 >= kMinUnclampedWi2;
-        const cplx vce = cmake(vc * e.re, -(vc * e.im));  // vcoul conj(e)
-        const cplx c1 = cmul(vce, cmake(a, -b));
-        const cplx c2 = cscale(wtr, vce);
+    __syncthreads();
+    const int rows = end > a.first ? (end - a.first) * BT : 0;
+    const int t = threadIdx.x % kBwdThreads;
+    if (t < 2 * rows) {
+        const int j = t >> 1, comp = t & 1;
+        double s = 0.0;
 #pragma unroll
-        for (int u0 = 0; u0 < kBandTile; u0 += G) {
-            const int n = nfirst + u0;
-            double xs[Kt], dc[Kt], r[Kt];
-            bool isA[Kt];
+        for (int k = 0; k < kBwdWaves; ++k) {
+            const double2 v = a.st->red[k][j];
+            s += comp ? v.y : v.x;
+        }
+        const int col = a.first + j / BT, n = a.n0 + j % BT;
+        if (n < a.nb)
+            reinterpret_cast<double *>(a.part + ((size_t)a.gblk * a.nb + n) * a.np + col)[comp] = s;
+    }
+    __syncthreads();
+}
+
+// Fast form of a wave's columns [p_lo, p_hi): every band n0 .. n0+BT-1 is
+// unoccupied and below nb.  With r_w the masked reciprocal of |x_w - om|^2,
+//   vcoul conj(e) Z = vcoul conj(e om) sum_w gh_w (x_w - om) r_w.
+// Up to four frequencies (FACTOR) it is the sum of (x_w c1_w - c2_w) r_w with
+// the constants c1_w = gh_w vcoul conj(e om) and c2_w = gh_w vcoul conj(e)
+// |om|^2 of a pair: two FMAs per term for the factor, two for the sum, and
+// per column eight products per frequency.  With more, whose constants would
+// spill, c1 S - c2 R with S = sum_w gh_w (x_w r_w) and R = sum_w gh_w r_w.
+// Either way the loop needs x and gh only, in scalar registers: x gh itself,
+// 12 complex values per column at nfreq 3 from the scalar cache, took 15
+// scalar loads with their waits per column against 4 here.  256 bands x 8192
+// rows x 409 columns, whole adjoint at nfreq 1, 2, 4: 1977 -> 1806, 2740 ->
+// 2647, 4452 -> 4252 us (FACTOR at 5, 6 and 8 instead ran 6-20 % slower than
+// before).  The frequencies of the band tile stay in scalar registers where
+// HOLD.
+template <int NW, int BT, bool AM>
+struct BandsFast {
+    static constexpr int G = bands_group(NW, BT);
+    static constexpr int Kt = G * NW;
+    static constexpr bool FACTOR = NW <= 4;
+    static constexpr bool HOLD = NW * BT <= 20;
+    double xs[BT * NW];
+    cplx gh[NW];
+    cplx om_next, e_next;
+
+    __device__ __forceinline__ void frequencies(int n, int nb, gptr<double> wx)
+    {
 #pragma unroll
-            for (int u = 0; u < G; ++u)
+        for (int u = 0; u < BT; ++u)
 #pragma unroll
-                for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
+            for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
+    }
+    __device__ __forceinline__ void start(int nb, int ng, int n0, int gc, int p,
+                                          gptr<double2> ieps, gptr<double2> wt, gptr<double> wx,
+                                          const double2 *__restrict__ ga)
+    {
+        om_next = cload(wt + (size_t)p * ng + gc);
+        e_next = cload(ieps + (size_t)p * ng + gc);
+        if (HOLD) frequencies(n0, nb, wx);
 #pragma unroll
-            for (int k = 0; k < Kt; ++k) {
-                const double dr = xs[k] - a;
-                const double wd = fma(dr, dr, wi2);
-                isA[k] = wd > thr;
-                dc[k] = wd;  // unclamped: see batch_reciprocal
-            }
-            batch_reciprocal<Kt>(dc, r, wide);
+        for (int w = 0; w < NW; ++w) gh[w] = half_of(ga, w);
+    }
+    // Columns [p, end) of the wave's [.., p_hi).
+    __device__ __forceinline__ void columns(int p, int end, int p_hi, int nb, int ng, int n0,
+                                            int gc, double vc, gptr<double2> aqsm,
+                                            gptr<double2> ieps, gptr<double2> wt,
+                                            gptr<double> wx, const cplx (&an)[BT],
+                                            AmCtx<BT> &amc, cplx (&acc)[BT])
+    {
+        const uint32_t row_bytes = (uint32_t)ng * (uint32_t)sizeof(double2);
+        Walker am_at;
+        am_at.start((uint64_t)(aqsm + (size_t)n0 * ng + p));
+        for (; p < end; ++p) {
+            // om and e of the next column are loaded one iteration ahead, so
+            // their latency overlaps this column's arithmetic
+            const cplx om = om_next, e = e_next;
+            const int pn = p + 1 < p_hi ? p + 1 : p;
+            om_next = cload(wt + (size_t)pn * ng + gc);
+            e_next = cload(ieps + (size_t)pn * ng + gc);
+            cplx am[BT];
 #pragma unroll
-            for (int u = 0; u < G; ++u) {
-#if GPP_EXEC_MASK == 2
-                // the first frequency starts S and R through a select, the
-                // others add under an execution mask written by the compare
-                const double r0 = mask_keep(isA[u * NW], r[u * NW]);
-                const cplx xg0 = cload(xgh + n + u);
-                const cplx g0 = cload(gh);
-                cplx S = cmake(r0 * xg0.re, r0 * xg0.im), R = cmake(r0 * g0.re, r0 * g0.im);
-#pragma unroll
-                for (int w = 1; w < NW; ++w) {
-                    const int k = u * NW + w;
-                    const cplx xg = cload(xgh + (size_t)w * nb + n + u);
-                    const cplx g = cload(gh + w);
-                    unsigned long long saved;
-                    asm("s_mov_b64 %[sv], exec\n\t"
-                        "v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
-                        "v_fma_f64 %[sr], %[r], %[xr], %[sr]\n\t"
-                        "v_fma_f64 %[si], %[r], %[xi], %[si]\n\t"
-                        "v_fma_f64 %[rr], %[r], %[gr], %[rr]\n\t"
-                        "v_fma_f64 %[ri], %[r], %[gi], %[ri]\n\t"
-                        "s_mov_b64 exec, %[sv]"
-                        : [sv] "=&s"(saved), [sr] "+v"(S.re), [si] "+v"(S.im), [rr] "+v"(R.re),
-                          [ri] "+v"(R.im)
-                        : [d] "v"(dc[k]), [thr] "v"(thr), [r] "v"(r[k]), [xr] "s"(xg.re),
-                          [xi] "s"(xg.im), [gr] "s"(g.re), [gi] "s"(g.im)
-                        : "vcc");
-                }
-#else
-                cplx S = cmake(0.0, 0.0), R = cmake(0.0, 0.0);
+            for (int u = 0; u < BT; ++u) am[u] = am_at.complex(u * row_bytes);
+            am_at.advance(sizeof(double2));
+            if (!HOLD) frequencies(opaque_uniform(n0), nb, wx);
+            const double a = om.re, b = om.im;
+            const double wi2 = b * b;
+            const double wtr = fma(a, a, wi2);
+            const double thr = branch_a_threshold(wtr);
+            const uint64_t narrow = __builtin_amdgcn_ballot_w64(!(wi2 >= kMinUnclampedWi2));
+            const cplx vce = cmake(vc * e.re, -(vc * e.im));  // vcoul conj(e)
+            const cplx vcw = cmul(vce, cmake(a, -b));         // vcoul conj(e om)
+            const cplx vct = cscale(wtr, vce);
+            cplx c1[FACTOR ? NW : 1], c2[FACTOR ? NW : 1];
+            if constexpr (FACTOR) {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
-                    const int k = u * NW + w;
-                    const double re = mask_keep(isA[k], r[k]);
-                    const cplx xg = cload(xgh + (size_t)w * nb + n + u);
-                    const cplx g = cload(gh + w);
-                    S.re = fma(re, xg.re, S.re);
-                    S.im = fma(re, xg.im, S.im);
-                    R.re = fma(re, g.re, R.re);
-                    R.im = fma(re, g.im, R.im);
+                    c1[w] = cmul(gh[w], vcw);
+                    c2[w] = cmul(gh[w], vct);
                 }
-#endif
-                const cplx vZ = cmake(c1.re * S.re - c1.im * S.im - c2.re * R.re + c2.im * R.im,
-                                      c1.re * S.im + c1.im * S.re - c2.re * R.im - c2.im * R.re);
-                const cplx am = cload(aqsm + (size_t)(n + u) * ng + p);
-                cmac(acc[u0 + u], am, vZ);
-                if constexpr (AM) am_put(amc, p, u0 + u, an[u0 + u], vZ);
             }
-            // one group's reciprocal chain at a time (register pressure)
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u0 = 0; u0 < BT; u0 += G) {
+                double d[Kt], c[Kt], r[Kt];
+#pragma unroll
+                for (int k = 0; k < Kt; ++k) {
+                    const double dr = xs[u0 * NW + k] - a;
+                    d[k] = fma(dr, dr, wi2);  // unclamped: see batch_prefix
+                }
+                const double all = batch_prefix<Kt>(d, c);
+                batch_back<Kt>(d, c, all, r);
+                if (__builtin_expect(batch_misses(all, narrow) != 0, 0)) one_by_one<Kt>(d, r);
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    // the first frequency starts the sums through a select,
+                    // the others add under an execution mask written by the
+                    // compare (all lanes are active here)
+                    const int k0 = u * NW;
+                    const double r0 = mask_keep(d[k0] > thr, r[k0]);
+                    const double x0 = xs[u0 * NW + k0];
+                    cplx vz;
+                    if constexpr (FACTOR) {
+                        vz = cmake(r0 * fma(x0, c1[0].re, -c2[0].re),
+                                   r0 * fma(x0, c1[0].im, -c2[0].im));
+#pragma unroll
+                        for (int w = 1; w < NW; ++w) {
+                            const double x = xs[u0 * NW + k0 + w];
+                            const cplx f = cmake(fma(x, c1[w].re, -c2[w].re),
+                                                 fma(x, c1[w].im, -c2[w].im));
+                            asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+                                "v_fma_f64 %[zr], %[r], %[fr], %[zr]\n\t"
+                                "v_fma_f64 %[zi], %[r], %[fi], %[zi]\n\t"
+                                "s_mov_b64 exec, -1"
+                                : [zr] "+v"(vz.re), [zi] "+v"(vz.im)
+                                : [d] "v"(d[k0 + w]), [thr] "v"(thr), [r] "v"(r[k0 + w]),
+                                  [fr] "v"(f.re), [fi] "v"(f.im)
+                                : "vcc");
+                        }
+                    } else {
+                        cplx S = cscale(r0 * x0, gh[0]), R = cscale(r0, gh[0]);
+#pragma unroll
+                        for (int w = 1; w < NW; ++w) {
+                            double rx;
+                            asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+                                "v_mul_f64 %[rx], %[r], %[x]\n\t"
+                                "v_fma_f64 %[rr], %[r], %[gr], %[rr]\n\t"
+                                "v_fma_f64 %[ri], %[r], %[gi], %[ri]\n\t"
+                                "v_fma_f64 %[sr], %[rx], %[gr], %[sr]\n\t"
+                                "v_fma_f64 %[si], %[rx], %[gi], %[si]\n\t"
+                                "s_mov_b64 exec, -1"
+                                : [rx] "=&v"(rx), [sr] "+v"(S.re), [si] "+v"(S.im),
+                                  [rr] "+v"(R.re), [ri] "+v"(R.im)
+                                : [d] "v"(d[k0 + w]), [thr] "v"(thr), [r] "v"(r[k0 + w]),
+                                  [x] "s"(xs[u0 * NW + k0 + w]), [gr] "s"(gh[w].re),
+                                  [gi] "s"(gh[w].im)
+                                : "vcc");
+                        }
+                        const cplx t = cmul(vct, R);
+                        vz = cmul(vcw, S);
+                        vz = cmake(vz.re - t.re, vz.im - t.im);
+                    }
+                    cmac(acc[u0 + u], am[u0 + u], vz);
+                    if constexpr (AM) am_put(amc, p, u0 + u, an[u0 + u], vz);
+                }
+                // one group's reciprocal chain at a time (register pressure)
+                if (G < BT) __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (AM) am_column_done(amc, p, end);
         }
-        if constexpr (AM) am_column_done(amc, p);
     }
-}
+};
 
-// Generic form: occupied bands (exchange terms) and a ragged last tile.
-template <int NW, bool AM>
-__device__ __forceinline__ void bands_generic(int nb, int nv, int ng, int n0, int gc, bool valid,
+// Generic form of the columns [p, end): occupied bands (exchange terms) and a
+// ragged last tile.
+template <int NW, int BT, bool AM>
+__device__ __forceinline__ void bands_generic(int p, int end, int nb, int nv, int ng, int n0,
+                                              int gc, bool valid,
                                               const double2 *__restrict__ aqsm,
                                               const double2 *__restrict__ ieps,
                                               const double2 *__restrict__ wt,
                                               const double *__restrict__ vcoul,
                                               const double *__restrict__ wx,
-                                              const double2 *__restrict__ gh,
+                                              const double2 *__restrict__ ga,
                                               const double2 *__restrict__ gs,
-                                              const cplx (&an)[kBandTile], AmCtx &amc,
-                                              cplx (&acc)[kBandTile])
+                                              const cplx (&an)[BT], AmCtx<BT> &amc,
+                                              cplx (&acc)[BT])
 {
-    constexpr int G = bands_group(NW);
-    for (int p = amc.p_lo; p < amc.p_hi; ++p) {
+    constexpr int G = bands_group(NW, BT);
+    for (; p < end; ++p) {
         const PairState ps = load_pair(wt, ieps, vcoul, p, ng, gc, valid);
         const cplx vce = cmake(ps.ve.re, -ps.ve.im);           // vcoul conj(e)
         const cplx vcw = cmul(vce, cmake(ps.om.re, -ps.om.im));  // vcoul conj(e om)
 #pragma unroll
-        for (int u0 = 0; u0 < kBandTile; u0 += G) {
+        for (int u0 = 0; u0 < BT; u0 += G) {
             const int n = n0 + u0;
             cplx K[G], L[G];
             const bool full = n + G <= nb && n >= nv;
             if (full) {
-                ch_bands_kl<NW, G, false>(n, nb, wx, gh, nullptr, ps.a, ps.b, ps.wi2, ps.thr,
-                                          ps.wide, K, L);
+                ch_bands_kl<NW, G, false>(n, nb, wx, ga, ps.a, ps.b, ps.wi2, ps.thr, ps.wide, K, L);
             } else {
 #pragma unroll
                 for (int u = 0; u < G; ++u) {
                     K[u] = cmake(0.0, 0.0);
                     if (n + u < nb) {
                         cplx K1[1], L1[1];
-                        ch_bands_kl<NW, 1, false>(n + u, nb, wx, gh, nullptr, ps.a, ps.b,
-                                                  ps.wi2, ps.thr, ps.wide, K1, L1);
+                        ch_bands_kl<NW, 1, false>(n + u, nb, wx, ga, ps.a, ps.b, ps.wi2, ps.thr,
+                                                  ps.wide, K1, L1);
                         K[u] = K1[0];
                     }
                 }
@@ -703,47 +726,60 @@ __device__ __forceinline__ void bands_generic(int nb, int nv, int ng, int n0, in
                 if constexpr (AM) am_put(amc, p, u0 + u, an[u0 + u], vZ);
             }
         }
-        if constexpr (AM) am_column_done(amc, p);
+        if constexpr (AM) am_column_done(amc, p, end);
     }
 }
 
-// Workgroup = kBandTile bands x 256 rows (one 64-row tile per wave) x one
-// segment of the G' range; band tile fastest (neighbouring workgroups
-// share the rows of wtilde/I_eps), then row block, then segment.  One
-// segment writes daqsntemp itself, several write partial sums (grad_an may
-// be NULL: daqsmtemp only).  With AM, also the daqsmtemp partials of the
-// workgroup's bands, rows and columns.
-template <int NW, bool AM>
-__global__ void __launch_bounds__(kBwdThreads)
-__attribute__((amdgpu_waves_per_eu(AM ? GPP_BWD_BANDS_AM_WAVES : GPP_BWD_BANDS_WAVES)))
+// Workgroup = BT bands x 256 rows (four 64-row tiles) x one segment of the G'
+// range, which PW waves per row tile share; band tile fastest (neighbouring
+// workgroups share the rows of wtilde/I_eps), then row block, then segment.
+// One segment writes daqsntemp itself, several write partial sums (grad_an
+// may be NULL: daqsmtemp only).  With AM, also the daqsmtemp partials of the
+// workgroup's bands, rows and columns.  The columns go in steps of kAmCols
+// per wave, the same number for every wave, since a step ends with a barrier.
+template <int NW, int BT, int PW, bool AM>
+__global__ void __launch_bounds__(kBwdThreads * PW)
+__attribute__((amdgpu_waves_per_eu(PW > 1 ? 4 : AM ? GPP_BWD_BANDS_AM_WAVES
+                                                   : GPP_BWD_BANDS_WAVES)))
 bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
           const double2 *__restrict__ aqsm, const double2 *__restrict__ aqsn,
           const double2 *__restrict__ ieps, const double2 *__restrict__ wt,
           const double *__restrict__ vcoul, const double *__restrict__ wx,
-          const double2 *__restrict__ gh, const double2 *__restrict__ xgh,
-          const double2 *__restrict__ gs, double2 *__restrict__ grad_an,
-          double2 *__restrict__ am_part)
+          const double2 *__restrict__ ga, const double2 *__restrict__ gs,
+          double2 *__restrict__ grad_an, double2 *__restrict__ am_part)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wid = wave % kBwdWaves, range = wave / kBwdWaves;
     const long wg = xcd_remap(blockIdx.x, gridDim.x);
     if (wg >= nwg) return;  // the whole workgroup leaves together
     const long per_seg = (long)ngb * nbt;
-    const int seg = (int)(wg / per_seg);
+    const int seg = __builtin_amdgcn_readfirstlane((int)(wg / per_seg));
     const long in_seg = wg - (long)seg * per_seg;
-    const int gblk = (int)(in_seg / nbt);
-    const int n0 = (int)(in_seg - (long)gblk * nbt) * kBandTile;
+    const int gblk = __builtin_amdgcn_readfirstlane((int)(in_seg / nbt));
+    const int n0 = __builtin_amdgcn_readfirstlane((int)(in_seg - (long)gblk * nbt) * BT);
     double2 *const dst = grad_an ? grad_an + (size_t)seg * nb * ng : nullptr;
     const int g = gblk * kRowsPerBlock + wid * kWave + lane;
     const bool valid = g < ng;
     const int gc = valid ? g : ng - 1;
 
-    AmCtx amc;
-    amc.st = nullptr;
-    if constexpr (AM) {
-        __shared__ AmStage stage;
-        amc.st = &stage;
-    }
+    // the wave's columns: range `range` of the segment's
+    const int seg_lo = __builtin_amdgcn_readfirstlane((int)((long)np * seg / nps));
+    const int seg_hi = __builtin_amdgcn_readfirstlane((int)((long)np * (seg + 1) / nps));
+    const int per = (seg_hi - seg_lo + PW - 1) / PW;
+    const int lo_r = seg_lo + range * per;
+    const int p_lo = lo_r < seg_hi ? lo_r : seg_hi;
+    const int p_hi = p_lo + per < seg_hi ? p_lo + per : seg_hi;
+
+    // LDS: the daqsmtemp stages of the PW ranges; afterwards the ranges'
+    // daqsntemp sums
+    constexpr size_t stage_bytes = AM ? sizeof(AmStage<BT>) * PW : 0;
+    constexpr size_t sums_bytes = sizeof(double2) * (PW - 1) * kBwdWaves * BT * kWave;
+    constexpr size_t lds_bytes = stage_bytes > sums_bytes ? stage_bytes : sums_bytes;
+    __shared__ __align__(16) unsigned char lds[lds_bytes > 0 ? lds_bytes : 16];
+
+    AmCtx<BT> amc;
+    amc.st = AM ? reinterpret_cast<AmStage<BT> *>(lds) + range : nullptr;
     amc.part = am_part;
     amc.wid = wid;
     amc.lane = lane;
@@ -751,29 +787,63 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
     amc.n0 = n0;
     amc.nb = nb;
     amc.np = np;
-    amc.p_lo = (int)((long)np * seg / nps);
-    amc.p_hi = (int)((long)np * (seg + 1) / nps);
-    amc.chunk = amc.p_lo;
 
-    cplx an[kBandTile];
+    cplx an[BT];
 #pragma unroll
-    for (int u = 0; u < kBandTile; ++u) {
+    for (int u = 0; u < BT; ++u) {
         an[u] = cmake(0.0, 0.0);
         if (AM && n0 + u < nb) an[u] = cload(aqsn + (size_t)(n0 + u) * ng + gc);
     }
-    cplx acc[kBandTile];
+    cplx acc[BT];
 #pragma unroll
-    for (int u = 0; u < kBandTile; ++u) acc[u] = cmake(0.0, 0.0);
-    if (n0 >= nv && n0 + kBandTile <= nb)
-        bands_fast<NW, AM>(nb, ng, n0, gc, valid ? vcoul[gc] : 0.0, as_global(aqsm),
-                           as_global(ieps), as_global(wt), as_global(wx), as_global(gh),
-                           as_global(xgh), an, amc, acc);
-    else
-        bands_generic<NW, AM>(nb, nv, ng, n0, gc, valid, aqsm, ieps, wt, vcoul, wx, gh, gs, an,
-                              amc, acc);
+    for (int u = 0; u < BT; ++u) acc[u] = cmake(0.0, 0.0);
+    const int step = AM ? kAmCols : per;
+    if (n0 >= nv && n0 + BT <= nb) {
+        const double vc = valid ? vcoul[gc] : 0.0;
+        BandsFast<NW, BT, AM> f;
+        f.start(nb, ng, n0, gc, p_lo < np ? p_lo : np - 1, as_global(ieps), as_global(wt),
+                as_global(wx), ga);
+        for (int at = 0; at < per; at += step) {
+            const int p = p_lo + at < p_hi ? p_lo + at : p_hi;
+            const int end = p + step < p_hi ? p + step : p_hi;
+            amc.first = p;
+            f.columns(p, end, p_hi, nb, ng, n0, gc, vc, as_global(aqsm), as_global(ieps),
+                      as_global(wt), as_global(wx), an, amc, acc);
+            if constexpr (AM) am_flush(amc, end);
+        }
+    } else {
+        for (int at = 0; at < per; at += step) {
+            const int p = p_lo + at < p_hi ? p_lo + at : p_hi;
+            const int end = p + step < p_hi ? p + step : p_hi;
+            amc.first = p;
+            bands_generic<NW, BT, AM>(p, end, nb, nv, ng, n0, gc, valid, aqsm, ieps, wt, vcoul, wx,
+                                      ga, gs, an, amc, acc);
+            if constexpr (AM) am_flush(amc, end);
+        }
+    }
+    if constexpr (PW > 1) {
+        // the ranges' sums into range 0's, in order
+        double2 *const sums = reinterpret_cast<double2 *>(lds);
+        __syncthreads();
+        if (range > 0) {
+#pragma unroll
+            for (int u = 0; u < BT; ++u)
+                sums[(((range - 1) * kBwdWaves + wid) * BT + u) * kWave + lane] =
+                    make_double2(acc[u].re, acc[u].im);
+        }
+        __syncthreads();
+        if (range > 0) return;
+#pragma unroll
+        for (int k = 0; k < PW - 1; ++k)
+#pragma unroll
+            for (int u = 0; u < BT; ++u) {
+                const double2 v = sums[((k * kBwdWaves + wid) * BT + u) * kWave + lane];
+                acc[u] = cadd(acc[u], cmake(v.x, v.y));
+            }
+    }
     if (dst && valid) {
 #pragma unroll
-        for (int u = 0; u < kBandTile; ++u) {
+        for (int u = 0; u < BT; ++u) {
             const int n = n0 + u;
             if (n < nb) dst[(size_t)n * ng + g] = make_double2(acc[u].re, acc[u].im);
         }
@@ -853,6 +923,8 @@ BwdGeometry bwd_geometry(const Dims32 &d)
         const long max_nps = d.np / kMinSegCols > 1 ? d.np / kMinSegCols : 1;
         geo.nps = (int)(nps < max_nps ? nps : max_nps);
         geo.band_tiles = per_seg * geo.nps;
+        geo.short_bands = geo.band_tiles < kBandsShortBelow;
+        if (geo.short_bands) geo.nbt = (d.nb + kShortTile - 1) / kShortTile;
         geo.band_blocks = (long)geo.ngb * geo.nbt * geo.nps;
         geo.am_part_elems = (size_t)geo.ngb * d.nb * d.np;
         geo.an_part_elems = geo.nps > 1 ? (size_t)geo.nps * d.nb * d.ng : 0;
@@ -871,36 +943,37 @@ static hipError_t launch_bwd_nw(const Dims32 &d, const BwdGeometry &geo, const D
                                 char *ws, hipStream_t st)
 {
     auto up = [](size_t e) { return (e * sizeof(double2) + 255) / 256 * 256; };
-    double2 *gh = reinterpret_cast<double2 *>(ws);
-    double2 *xgh = reinterpret_cast<double2 *>(ws + up(geo.gh_elems));
-    double2 *am_part = reinterpret_cast<double2 *>(ws + up(geo.gh_elems) + up(geo.xgh_elems));
-    double2 *an_part = reinterpret_cast<double2 *>(ws + up(geo.gh_elems) + up(geo.xgh_elems) +
-                                                   up(geo.am_part_elems));
-    const long prep = (long)d.nw * d.nb > d.nw ? (long)d.nw * d.nb : d.nw;
-    hipLaunchKernelGGL(bwd_prepare, dim3((unsigned)((prep + 255) / 256)), dim3(256), 0, st,
-                       d.nb, d.nw, in.wx, ga, gh, xgh);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // the first two sections (once the scaled upstream gradient) lie unused:
+    // the workspace keeps its size
+    char *const after = ws + up(geo.gh_elems) + up(geo.xgh_elems);
+    double2 *am_part = reinterpret_cast<double2 *>(after);
+    double2 *an_part = reinterpret_cast<double2 *>(after + up(geo.am_part_elems));
+    hipError_t e;
     if (out.grad_wt || out.grad_ieps) {
         hipLaunchKernelGGL(bwd_pairs<NW>, dim3((unsigned)geo.pair_blocks), dim3(kBwdThreads), 0,
                            st, d.nb, d.nv, d.ng, d.np, geo.pair_blocks, in.aqsm, in.aqsn,
-                           in.ieps, in.wt, in.vcoul, in.wx, gh, xgh, gs, out.grad_wt,
+                           in.ieps, in.wt, in.vcoul, in.wx, ga, gs, out.grad_wt,
                            out.grad_ieps);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (out.grad_an || out.grad_am) {
         double2 *an_dst = !out.grad_an ? nullptr : (geo.nps > 1 ? an_part : out.grad_an);
-        if (out.grad_am)
-            hipLaunchKernelGGL((bwd_bands<NW, true>), dim3((unsigned)geo.band_blocks),
-                               dim3(kBwdThreads), 0, st, d.nb, d.nv, d.ng, d.np, geo.band_blocks,
+        const dim3 grid((unsigned)geo.band_blocks);
+        const dim3 block(kBwdThreads * (geo.short_bands ? kShortRanges : 1));
+        double2 *const am_dst = out.grad_am ? am_part : nullptr;
+        const auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, st, d.nb, d.nv, d.ng, d.np, geo.band_blocks,
                                geo.nbt, geo.ngb, geo.nps, in.aqsm, in.aqsn, in.ieps, in.wt,
-                               in.vcoul, in.wx, gh, xgh, gs, an_dst, am_part);
+                               in.vcoul, in.wx, ga, gs, an_dst, am_dst);
+            return hipGetLastError();
+        };
+        if (geo.short_bands)
+            e = out.grad_am ? launch(bwd_bands<NW, kShortTile, kShortRanges, true>)
+                            : launch(bwd_bands<NW, kShortTile, kShortRanges, false>);
         else
-            hipLaunchKernelGGL((bwd_bands<NW, false>), dim3((unsigned)geo.band_blocks),
-                               dim3(kBwdThreads), 0, st, d.nb, d.nv, d.ng, d.np, geo.band_blocks,
-                               geo.nbt, geo.ngb, geo.nps, in.aqsm, in.aqsn, in.ieps, in.wt,
-                               in.vcoul, in.wx, gh, xgh, gs, an_dst, nullptr);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+            e = out.grad_am ? launch(bwd_bands<NW, kBandTile, 1, true>)
+                            : launch(bwd_bands<NW, kBandTile, 1, false>);
+        if (e != hipSuccess) return e;
         if (out.grad_an && geo.nps > 1) {
             const long nbg = (long)d.nb * d.ng;
             hipLaunchKernelGGL(reduce_an, dim3((unsigned)((nbg + 255) / 256)), dim3(256), 0, st,

@@ -205,15 +205,6 @@ __device__ __forceinline__ void batch_reciprocal(const double (&d)[K], double (&
         one_by_one<K>(d, r);
 }
 
-// How the hot loops apply the branch-A test to a term.  2: the compare
-// itself writes the wave's execution mask (v_cmpx) around the term's
-// accumulation; 1: the same mask through a compiler-generated branch (a
-// compare, then a scalar mask update); in both, masked lanes add nothing
-// and no select is spent.  0: through mask_keep on the reciprocal.
-#ifndef GPP_EXEC_MASK
-#define GPP_EXEC_MASK 2
-#endif
-
 // keep ? v : (a value of magnitude below 2^-1042) with one 32-bit select:
 // only the high word (sign, exponent, top mantissa bits) is cleared, which
 // leaves a denormal made of v's low word.  Added to any accumulator above

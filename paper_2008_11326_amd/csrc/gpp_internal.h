@@ -38,6 +38,7 @@ struct BwdGeometry {
     int nbt = 0;             // band tiles of the bands kernel
     int ngt = 0;             // 64-row g tiles of the bands kernel
     int nps = 1;             // segments of the bands kernel's p range
+    bool short_bands = false;  // bands kernel: the form for short grids
     long band_tiles = 0;     // bands-kernel waves (segments x g tiles x band tiles)
     long band_blocks = 0;
     size_t gh_elems = 0, xgh_elems = 0, am_part_elems = 0;  // complex elements
