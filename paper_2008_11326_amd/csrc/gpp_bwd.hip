@@ -127,95 +127,6 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Exchange term of an occupied band: ssx = e sigma, d ssx/d om = e delta,
-// with d = x - om, s = x + om and D = d s = x^2 - om^2:
-//   A:  sigma = om^2 / D,       delta = 2 om x^2 / D^2
-//   B:  sigma = -om / (2 s),    delta = -x / (2 s^2)
-// evaluated without a divide as in the forward: 1/D = conj(D) r rs and
-// 1/s = conj(s) rs with r = 1/|d|^2, rs = 1/|s|^2, where conj(D) =
-// (fma(Re d, Re s, (Im om)^2), 2 Re om Im om) and om conj(s) =
-// (fma(Re om, Re s, (Im om)^2), Im om x).
-__device__ inline void sx_sigma_delta(double x, double a, double b, double wi2, double wtr,
-                                      double thr, cplx &sigma, cplx &delta)
-{
-    const double dr = x - a, sp = x + a;
-    const double wd = fma(dr, dr, wi2);
-    if (wd > thr) {  // A
-        const double ws = fma(sp, sp, wi2);
-        const double q = rcp_nr2(wd) * rcp_nr2(ws);
-        const double ab2 = 2.0 * a * b;
-        const cplx cd = cmake(fma(dr, sp, wi2), ab2);  // conj(D)
-        const cplx om2 = cmake(fma(a, a, -wi2), ab2);  // om^2
-        sigma = cscale(q, cmul(om2, cd));
-        const cplx cd2 = cmul(cd, cd);
-        delta = cscale(2.0 * x * x * q * q, cmul(cmake(a, b), cd2));
-    } else if (branch_b_holds(wtr, wd)) {  // B
-        const double ws = fma(sp, sp, wi2);
-        const double h = -0.5 * rcp_nr2(ws);
-        sigma = cmake(fma(a, sp, wi2) * h, (b * x) * h);
-        // conj(s)^2 = (sp^2 - b^2, -2 sp b)
-        const double hh = h * rcp_nr2(ws) * x;
-        delta = cmake(fma(sp, sp, -wi2) * hh, -2.0 * sp * b * hh);
-    } else {
-        sigma = delta = cmake(0.0, 0.0);
-    }
-}
-
-// K (and, with WANT_L, L) of BU bands starting at band n for one lane:
-// batch-inverted reciprocals over the BU*NW terms, masked to branch A.
-template <int NW, int BU, bool WANT_L>
-__device__ __forceinline__ void ch_bands_kl(int n, int nb, const double *__restrict__ wx,
-                                            const double2 *__restrict__ ga, double a, double b,
-                                            double wi2, double thr, bool wide, cplx (&K)[BU],
-                                            cplx (&L)[BU])
-{
-    constexpr int Kt = BU * NW;
-    double xs[Kt], dc[Kt], drs[Kt], r[Kt];
-    bool isA[Kt];
-#pragma unroll
-    for (int u = 0; u < BU; ++u)
-#pragma unroll
-        for (int w = 0; w < NW; ++w) xs[u * NW + w] = wx[(size_t)w * nb + n + u];
-#pragma unroll
-    for (int k = 0; k < Kt; ++k) {
-        drs[k] = xs[k] - a;
-        const double wd = fma(drs[k], drs[k], wi2);
-        isA[k] = wd > thr;
-        dc[k] = wd;  // unclamped: see batch_reciprocal
-    }
-    batch_reciprocal<Kt>(dc, r, wide);
-#pragma unroll
-    for (int u = 0; u < BU; ++u) {
-        K[u] = L[u] = cmake(0.0, 0.0);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const int k = u * NW + w;
-            const double re = mask_keep(isA[k], r[k]);
-            const cplx uu = cmake(drs[k] * re, -b * re);  // conj(1/(x - om))
-            const cplx gh = half_of(ga, w);
-            cmac(K[u], gh, uu);
-            if (WANT_L) cmac(L[u], cscale(xs[k], gh), cmul(uu, uu));
-        }
-    }
-}
-
-// KS, LS of one occupied band n for one lane.
-template <int NW>
-__device__ __forceinline__ void sx_band_kl(int n, int nb, const double *__restrict__ wx,
-                                           const double2 *__restrict__ gs, double a, double b,
-                                           double wi2, double wtr, double thr, cplx &KS, cplx &LS)
-{
-    KS = LS = cmake(0.0, 0.0);
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        cplx sigma, delta;
-        sx_sigma_delta(wx[(size_t)w * nb + n], a, b, wi2, wtr, thr, sigma, delta);
-        const cplx g = cload(gs + w);
-        cmac(KS, g, cmake(sigma.re, -sigma.im));
-        cmac(LS, g, cmake(delta.re, -delta.im));
-    }
-}
-
 struct PairState {
     double a, b, wi2, wtr, thr;
     double b2, wi2x2;  // 2 Im om and 2 (Im om)^2
@@ -223,22 +134,93 @@ struct PairState {
     cplx om, e, ve;  // ve = vcoul[g] e (0 for rows beyond ncouls)
 };
 
-__device__ __forceinline__ PairState load_pair(const double2 *wt, const double2 *ieps,
-                                               const double *vcoul, int p, int ng, int gc,
-                                               bool valid)
+// One band of one lane with frequencies x (wave-uniform): its Z = conj(om) K
+// [+ KS] and, with WANT_W, W = L [+ LS]; OCC adds the exchange parts.  Those,
+// ssx = e sigma and d ssx/d om = e delta, with d = x - om, s = x + om and
+// D = d s = x^2 - om^2, are
+//   A:  sigma = om^2 / D,       delta = 2 om x^2 / D^2
+//   B:  sigma = -om / (2 s),    delta = -x / (2 s^2)
+// evaluated without a divide as in the forward: 1/D = conj(D) r rs and
+// 1/s = conj(s) rs with r = 1/|d|^2, rs = 1/|s|^2, where conj(D) =
+// (fma(Re d, Re s, (Im om)^2), 2 Re om Im om) and om conj(s) =
+// (fma(Re om, Re s, (Im om)^2), Im om x); selects pick the branch's value.
+// The reciprocals come from batch inversions up to four frequencies, one by
+// one beyond (register count).
+template <int NW, bool OCC, bool WANT_W>
+__device__ __forceinline__ void band_zw(const double (&x)[NW], const double2 *__restrict__ ga,
+                                        const double2 *__restrict__ gs, const PairState &ps,
+                                        cplx &Z, cplx &W)
+{
+    const double a = ps.a, b = ps.b, wi2 = ps.wi2;
+    double d[NW], r[NW], ws[NW], rs[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const double dr = x[w] - a, sp = x[w] + a;
+        d[w] = fma(dr, dr, wi2);
+        ws[w] = fma(sp, sp, wi2);
+    }
+    if constexpr (NW <= 4) {
+        batch_reciprocal<NW>(d, r, ps.wide);
+        if (OCC) batch_reciprocal<NW>(ws, rs, ps.wide);
+    } else {
+        one_by_one<NW>(d, r);
+        if (OCC) one_by_one<NW>(ws, rs);
+    }
+    cplx K = cmake(0.0, 0.0), L = cmake(0.0, 0.0), KS = K, LS = K;
+    const double ab2 = 2.0 * a * b;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const double dr = x[w] - a, sp = x[w] + a;
+        const bool isA = d[w] > ps.thr;
+        const double rm = isA ? r[w] : 0.0;
+        const cplx uu = cmake(dr * rm, -b * rm);  // conj(1/(x - om))
+        const cplx gh = half_of(ga, w);
+        cmac(K, gh, uu);
+        if (WANT_W) cmac(L, cscale(x[w], gh), cmul(uu, uu));
+        if constexpr (OCC) {
+            const bool isB = branch_b_holds(ps.wtr, d[w]);
+            const double q = rm * rs[w];
+            const cplx cd = cmake(fma(dr, sp, wi2), ab2);  // conj(D)
+            const cplx om2 = cmake(fma(a, a, -wi2), ab2);
+            const cplx sa = cscale(q, cmul(om2, cd));
+            const double h = -0.5 * rs[w];
+            const cplx sb = cmake(fma(a, sp, wi2) * h, (b * x[w]) * h);
+            const cplx sigma = cmake(isA ? sa.re : (isB ? sb.re : 0.0),
+                                     isA ? sa.im : (isB ? sb.im : 0.0));
+            cmac(KS, cload(gs + w), cmake(sigma.re, -sigma.im));
+            if constexpr (WANT_W) {
+                const cplx da = cscale(2.0 * x[w] * x[w] * q * q, cmul(ps.om, cmul(cd, cd)));
+                // conj(s)^2 = (sp^2 - b^2, -2 sp b)
+                const double hh = h * rs[w] * x[w];
+                const cplx db = cmake(fma(sp, sp, -wi2) * hh, -2.0 * sp * b * hh);
+                const cplx delta = cmake(isA ? da.re : (isB ? db.re : 0.0),
+                                         isA ? da.im : (isB ? db.im : 0.0));
+                cmac(LS, cload(gs + w), cmake(delta.re, -delta.im));
+            }
+        }
+    }
+    Z = cmul(cmake(a, -b), K);
+    W = L;
+    if constexpr (OCC) {
+        Z = cadd(Z, KS);
+        W = cadd(W, LS);
+    }
+}
+
+__device__ __forceinline__ PairState make_pair(cplx om, cplx e, double v)
 {
     PairState s;
-    s.om = cload(wt + (size_t)p * ng + gc);
-    s.e = cload(ieps + (size_t)p * ng + gc);
-    s.a = s.om.re;
-    s.b = s.om.im;
+    s.om = om;
+    s.e = e;
+    s.a = om.re;
+    s.b = om.im;
     s.wi2 = s.b * s.b;
     s.b2 = 2.0 * s.b;
     s.wi2x2 = 2.0 * s.wi2;
     s.wtr = fma(s.a, s.a, s.wi2);
     s.thr = branch_a_threshold(s.wtr);
     s.wide = s.wi2 >= kMinUnclampedWi2;
-    s.ve = cscale(valid ? vcoul[gc] : 0.0, s.e);
+    s.ve = cscale(v, e);
     return s;
 }
 
@@ -340,28 +322,28 @@ __device__ __forceinline__ int pairs_bands(int n, int nb, int ng, gptr<double2> 
     }
 }
 
-// Occupied bands [0, nocc) of one lane: K and L (Coulomb hole) and KS and LS
-// (exchange) per band, then Ge += conj(M) Z and Gw += conj(M) W.
+// Occupied bands [0, nocc) of one lane: Ge += conj(M) Z and Gw += conj(M) W.
+// The next band's values load while this one computes.
 template <int NW>
-__device__ __forceinline__ void pairs_occupied(int nocc, int nb, int ng,
-                                               const double2 *__restrict__ aqsn,
-                                               const double2 *__restrict__ am_col,
-                                               const double *__restrict__ wx,
+__device__ __forceinline__ void pairs_occupied(int nocc, int nb, int ng, gptr<double2> aqsn,
+                                               gptr<double2> am_col, gptr<double> wx,
                                                const double2 *__restrict__ ga,
                                                const double2 *__restrict__ gs,
                                                const PairState &ps, uint32_t goff, cplx &Ge,
                                                cplx &Gw)
 {
-    const cplx cw = cmake(ps.om.re, -ps.om.im);  // conj(om)
+    if (nocc <= 0) return;
+    OccupiedBand<NW> cur;
+    cur.load(0, nb, ng, aqsn, goff, am_col, wx);
     for (int n = 0; n < nocc; ++n) {
-        cplx K[1], L[1], KS, LS;
-        ch_bands_kl<NW, 1, true>(n, nb, wx, ga, ps.a, ps.b, ps.wi2, ps.thr, ps.wide, K, L);
-        sx_band_kl<NW>(n, nb, wx, gs, ps.a, ps.b, ps.wi2, ps.wtr, ps.thr, KS, LS);
-        const cplx an = load_row_elem(as_global(aqsn) + (size_t)n * ng, ng, goff);
-        const cplx am = cload(am_col + (size_t)n * ng);
-        const cplx cM = cmul_conj(am, an);  // conj(M) = conj(an) am
-        cmac(Ge, cM, cadd(cmul(cw, K[0]), KS));
-        cmac(Gw, cM, cadd(L[0], LS));
+        OccupiedBand<NW> next;
+        next.load(n + 1 < nocc ? n + 1 : n, nb, ng, aqsn, goff, am_col, wx);
+        cplx Z, W;
+        band_zw<NW, true, true>(cur.x, ga, gs, ps, Z, W);
+        const cplx cM = cmul_conj(cur.am, cur.an);  // conj(M) = conj(an) am
+        cmac(Ge, cM, Z);
+        cmac(Gw, cM, W);
+        cur = next;
     }
 }
 
@@ -387,13 +369,16 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
     const int g = gb * kRowsPerBlock + wid * kWave + lane;
     const bool valid = g < ng;
     const int gc = valid ? g : ng - 1;
-    const PairState ps = load_pair(wt, ieps, vcoul, p, ng, gc, valid);
+    const double v = valid ? vcoul[gc] : 0.0;
+    const cplx om = cload(wt + (size_t)p * ng + gc), e = cload(ieps + (size_t)p * ng + gc);
+    const PairState ps = make_pair(om, e, v);
     const double2 *am_col = aqsm + p;
     const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
 
     cplx Ge = cmake(0.0, 0.0), Gw = cmake(0.0, 0.0);
     const int nocc = nv < nb ? nv : nb;
-    pairs_occupied<NW>(nocc, nb, ng, aqsn, am_col, wx, ga, gs, ps, goff, Ge, Gw);
+    pairs_occupied<NW>(nocc, nb, ng, as_global(aqsn), as_global(am_col), as_global(wx), ga, gs, ps,
+                       goff, Ge, Gw);
     cplx A2[NW], B1[NW], B2[NW], B3[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) A2[w] = B1[w] = B2[w] = B3[w] = cmake(0.0, 0.0);
@@ -419,7 +404,6 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
     Gw = cadd(Gw, SL);
 
     if (valid) {
-        const double v = vcoul[g];
         const size_t idx = (size_t)p * ng + g;
         if (grad_ieps) {
             const cplx r = cscale(v, Ge);
@@ -669,66 +653,65 @@ struct BandsFast {
     }
 };
 
-// Generic form of the columns [p, end): occupied bands (exchange terms) and a
-// ragged last tile.
+// Generic form of a wave's columns: occupied bands (exchange terms) and a
+// ragged last tile, band by band.
 template <int NW, int BT, bool AM>
-__device__ __forceinline__ void bands_generic(int p, int end, int nb, int nv, int ng, int n0,
-                                              int gc, bool valid,
-                                              const double2 *__restrict__ aqsm,
-                                              const double2 *__restrict__ ieps,
-                                              const double2 *__restrict__ wt,
-                                              const double *__restrict__ vcoul,
-                                              const double *__restrict__ wx,
-                                              const double2 *__restrict__ ga,
-                                              const double2 *__restrict__ gs,
-                                              const cplx (&an)[BT], AmCtx<BT> &amc,
-                                              cplx (&acc)[BT])
-{
-    constexpr int G = bands_group(NW, BT);
-    for (; p < end; ++p) {
-        const PairState ps = load_pair(wt, ieps, vcoul, p, ng, gc, valid);
-        const cplx vce = cmake(ps.ve.re, -ps.ve.im);           // vcoul conj(e)
-        const cplx vcw = cmul(vce, cmake(ps.om.re, -ps.om.im));  // vcoul conj(e om)
+struct BandsGeneric {
+    double xs[BT][NW];
+    uint32_t row_off[BT];  // of the bands' aqsmtemp rows; past nb the last row again
+    cplx om_next, e_next;
+
+    __device__ __forceinline__ void start(int nb, int ng, int n0, int gc, int p,
+                                          gptr<double2> ieps, gptr<double2> wt, gptr<double> wx)
+    {
+        om_next = cload(wt + (size_t)p * ng + gc);
+        e_next = cload(ieps + (size_t)p * ng + gc);
 #pragma unroll
-        for (int u0 = 0; u0 < BT; u0 += G) {
-            const int n = n0 + u0;
-            cplx K[G], L[G];
-            const bool full = n + G <= nb && n >= nv;
-            if (full) {
-                ch_bands_kl<NW, G, false>(n, nb, wx, ga, ps.a, ps.b, ps.wi2, ps.thr, ps.wide, K, L);
-            } else {
+        for (int u = 0; u < BT; ++u) {
+            const int n = n0 + u < nb ? n0 + u : nb - 1;
+            row_off[u] = (uint32_t)(n - n0) * (uint32_t)ng * (uint32_t)sizeof(double2);
 #pragma unroll
-                for (int u = 0; u < G; ++u) {
-                    K[u] = cmake(0.0, 0.0);
-                    if (n + u < nb) {
-                        cplx K1[1], L1[1];
-                        ch_bands_kl<NW, 1, false>(n + u, nb, wx, ga, ps.a, ps.b, ps.wi2, ps.thr,
-                                                  ps.wide, K1, L1);
-                        K[u] = K1[0];
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int nn = n + u;
-                cplx vZ = cmake(0.0, 0.0);
-                if (nn < nb) {
-                    // vcoul conj(e) Z = vcoul conj(e om) K [+ vcoul conj(e) KS]
-                    vZ = cmul(vcw, K[u]);
-                    if (nn < nv) {
-                        cplx KS, LS;
-                        sx_band_kl<NW>(nn, nb, wx, gs, ps.a, ps.b, ps.wi2, ps.wtr, ps.thr, KS, LS);
-                        cmac(vZ, vce, KS);
-                    }
-                    const cplx am = cload(aqsm + (size_t)nn * ng + p);
-                    cmac(acc[u0 + u], am, vZ);
-                }
-                if constexpr (AM) am_put(amc, p, u0 + u, an[u0 + u], vZ);
-            }
+            for (int w = 0; w < NW; ++w) xs[u][w] = wx[(size_t)w * nb + n];
         }
-        if constexpr (AM) am_column_done(amc, p, end);
     }
-}
+    // Columns [p, end) of the wave's [.., p_hi).
+    __device__ __forceinline__ void columns(int p, int end, int p_hi, int nb, int nv, int ng,
+                                            int n0, int gc, double vc, gptr<double2> aqsm,
+                                            gptr<double2> ieps, gptr<double2> wt,
+                                            const double2 *__restrict__ ga,
+                                            const double2 *__restrict__ gs,
+                                            const cplx (&an)[BT], AmCtx<BT> &amc,
+                                            cplx (&acc)[BT])
+    {
+        Walker am_at;
+        am_at.start((uint64_t)(aqsm + (size_t)n0 * ng + p));
+        for (; p < end; ++p) {
+            const cplx om = om_next, e = e_next;
+            const int pn = p + 1 < p_hi ? p + 1 : p;
+            om_next = cload(wt + (size_t)pn * ng + gc);
+            e_next = cload(ieps + (size_t)pn * ng + gc);
+            cplx am[BT];
+#pragma unroll
+            for (int u = 0; u < BT; ++u) am[u] = am_at.complex(row_off[u]);
+            am_at.advance(sizeof(double2));
+            const PairState ps = make_pair(om, e, vc);
+            const cplx vce = cmake(ps.ve.re, -ps.ve.im);  // vcoul conj(e)
+#pragma unroll
+            for (int u = 0; u < BT; ++u) {
+                cplx vz = cmake(0.0, 0.0);
+                if (n0 + u < nb) {  // wave-uniform, like the next
+                    cplx Z, W;
+                    if (n0 + u < nv) band_zw<NW, true, false>(xs[u], ga, gs, ps, Z, W);
+                    else band_zw<NW, false, false>(xs[u], ga, gs, ps, Z, W);
+                    vz = cmul(vce, Z);
+                    cmac(acc[u], am[u], vz);
+                }
+                if constexpr (AM) am_put(amc, p, u, an[u], vz);
+            }
+            if constexpr (AM) am_column_done(amc, p, end);
+        }
+    }
+};
 
 // Workgroup = BT bands x 256 rows (four 64-row tiles) x one segment of the G'
 // range, which PW waves per row tile share; band tile fastest (neighbouring
@@ -798,8 +781,8 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
 #pragma unroll
     for (int u = 0; u < BT; ++u) acc[u] = cmake(0.0, 0.0);
     const int step = AM ? kAmCols : per;
+    const double vc = valid ? vcoul[gc] : 0.0;
     if (n0 >= nv && n0 + BT <= nb) {
-        const double vc = valid ? vcoul[gc] : 0.0;
         BandsFast<NW, BT, AM> f;
         f.start(nb, ng, n0, gc, p_lo < np ? p_lo : np - 1, as_global(ieps), as_global(wt),
                 as_global(wx), ga);
@@ -812,12 +795,15 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
             if constexpr (AM) am_flush(amc, end);
         }
     } else {
+        BandsGeneric<NW, BT, AM> f;
+        f.start(nb, ng, n0, gc, p_lo < np ? p_lo : np - 1, as_global(ieps), as_global(wt),
+                as_global(wx));
         for (int at = 0; at < per; at += step) {
             const int p = p_lo + at < p_hi ? p_lo + at : p_hi;
             const int end = p + step < p_hi ? p + step : p_hi;
             amc.first = p;
-            bands_generic<NW, BT, AM>(p, end, nb, nv, ng, n0, gc, valid, aqsm, ieps, wt, vcoul, wx,
-                                      ga, gs, an, amc, acc);
+            f.columns(p, end, p_hi, nb, nv, ng, n0, gc, vc, as_global(aqsm), as_global(ieps),
+                      as_global(wt), ga, gs, an, amc, acc);
             if constexpr (AM) am_flush(amc, end);
         }
     }
