@@ -144,8 +144,9 @@ struct PairState {
 // 1/s = conj(s) rs with r = 1/|d|^2, rs = 1/|s|^2, where conj(D) =
 // (fma(Re d, Re s, (Im om)^2), 2 Re om Im om) and om conj(s) =
 // (fma(Re om, Re s, (Im om)^2), Im om x); selects pick the branch's value.
-// The reciprocals come from batch inversions up to four frequencies, one by
-// one beyond (register count).
+// The reciprocals come one by one: delta takes their squares, and those of a
+// batch inversion (one Newton step, shared error) raised the dwtilde error of
+// a problem with few bands from 3.8e-16 to 1.7e-15.
 template <int NW, bool OCC, bool WANT_W>
 __device__ __forceinline__ void band_zw(const double (&x)[NW], const double2 *__restrict__ ga,
                                         const double2 *__restrict__ gs, const PairState &ps,
@@ -159,13 +160,8 @@ __device__ __forceinline__ void band_zw(const double (&x)[NW], const double2 *__
         d[w] = fma(dr, dr, wi2);
         ws[w] = fma(sp, sp, wi2);
     }
-    if constexpr (NW <= 4) {
-        batch_reciprocal<NW>(d, r, ps.wide);
-        if (OCC) batch_reciprocal<NW>(ws, rs, ps.wide);
-    } else {
-        one_by_one<NW>(d, r);
-        if (OCC) one_by_one<NW>(ws, rs);
-    }
+    one_by_one<NW>(d, r);
+    if (OCC) one_by_one<NW>(ws, rs);
     cplx K = cmake(0.0, 0.0), L = cmake(0.0, 0.0), KS = K, LS = K;
     const double ab2 = 2.0 * a * b;
 #pragma unroll
@@ -506,10 +502,9 @@ __device__ __forceinline__ void am_flush(AmCtx<BT> &a, int end)
 // unoccupied and below nb.  With r_w the masked reciprocal of |x_w - om|^2,
 //   vcoul conj(e) Z = vcoul conj(e om) sum_w gh_w (x_w - om) r_w.
 // Up to four frequencies (FACTOR) it is the sum of (x_w c1_w - c2_w) r_w with
-// the constants c1_w = gh_w vcoul conj(e om) and c2_w = gh_w vcoul conj(e)
-// |om|^2 of a pair: two FMAs per term for the factor, two for the sum, and
+// the constants c1_w = gh_w vcoul conj(e om) and c2_w = om c1_w of a pair: two FMAs per term for the factor, two for the sum, and
 // per column eight products per frequency.  With more, whose constants would
-// spill, c1 S - c2 R with S = sum_w gh_w (x_w r_w) and R = sum_w gh_w r_w.
+// spill, vcoul conj(e om) (S - om R) with S = sum_w gh_w (x_w r_w) and R = sum_w gh_w r_w.
 // Either way the loop needs x and gh only, in scalar registers: x gh itself,
 // 12 complex values per column at nfreq 3 from the scalar cache, took 15
 // scalar loads with their waits per column against 4 here.  256 bands x 8192
@@ -573,13 +568,14 @@ struct BandsFast {
             const uint64_t narrow = __builtin_amdgcn_ballot_w64(!(wi2 >= kMinUnclampedWi2));
             const cplx vce = cmake(vc * e.re, -(vc * e.im));  // vcoul conj(e)
             const cplx vcw = cmul(vce, cmake(a, -b));         // vcoul conj(e om)
-            const cplx vct = cscale(wtr, vce);
             cplx c1[FACTOR ? NW : 1], c2[FACTOR ? NW : 1];
             if constexpr (FACTOR) {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
+                    // c2 from the rounded c1, so that x c1 - c2 cancels
+                    // against om c1 itself
                     c1[w] = cmul(gh[w], vcw);
-                    c2[w] = cmul(gh[w], vct);
+                    c2[w] = cmul(om, c1[w]);
                 }
             }
 #pragma unroll
@@ -638,9 +634,9 @@ struct BandsFast {
                                   [gi] "s"(gh[w].im)
                                 : "vcc");
                         }
-                        const cplx t = cmul(vct, R);
-                        vz = cmul(vcw, S);
-                        vz = cmake(vz.re - t.re, vz.im - t.im);
+                        // S - om R
+                        vz = cmul(vcw, cmake(fma(om.im, R.im, fma(-om.re, R.re, S.re)),
+                                             fma(-om.im, R.re, fma(-om.re, R.im, S.im))));
                     }
                     cmac(acc[u0 + u], am[u0 + u], vz);
                     if constexpr (AM) am_put(amc, p, u0 + u, an[u0 + u], vz);
