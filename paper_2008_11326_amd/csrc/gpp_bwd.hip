@@ -329,14 +329,15 @@ __device__ __forceinline__ void pairs_occupied(int nocc, int nb, int ng, gptr<do
                                                cplx &Gw)
 {
     if (nocc <= 0) return;
-    OccupiedBand<NW> cur;
-    cur.load(0, nb, ng, aqsn, goff, am_col, wx);
+    const int pc[1] = {0};
+    OccupiedBand<NW, 1> cur;
+    cur.load(0, nb, ng, aqsn, goff, am_col, pc, wx);
     for (int n = 0; n < nocc; ++n) {
-        OccupiedBand<NW> next;
-        next.load(n + 1 < nocc ? n + 1 : n, nb, ng, aqsn, goff, am_col, wx);
+        OccupiedBand<NW, 1> next;
+        next.load(n + 1 < nocc ? n + 1 : n, nb, ng, aqsn, goff, am_col, pc, wx);
         cplx Z, W;
         band_zw<NW, true, true>(cur.x, ga, gs, ps, Z, W);
-        const cplx cM = cmul_conj(cur.am, cur.an);  // conj(M) = conj(an) am
+        const cplx cM = cmul_conj(cur.am[0], cur.an);  // conj(M) = conj(an) am
         cmac(Ge, cM, Z);
         cmac(Gw, cM, W);
         cur = next;

@@ -78,7 +78,9 @@ fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_ban
           const double *__restrict__ vcoul, const double *__restrict__ wx,
           double *__restrict__ partials)
 {
+    constexpr int kKeep = WAVES > kFwdWaves ? 3 * C : 0;  // split form: see RowSink
     __shared__ double red[WAVES][4 * NW];
+    __shared__ double kept[WAVES][kKeep > 0 ? kKeep * kWave : 1];
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const long wave = (long)xcd_remap(blockIdx.x, gridDim.x) * WAVES + wid;
@@ -100,7 +102,7 @@ fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_ban
             n_lo = __builtin_amdgcn_readfirstlane(split_at<BU>(k, shift, lo, occ, hi));
             n_hi = __builtin_amdgcn_readfirstlane(split_at<BU>(k + 1, shift, lo, occ, hi));
         }
-        RowSink<NW> sink{red[wid], lane};
+        RowSink<NW, kKeep> sink{red[wid], lane, kept[wid]};
         if (n_lo < n_hi)
             fwd_tile_body<NW, BU, C>(nb, nv, n_lo, n_hi, ng, np, C * pt, gt, lane, as_global(aqsm),
                                      as_global(aqsn), as_global(ieps), as_global(wt),

@@ -120,8 +120,8 @@ struct BandGroup {
     }
 };
 
-// Coulomb-hole sums of NC columns over the whole groups of BU unoccupied
-// bands in [n, n_hi), the first of them loaded in `cur`; returns the first
+// Coulomb-hole sums of NC columns over the whole groups of BU bands in
+// [n, n_hi), the first of them loaded in `cur`; returns the first
 // band left over.  The BU*NW*NC denominators of a group share one batch
 // inversion; they go in unclamped: every one is at least (Im om)^2, and where
 // a lane has a column with (Im om)^2 below kMinUnclampedWi2 (the wave mask
@@ -220,119 +220,104 @@ __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<do
     }
 }
 
-// Frequencies W0 .. W0+G-1 of one occupied band (see occupied_bands).
-template <int NW, int W0, int G>
-__device__ __forceinline__ void occupied_freqs(const double (&x)[NW], double a, double b,
-                                               double wi2, double wtr, double thr, bool wide,
-                                               cplx om2, cplx qm, cplx (&P1)[NW],
-                                               cplx (&P2)[NW], cplx (&SX)[NW])
-{
-    double xs[G], wd[G], ws[G], r[G], rs[G];
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        xs[k] = x[W0 + k];
-        const double dr = xs[k] - a, sp = xs[k] + a;
-        wd[k] = fma(dr, dr, wi2);  // |x - om|^2, the branch's wdiffr
-        ws[k] = fma(sp, sp, wi2);  // |x + om|^2
-    }
-    if constexpr (G > 1) {
-        batch_reciprocal<G>(wd, r, wide);
-        batch_reciprocal<G>(ws, rs, wide);
-    } else {
-        r[0] = rcp_nr2(wd[0]);
-        rs[0] = rcp_nr2(ws[0]);
-    }
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        const int w = W0 + k;
-        const double dr = xs[k] - a, sp = xs[k] + a;
-        const bool isA = wd[k] > thr;
-        const double rc = isA ? r[k] : 0.0;
-        const double rx = rc * xs[k];
-        P1[w].re = fma(rx, qm.re, P1[w].re);
-        P1[w].im = fma(rx, qm.im, P1[w].im);
-        P2[w].re = fma(rc, qm.re, P2[w].re);
-        P2[w].im = fma(rc, qm.im, P2[w].im);
-        // both branches' values carry rs: A = r om^2 conj(d s), B = -om conj(s) / 2
-        const cplx na = cscale(r[k], cmul(om2, cmake(fma(dr, sp, wi2), om2.im)));
-        const cplx nb2 = cmake(-0.5 * fma(a, sp, wi2), -0.5 * (b * xs[k]));
-        const bool isB = branch_b_holds(wtr, wd[k]);
-        cplx t;
-        t.re = rs[k] * (isA ? na.re : (isB ? nb2.re : 0.0));
-        t.im = rs[k] * (isA ? na.im : (isB ? nb2.im : 0.0));
-        cmac(SX[w], qm, t);
-    }
-}
-
-// Frequencies per batch-inverted group of an occupied band: all three at
-// up to three frequencies; one at a time beyond, where the groups'
-// reciprocals would raise the kernel's register count above the hot loop's.
-#ifndef GPP_OCC_GROUP
-#define GPP_OCC_GROUP 0
-#endif
-constexpr int occ_group(int nw) { return GPP_OCC_GROUP ? GPP_OCC_GROUP : (nw <= 3 ? nw : 1); }
-
-template <int NW, int W0>
-__device__ __forceinline__ void occupied_groups(const double (&x)[NW], double a, double b,
-                                                double wi2, double wtr, double thr, bool wide,
-                                                cplx om2, cplx qm, cplx (&P1)[NW],
-                                                cplx (&P2)[NW], cplx (&SX)[NW])
-{
-    constexpr int G = NW - W0 < occ_group(NW) ? NW - W0 : occ_group(NW);
-    occupied_freqs<NW, W0, G>(x, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
-    if constexpr (W0 + G < NW)
-        occupied_groups<NW, W0 + G>(x, a, b, wi2, wtr, thr, wide, om2, qm, P1, P2, SX);
-}
-
-// One occupied band's values for one column.
-template <int NW>
+// One occupied band's values for NC columns.
+template <int NW, int NC>
 struct OccupiedBand {
-    cplx an, am;
+    cplx an, am[NC];
     double x[NW];
     __device__ __forceinline__ void load(int n, int nb, int ng, gptr<double2> aqsn, uint32_t goff,
-                                         gptr<double2> am_col, gptr<double> wx) {
+                                         gptr<double2> aqsm, const int (&pc)[NC],
+                                         gptr<double> wx) {
         an = load_row_elem(aqsn + (size_t)n * ng, ng, goff);
-        am = cload(am_col + (size_t)n * ng);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) am[c] = cload(aqsm + pc[c] + (size_t)n * ng);
 #pragma unroll
         for (int w = 0; w < NW; ++w) x[w] = wx[(size_t)w * nb + n];
     }
 };
 
-// Occupied bands n0 <= n < n1 (all below nvband) of one lane and one column,
-// band n0 loaded in `cur`: Coulomb-hole terms into P1/P2 and
-// screened-exchange terms (ssx / e) into SX.  With d = x - om and s = x + om,
-// the exchange term is
+// Screened exchange of the occupied bands n0 <= n < n1 (all below nvband) of
+// one lane and NC columns: sums of ssx / (e om) in SX.  With d = x - om and
+// s = x + om, the exchange term is
 //   A:  om^2 / (d s) = om^2 conj(d s) r rs,     r = 1/|d|^2, rs = 1/|s|^2
 //   B:  -om / (2 s)  = -om conj(s) rs / 2
-// where d s = x^2 - om^2 has real part fma(Re d, Re s, (Im om)^2) (both
-// factors exact to rounding even where x is near -Re om) and imaginary
-// part -2 Re om Im om, and om conj(s) = (fma(Re om, Re s, (Im om)^2),
-// Im om x).  The band's reciprocals of |d|^2 and of |s|^2 come from two
-// batch inversions per group of frequencies (both are at least
-// (Im om)^2, like the hot loop's denominators); the branch picks each
-// term's value by selects, so a value computed for another branch never
-// reaches the sums.  The next band (after the last, the next column's first)
-// loads while this one computes: with few bands per wave each exposed load
-// would be a visible part of its time.  (Loading the first group and the first
-// occupied band at the tile's start as well cost more registers than it won:
-// 61 bands x 777 rows x 38 columns at nfreq 2 ran 18.5 instead of 15.7 us.)
-template <int NW>
-__device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng, gptr<double2> aqsn,
-                                               uint32_t goff, gptr<double2> am_col,
-                                               gptr<double2> am_next, gptr<double> wx, cplx om,
-                                               double wi2, double thr, OccupiedBand<NW> &cur,
-                                               cplx (&P1)[NW], cplx (&P2)[NW], cplx (&SX)[NW])
+// where conj(d s) = (u, 2 Re om Im om) with u = fma(Re d, Re s, (Im om)^2)
+// (both factors exact to rounding even where x is near -Re om), so om
+// conj(d s) is linear in u.  One batch inversion per band gives the r rs of
+// all columns and frequencies, 1/(|d|^2 |s|^2); rs is that times |d|^2.  (Both
+// are at least (Im om)^2 >= 2^-60 where the batch is used, so a product of up
+// to 8 pairs stays normal; the other lanes' wave inverts each by itself,
+// which keeps rs finite on an exact pole.)  Selects pick the branch, so a
+// value computed for another branch never reaches the sums.
+// The Coulomb-hole terms of these bands run in the hot loop like all others,
+// and this runs after it, when the hole's sums have left the registers.
+// Before it, 32 x 512 x 64 with two occupied bands took 11.6 us (now 10.3).
+// Both done here, column by column, with an inversion each for |d|^2 and
+// |s|^2 and the accumulators of the hot loop alive, 64 occupied bands of 128
+// at 4096 rows x 204 columns, nfreq 3, took 463 us in place of 456.
+template <int NW, int NC>
+__device__ __forceinline__ void exchange_bands(int n0, int n1, int nb, int ng, gptr<double2> aqsn,
+                                               uint32_t goff, gptr<double2> aqsm,
+                                               const int (&pc)[NC], gptr<double> wx,
+                                               const cplx (&om)[NC], const double (&wi2)[NC],
+                                               const double (&thr)[NC], uint64_t narrow,
+                                               cplx (&SX)[NC][NW])
 {
-    const double a = om.re, b = om.im;
-    const double wtr = fma(a, a, wi2);
-    const cplx om2 = cmake(fma(a, a, -wi2), 2.0 * a * b);  // om^2
-    const bool wide = wi2 >= kMinUnclampedWi2;
+    constexpr int K = NC * NW;
+    static_assert(K <= 8, "the 2^-60 lane bound keeps products of 8 pairs normal");
+    OccupiedBand<NW, NC> cur;
+    cur.load(n0, nb, ng, aqsn, goff, aqsm, pc, wx);
     for (int n = n0; n < n1; ++n) {
-        const bool more = n + 1 < n1;
-        OccupiedBand<NW> next;
-        next.load(more ? n + 1 : n0, nb, ng, aqsn, goff, more ? am_col : am_next, wx);
-        occupied_groups<NW, 0>(cur.x, a, b, wi2, wtr, thr, wide, om2, cmul_conj(cur.an, cur.am),
-                               P1, P2, SX);
+        OccupiedBand<NW, NC> next;  // loads while this band computes
+        next.load(n + 1 < n1 ? n + 1 : n, nb, ng, aqsn, goff, aqsm, pc, wx);
+        double d[K], q[K], rs[K];
+        {
+            double pr[K], ws[K], c[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const double x = cur.x[k % NW], a = om[k / NW].re;
+                const double dr = x - a, sp = x + a;
+                d[k] = fma(dr, dr, wi2[k / NW]);  // |x - om|^2, the branch's wdiffr
+                ws[k] = fma(sp, sp, wi2[k / NW]);  // |x + om|^2
+                pr[k] = d[k] * ws[k];
+            }
+            const double all = batch_prefix<K>(pr, c);
+            batch_back<K>(pr, c, all, q);
+            // one Newton step each takes the roundings of the batch's chain
+            // back out: asxtemp is off by 3.6e-16 of its value at 2048 rows x
+            // 102 columns, nfreq 5, without it by 4.5e-16 (time there 44.4
+            // and 44.6 us)
+#pragma unroll
+            for (int k = 0; k < K; ++k) q[k] = fma(fma(-pr[k], q[k], 1.0), q[k], q[k]);
+#pragma unroll
+            for (int k = 0; k < K; ++k) rs[k] = q[k] * d[k];
+            if (__builtin_expect(batch_misses(all, narrow) != 0, 0)) {
+                one_by_one<K>(d, q);
+                one_by_one<K>(ws, rs);
+#pragma unroll
+                for (int k = 0; k < K; ++k) q[k] *= rs[k];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const cplx qm = qm_of(cur.an, cur.am[c]);
+            const double a = om[c].re, b = om[c].im;
+            const double wtr = fma(a, a, wi2[c]);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int k = c * NW + w;
+                const double x = cur.x[w];
+                const double dr = x - a, sp = x + a;
+                const double u = fma(dr, sp, wi2[c]);
+                const bool isA = d[k] > thr[c];
+                const bool isB = branch_b_holds(wtr, d[k]);
+                // om conj(d s) = (a u - 2 a b^2, b u + 2 a^2 b); conj(s) = (sp, -b)
+                const double vr = isA ? a * fma(-2.0, wi2[c], u) : sp;
+                const double vi = isA ? b * fma(2.0 * a, a, u) : -b;
+                const double f = isA ? q[k] : (isB ? -0.5 * rs[k] : 0.0);
+                cmac(SX[c][w], qm, cmake(f * vr, f * vi));
+            }
+        }
         cur = next;
     }
 }
@@ -342,11 +327,19 @@ __device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng, g
 // called or not, at most once.
 //
 // A row of 4 NW wave totals in LDS, achtemp re, im, asxtemp re, im per
-// frequency, so that no total stays in registers over the band loop.
-template <int NW>
+// frequency, so that no total stays in registers over the band loop.  With
+// KEEP values of the lane that the tile needs only at its end wait in LDS as
+// well (`kept`, KEEP x 64 doubles): under the 128-VGPR cap of the 16-wave
+// workgroups the compiler would spill them to memory, whose way back is a
+// visible part of a short tile's time.
+template <int NW, int KEEP = 0>
 struct RowSink {
+    static constexpr int kKeep = KEEP;
     double *row;
     int lane;
+    double *kept;
+    __device__ __forceinline__ void keep(int i, double v) const { kept[i * kWave + lane] = v; }
+    __device__ __forceinline__ double fetch(int i) const { return kept[i * kWave + lane]; }
     __device__ __forceinline__ void hole(const double (&v)[2 * NW]) const {
         wave_totals<2 * NW>(v, lane, [&](int i, double t) { row[i + (i & ~1)] = t; });
     }
@@ -357,6 +350,7 @@ struct RowSink {
 // Running sums of a persistent wave, in scalar registers.
 template <int NW>
 struct RunningSink {
+    static constexpr int kKeep = 0;
     cplx ach[NW], asx[NW];
     __device__ __forceinline__ void clear() {
 #pragma unroll
@@ -394,10 +388,7 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     int pc[NC];
     cplx om[NC], ev[NC];
     double a[NC], wi2[NC], thr[NC];
-    cplx P1[NC][NW], P2[NC][NW];
     const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
-    const int occ_hi = nv < n_hi ? nv : n_hi;
-    int n = nv > n_lo ? nv : n_lo;
     // every column's loads before the first value is used, also e, which the
     // sums need only at the end: one wait for all of them
     const double v = valid ? vcoul[gc] : 0.0;
@@ -415,42 +406,29 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
         wi2[c] = om[c].im * om[c].im;
         thr[c] = branch_a_threshold(fma(a[c], a[c], wi2[c]));
         wide_all = wide_all && wi2[c] >= kMinUnclampedWi2;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
     }
+    const uint64_t narrow = __builtin_amdgcn_ballot_w64(!wide_all);
 
-    // occupied bands; their exchange sums leave for the sink before the hot
-    // loop
-    if (occ_hi > n_lo) {
-        OccupiedBand<NW> occ;
-        occ.load(n_lo, nb, ng, aqsn, goff, aqsm + pc[0], wx);
-        double v2[2 * NW];
-#pragma unroll
-        for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
+    if constexpr (Sink::kKeep > 0) {
+        static_assert(Sink::kKeep == 3 * NC, "three values per column");
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            cplx SX[NW];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) SX[w] = cmake(0.0, 0.0);
-            occupied_bands<NW>(n_lo, occ_hi, nb, ng, aqsn, goff, aqsm + pc[c],
-                               aqsm + pc[c + 1 < NC ? c + 1 : c], wx, om[c], wi2[c], thr[c], occ,
-                               P1[c], P2[c], SX);
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const cplx t = cmul(ev[c], SX[w]);
-                v2[2 * w] += t.re;
-                v2[2 * w + 1] += t.im;
-            }
+            sink.keep(3 * c, ev[c].re);
+            sink.keep(3 * c + 1, ev[c].im);
+            sink.keep(3 * c + 2, om[c].im);
         }
-        sink.exchange(v2);
     }
 
-    // unoccupied bands: CH only, whole groups, then band by band
-    const uint64_t narrow = __builtin_amdgcn_ballot_w64(!wide_all);
+    // Coulomb hole of all bands, whole groups, then band by band
+    cplx P1[NC][NW], P2[NC][NW];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
     BandGroup<NW, BU> first;
-    first.load_first(n, nb, ng, aqsn, goff, wx);
-    n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow, first,
-                             P1, P2);
+    first.load_first(n_lo, nb, ng, aqsn, goff, wx);
+    const int n = ch_bands<NW, BU, NC>(n_lo, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr,
+                                       narrow, first, P1, P2);
     if constexpr (BU > 1) {
         if (n < n_hi) {
             BandGroup<NW, 1> rest;
@@ -465,6 +443,10 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
     for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
+        if constexpr (Sink::kKeep > 0) {
+            ev[c] = cmake(sink.fetch(3 * c), sink.fetch(3 * c + 1));
+            om[c] = cmake(a[c], sink.fetch(3 * c + 2));
+        }
         const double wtr = fma(a[c], a[c], wi2[c]);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
@@ -478,6 +460,32 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
         }
     }
     sink.hole(v2);
+
+    // occupied bands: their screened exchange, after the hole so that neither
+    // holds the other's sums in registers
+    const int occ_hi = nv < n_hi ? nv : n_hi;
+    if (occ_hi > n_lo) {
+        cplx SX[NC][NW];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) SX[c][w] = cmake(0.0, 0.0);
+        exchange_bands<NW, NC>(n_lo, occ_hi, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr, narrow,
+                               SX);
+#pragma unroll
+        for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const cplx evom = cmul(ev[c], om[c]);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const cplx t = cmul(evom, SX[c][w]);
+                v2[2 * w] += t.re;
+                v2[2 * w + 1] += t.im;
+            }
+        }
+        sink.exchange(v2);
+    }
 }
 
 }  // namespace gpp
