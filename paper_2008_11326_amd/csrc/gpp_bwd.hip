@@ -85,7 +85,8 @@ constexpr int kBandTile = GPP_BWD_BAND_TILE;       // bands per bands-kernel wor
 #ifndef GPP_BWD_BANDS_ROUNDS
 #define GPP_BWD_BANDS_ROUNDS 16
 #endif
-constexpr long kBandsWaveSlots = 256L * 4 * GPP_BWD_BANDS_WAVES;
+constexpr long kBandsCUs = 256;
+constexpr long kBandsWaveSlots = kBandsCUs * 4 * GPP_BWD_BANDS_WAVES;
 constexpr int kBandsRounds = GPP_BWD_BANDS_ROUNDS;
 constexpr int kMinSegCols = 64;
 // Bands per batch-inverted group of the bands kernel: the largest divisor
@@ -98,13 +99,29 @@ constexpr int bands_group(int nw, int bt)
 }
 // Short grids of the bands kernel (fewer than kBandsShortBelow waves of the
 // long form) take kShortTile bands per workgroup and kShortRanges waves per
-// row tile, each on its own part of the column segment.
+// row tile, each on its own part of the column segment; or one band per
+// workgroup where that still makes at most one workgroup per compute unit
+// (whole adjoint of 32 bands x 512 rows x 64 columns, nfreq 3: 32.1 -> 24.4 us
+// without occupied bands, 43 -> 40.9 with two).
+constexpr int kTinyTile = 1;
 constexpr int kShortTile = 2;
 constexpr int kShortRanges = 4;
 #ifndef GPP_BWD_SHORT_BELOW
 #define GPP_BWD_SHORT_BELOW 8192
 #endif
 constexpr long kBandsShortBelow = GPP_BWD_SHORT_BELOW;
+// An occupied band costs about three others (its exchange terms, and single
+// reciprocals), so a tile of them outlasts the rest: they take a tile each
+// where there are at most kSingleOccupied, or the short form runs at most
+// kSingleBlocks workgroups.  More of them fill the GPU by themselves, and
+// share a pair's constants better in whole tiles.  Whole adjoint, rows x
+// bands x columns (occupied, nfreq), shared and single tiles: 512 x 32 x 64
+// (2, 3) 63.7 and 43.0 us, 1024 x 64 x 102 (32, 5) 202 and 151, 2048 x 64 x 102
+// (2, 3) 121.8 and 102.4, 8192 x 256 x 409 (4, 5) 5300 and 5120, 6000 x 200 x
+// 300 (12, 8) 4110 and 3770; but 3001 x 101 x 150 (20, 5) 489 and 500, 8192 x
+// 256 x 409 (40, 3) 4720 and 4850.
+constexpr int kSingleOccupied = 12;
+constexpr long kSingleBlocks = 1024;
 // daqsmtemp sums of the bands kernel: the slab holds the terms of 8 / BT G'
 // columns (BT rows each); every kAmCols columns the row tiles' sums are added
 // and written.
@@ -250,18 +267,18 @@ __device__ __forceinline__ void pairs_term(double d, double thr, double r, doubl
 }
 
 // The band sums of one lane over the whole groups of G unoccupied bands in
-// [n, nb): one batch inversion over a group's G*NW denominators, then
+// [n, end): one batch inversion over a group's G*NW denominators, then
 // pairs_term per term; returns the first band left over.  Loads run ahead
 // and addresses run along as in the forward's loop (ch_bands).
 template <int NW, int G>
-__device__ __forceinline__ int pairs_bands(int n, int nb, int ng, gptr<double2> aqsn,
+__device__ __forceinline__ int pairs_bands(int n, int end, int nb, int ng, gptr<double2> aqsn,
                                            uint32_t goff, gptr<double2> am_col, gptr<double> wx,
                                            const PairState &ps, cplx (&A2)[NW], cplx (&B1)[NW],
                                            cplx (&B2)[NW], cplx (&B3)[NW])
 {
     constexpr int Kt = G * NW;
     static_assert(Kt <= 12, "a group holds at most 12 denominators");
-    int left = (nb - n) / G;
+    int left = (end - n) / G;
     if (left <= 0) return n;
     const uint64_t narrow = __builtin_amdgcn_ballot_w64(!ps.wide);
     const uint32_t row_bytes = (uint32_t)ng * (uint32_t)sizeof(double2);
@@ -318,23 +335,23 @@ __device__ __forceinline__ int pairs_bands(int n, int nb, int ng, gptr<double2> 
     }
 }
 
-// Occupied bands [0, nocc) of one lane: Ge += conj(M) Z and Gw += conj(M) W.
+// Occupied bands [n, end) of one lane: Ge += conj(M) Z and Gw += conj(M) W.
 // The next band's values load while this one computes.
 template <int NW>
-__device__ __forceinline__ void pairs_occupied(int nocc, int nb, int ng, gptr<double2> aqsn,
+__device__ __forceinline__ void pairs_occupied(int n, int end, int nb, int ng, gptr<double2> aqsn,
                                                gptr<double2> am_col, gptr<double> wx,
                                                const double2 *__restrict__ ga,
                                                const double2 *__restrict__ gs,
                                                const PairState &ps, uint32_t goff, cplx &Ge,
                                                cplx &Gw)
 {
-    if (nocc <= 0) return;
+    if (n >= end) return;
     const int pc[1] = {0};
     OccupiedBand<NW, 1> cur;
-    cur.load(0, nb, ng, aqsn, goff, am_col, pc, wx);
-    for (int n = 0; n < nocc; ++n) {
+    cur.load(n, nb, ng, aqsn, goff, am_col, pc, wx);
+    for (; n < end; ++n) {
         OccupiedBand<NW, 1> next;
-        next.load(n + 1 < nocc ? n + 1 : n, nb, ng, aqsn, goff, am_col, pc, wx);
+        next.load(n + 1 < end ? n + 1 : n, nb, ng, aqsn, goff, am_col, pc, wx);
         cplx Z, W;
         band_zw<NW, true, true>(cur.x, ga, gs, ps, Z, W);
         const cplx cM = cmul_conj(cur.am[0], cur.an);  // conj(M) = conj(an) am
@@ -346,8 +363,11 @@ __device__ __forceinline__ void pairs_occupied(int nocc, int nb, int ng, gptr<do
 
 // ---- pairs kernel: dwtilde and dI_eps -------------------------------------
 // Workgroup = 256 rows (one 64-row tile per wave) x one G' column p, p
-// fastest, so concurrently resident workgroups share one row block.
-template <int NW>
+// fastest, so concurrently resident workgroups share one row block.  With
+// SHARE, for grids that leave SIMDs without a wave, a workgroup's four waves
+// share one 64-row tile's bands instead and the first of them adds their
+// gradients.
+template <int NW, bool SHARE>
 __global__ void __launch_bounds__(kBwdThreads)
 __attribute__((amdgpu_waves_per_eu(pairs_waves(NW))))
 bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restrict__ aqsm,
@@ -357,13 +377,16 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
           const double2 *__restrict__ gs, double2 *__restrict__ grad_wt,
           double2 *__restrict__ grad_ieps)
 {
+    constexpr int S = SHARE ? kBwdWaves : 1;  // waves per tile
+    constexpr int G = pairs_group(NW);
+    __shared__ double2 part[SHARE ? S - 1 : 1][2][SHARE ? kWave : 1];
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const long blk = xcd_remap(blockIdx.x, gridDim.x);
-    if (blk >= nblocks) return;  // no barriers in this kernel
+    if (blk >= nblocks) return;  // the whole workgroup leaves together
     const int gb = (int)(blk / np);
     const int p = (int)(blk - (long)gb * np);
-    const int g = gb * kRowsPerBlock + wid * kWave + lane;
+    const int g = (SHARE ? gb : gb * kBwdWaves + wid) * kWave + lane;
     const bool valid = g < ng;
     const int gc = valid ? g : ng - 1;
     const double v = valid ? vcoul[gc] : 0.0;
@@ -372,19 +395,24 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
     const double2 *am_col = aqsm + p;
     const uint32_t goff = (uint32_t)gc * (uint32_t)sizeof(double2);
 
+    // the wave's bands: its shares of the occupied ones and of the groups
+    const int nocc = nv < nb ? nv : nb, k = SHARE ? wid : 0;
+    const int groups = (nb - nocc + G - 1) / G;
+    const int last = nocc + groups * (k + 1) / S * G;
+    const int end = last < nb ? last : nb;
+
     cplx Ge = cmake(0.0, 0.0), Gw = cmake(0.0, 0.0);
-    const int nocc = nv < nb ? nv : nb;
-    pairs_occupied<NW>(nocc, nb, ng, as_global(aqsn), as_global(am_col), as_global(wx), ga, gs, ps,
-                       goff, Ge, Gw);
+    pairs_occupied<NW>(nocc * k / S, nocc * (k + 1) / S, nb, ng, as_global(aqsn),
+                       as_global(am_col), as_global(wx), ga, gs, ps, goff, Ge, Gw);
     cplx A2[NW], B1[NW], B2[NW], B3[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) A2[w] = B1[w] = B2[w] = B3[w] = cmake(0.0, 0.0);
-    int n = nocc;
-    n = pairs_bands<NW, pairs_group(NW)>(n, nb, ng, as_global(aqsn), goff, as_global(am_col),
-                                         as_global(wx), ps, A2, B1, B2, B3);
-    if constexpr (pairs_group(NW) > 1)
-        pairs_bands<NW, 1>(n, nb, ng, as_global(aqsn), goff, as_global(am_col), as_global(wx), ps,
-                           A2, B1, B2, B3);
+    int n = nocc + groups * k / S * G;
+    n = pairs_bands<NW, G>(n, end, nb, ng, as_global(aqsn), goff, as_global(am_col),
+                           as_global(wx), ps, A2, B1, B2, B3);
+    if constexpr (G > 1)
+        pairs_bands<NW, 1>(n, end, nb, ng, as_global(aqsn), goff, as_global(am_col),
+                           as_global(wx), ps, A2, B1, B2, B3);
     // sum_n conj(M) K and sum_n conj(M) L from the band sums
     cplx SK = cmake(0.0, 0.0), SL = cmake(0.0, 0.0);
 #pragma unroll
@@ -400,6 +428,20 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
     cmac(Ge, cmake(ps.om.re, -ps.om.im), SK);
     Gw = cadd(Gw, SL);
 
+    if constexpr (SHARE) {
+        if (wid > 0) {
+            part[wid - 1][0][lane] = make_double2(Ge.re, Ge.im);
+            part[wid - 1][1][lane] = make_double2(Gw.re, Gw.im);
+        }
+        __syncthreads();
+        if (wid > 0) return;
+#pragma unroll
+        for (int i = 0; i < S - 1; ++i) {
+            const double2 pe = part[i][0][lane], pw = part[i][1][lane];
+            Ge = cadd(Ge, cmake(pe.x, pe.y));
+            Gw = cadd(Gw, cmake(pw.x, pw.y));
+        }
+    }
     if (valid) {
         const size_t idx = (size_t)p * ng + g;
         if (grad_ieps) {
@@ -430,7 +472,7 @@ template <int BT>
 struct AmCtx {
     AmStage<BT> *st;
     double2 *part;  // am_part: [256-row block][nb][np]
-    int wid, lane, gblk, n0, nb, np, first;
+    int wid, lane, gblk, n0, n_end, nb, np, first;
 };
 
 // This lane's daqsmtemp term of band u at column p: an conj(vcoul conj(e) Z).
@@ -493,7 +535,7 @@ __device__ __forceinline__ void am_flush(AmCtx<BT> &a, int end)
             s += comp ? v.y : v.x;
         }
         const int col = a.first + j / BT, n = a.n0 + j % BT;
-        if (n < a.nb)
+        if (n < a.n_end)
             reinterpret_cast<double *>(a.part + ((size_t)a.gblk * a.nb + n) * a.np + col)[comp] = s;
     }
     __syncthreads();
@@ -517,7 +559,7 @@ template <int NW, int BT, bool AM>
 struct BandsFast {
     static constexpr int G = bands_group(NW, BT);
     static constexpr int Kt = G * NW;
-    static constexpr bool FACTOR = NW <= 4;
+    static constexpr bool FACTOR = NW <= 4 && BT > 1;
     static constexpr bool HOLD = NW * BT <= 20;
     double xs[BT * NW];
     cplx gh[NW];
@@ -672,7 +714,7 @@ struct BandsGeneric {
         }
     }
     // Columns [p, end) of the wave's [.., p_hi).
-    __device__ __forceinline__ void columns(int p, int end, int p_hi, int nb, int nv, int ng,
+    __device__ __forceinline__ void columns(int p, int end, int p_hi, int n_end, int nv, int ng,
                                             int n0, int gc, double vc, gptr<double2> aqsm,
                                             gptr<double2> ieps, gptr<double2> wt,
                                             const double2 *__restrict__ ga,
@@ -696,7 +738,7 @@ struct BandsGeneric {
 #pragma unroll
             for (int u = 0; u < BT; ++u) {
                 cplx vz = cmake(0.0, 0.0);
-                if (n0 + u < nb) {  // wave-uniform, like the next
+                if (n0 + u < n_end) {  // wave-uniform, like the next
                     cplx Z, W;
                     if (n0 + u < nv) band_zw<NW, true, false>(xs[u], ga, gs, ps, Z, W);
                     else band_zw<NW, false, false>(xs[u], ga, gs, ps, Z, W);
@@ -721,7 +763,7 @@ template <int NW, int BT, int PW, bool AM>
 __global__ void __launch_bounds__(kBwdThreads * PW)
 __attribute__((amdgpu_waves_per_eu(PW > 1 ? 4 : AM ? GPP_BWD_BANDS_AM_WAVES
                                                    : GPP_BWD_BANDS_WAVES)))
-bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
+bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int single, int ngb, int nps,
           const double2 *__restrict__ aqsm, const double2 *__restrict__ aqsn,
           const double2 *__restrict__ ieps, const double2 *__restrict__ wt,
           const double *__restrict__ vcoul, const double *__restrict__ wx,
@@ -737,7 +779,10 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
     const int seg = __builtin_amdgcn_readfirstlane((int)(wg / per_seg));
     const long in_seg = wg - (long)seg * per_seg;
     const int gblk = __builtin_amdgcn_readfirstlane((int)(in_seg / nbt));
-    const int n0 = __builtin_amdgcn_readfirstlane((int)(in_seg - (long)gblk * nbt) * BT);
+    // the first `single` tiles hold one (occupied) band, the others BT
+    const int tile = __builtin_amdgcn_readfirstlane((int)(in_seg - (long)gblk * nbt));
+    const int n0 = tile < single ? tile : single + (tile - single) * BT;
+    const int n_end = tile < single ? tile + 1 : nb;
     double2 *const dst = grad_an ? grad_an + (size_t)seg * nb * ng : nullptr;
     const int g = gblk * kRowsPerBlock + wid * kWave + lane;
     const bool valid = g < ng;
@@ -765,6 +810,7 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
     amc.lane = lane;
     amc.gblk = gblk;
     amc.n0 = n0;
+    amc.n_end = n_end;
     amc.nb = nb;
     amc.np = np;
 
@@ -799,7 +845,7 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
             const int p = p_lo + at < p_hi ? p_lo + at : p_hi;
             const int end = p + step < p_hi ? p + step : p_hi;
             amc.first = p;
-            f.columns(p, end, p_hi, nb, nv, ng, n0, gc, vc, as_global(aqsm), as_global(ieps),
+            f.columns(p, end, p_hi, n_end, nv, ng, n0, gc, vc, as_global(aqsm), as_global(ieps),
                       as_global(wt), ga, gs, an, amc, acc);
             if constexpr (AM) am_flush(amc, end);
         }
@@ -828,7 +874,7 @@ bwd_bands(int nb, int nv, int ng, int np, long nwg, int nbt, int ngb, int nps,
 #pragma unroll
         for (int u = 0; u < BT; ++u) {
             const int n = n0 + u;
-            if (n < nb) dst[(size_t)n * ng + g] = make_double2(acc[u].re, acc[u].im);
+            if (n < n_end) dst[(size_t)n * ng + g] = make_double2(acc[u].re, acc[u].im);
         }
     }
 }
@@ -885,6 +931,22 @@ __global__ void fill_zero_n(double2 *a, long n)
     if (i < n) a[i] = make_double2(0.0, 0.0);
 }
 
+// Whether a pairs workgroup's four waves share one tile: where that is less
+// work on the fullest compute unit, a tile's fixed part (set-up, gradients)
+// counting as kPairsTileBands bands; at most 1/64 less counts as equal.
+// Whole adjoint, rows x bands x columns (nfreq), apart and shared: 512 x 32 x
+// 64 (3) 41.4 and 37.4 us, 1400 x 64 x 102 (5) 118.5 and 107.9, 3001 x 101 x
+// 150 (5) 354 and 338; but 3072 x 64 x 102 (3) 128.2 and 130.2, 2048 x 16 x 102
+// (3) 60.2 and 62.0.
+constexpr int kPairsTileBands = 3;
+static bool pairs_share(long gtiles, int ngb, int np, int nb)
+{
+    const auto cost = [](long blocks, double bands) {
+        return (double)((blocks + kBandsCUs - 1) / kBandsCUs) * (bands + kPairsTileBands);
+    };
+    return cost(gtiles * np, (double)nb / kBwdWaves) < cost((long)ngb * np, nb) * (1 - 1.0 / 64);
+}
+
 BwdGeometry bwd_geometry(const Dims32 &d)
 {
     BwdGeometry geo{};
@@ -892,7 +954,9 @@ BwdGeometry bwd_geometry(const Dims32 &d)
     geo.xgh_elems = (size_t)d.nw * d.nb;
     if (d.nb > 0 && d.ng > 0 && d.np > 0) {
         geo.ngb = (d.ng + kRowsPerBlock - 1) / kRowsPerBlock;
-        geo.pair_blocks = (long)geo.ngb * d.np;
+        const long gtiles = (d.ng + kWave - 1) / kWave;
+        geo.share_pairs = pairs_share(gtiles, geo.ngb, d.np, d.nb);
+        geo.pair_blocks = (geo.share_pairs ? gtiles : geo.ngb) * d.np;
         geo.nbt = (d.nb + kBandTile - 1) / kBandTile;
         geo.ngt = geo.ngb * kBwdWaves;
         // Split the p loop into segments when one pass has too few waves:
@@ -907,7 +971,14 @@ BwdGeometry bwd_geometry(const Dims32 &d)
         geo.nps = (int)(nps < max_nps ? nps : max_nps);
         geo.band_tiles = per_seg * geo.nps;
         geo.short_bands = geo.band_tiles < kBandsShortBelow;
-        if (geo.short_bands) geo.nbt = (d.nb + kShortTile - 1) / kShortTile;
+        const long per_band = (long)geo.ngb * geo.nps;
+        geo.tile_bands = !geo.short_bands                  ? kBandTile
+                         : per_band * d.nb <= kBandsCUs ? kTinyTile
+                                                           : kShortTile;
+        const int nocc = d.nv < d.nb ? d.nv : d.nb, bt = geo.tile_bands;
+        const bool few = geo.short_bands && per_band * ((d.nb + bt - 1) / bt) <= kSingleBlocks;
+        geo.single = nocc <= kSingleOccupied || few ? nocc : 0;
+        geo.nbt = geo.single + (d.nb - geo.single + bt - 1) / bt;
         geo.band_blocks = (long)geo.ngb * geo.nbt * geo.nps;
         geo.am_part_elems = (size_t)geo.ngb * d.nb * d.np;
         geo.an_part_elems = geo.nps > 1 ? (size_t)geo.nps * d.nb * d.ng : 0;
@@ -933,10 +1004,10 @@ static hipError_t launch_bwd_nw(const Dims32 &d, const BwdGeometry &geo, const D
     double2 *an_part = reinterpret_cast<double2 *>(after + up(geo.am_part_elems));
     hipError_t e;
     if (out.grad_wt || out.grad_ieps) {
-        hipLaunchKernelGGL(bwd_pairs<NW>, dim3((unsigned)geo.pair_blocks), dim3(kBwdThreads), 0,
-                           st, d.nb, d.nv, d.ng, d.np, geo.pair_blocks, in.aqsm, in.aqsn,
-                           in.ieps, in.wt, in.vcoul, in.wx, ga, gs, out.grad_wt,
-                           out.grad_ieps);
+        const auto kernel = geo.share_pairs ? bwd_pairs<NW, true> : bwd_pairs<NW, false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)geo.pair_blocks), dim3(kBwdThreads), 0, st,
+                           d.nb, d.nv, d.ng, d.np, geo.pair_blocks, in.aqsm, in.aqsn, in.ieps,
+                           in.wt, in.vcoul, in.wx, ga, gs, out.grad_wt, out.grad_ieps);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (out.grad_an || out.grad_am) {
@@ -946,11 +1017,14 @@ static hipError_t launch_bwd_nw(const Dims32 &d, const BwdGeometry &geo, const D
         double2 *const am_dst = out.grad_am ? am_part : nullptr;
         const auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, 0, st, d.nb, d.nv, d.ng, d.np, geo.band_blocks,
-                               geo.nbt, geo.ngb, geo.nps, in.aqsm, in.aqsn, in.ieps, in.wt,
+                               geo.nbt, geo.single, geo.ngb, geo.nps, in.aqsm, in.aqsn, in.ieps, in.wt,
                                in.vcoul, in.wx, ga, gs, an_dst, am_dst);
             return hipGetLastError();
         };
-        if (geo.short_bands)
+        if (geo.tile_bands == kTinyTile)
+            e = out.grad_am ? launch(bwd_bands<NW, kTinyTile, kShortRanges, true>)
+                            : launch(bwd_bands<NW, kTinyTile, kShortRanges, false>);
+        else if (geo.short_bands)
             e = out.grad_am ? launch(bwd_bands<NW, kShortTile, kShortRanges, true>)
                             : launch(bwd_bands<NW, kShortTile, kShortRanges, false>);
         else

@@ -38,7 +38,10 @@ struct BwdGeometry {
     int nbt = 0;             // band tiles of the bands kernel
     int ngt = 0;             // 64-row g tiles of the bands kernel
     int nps = 1;             // segments of the bands kernel's p range
+    bool share_pairs = false;  // pairs kernel: a workgroup's waves share a tile
     bool short_bands = false;  // bands kernel: the form for short grids
+    int tile_bands = 0;        // bands per tile of the bands kernel
+    int single = 0;            // its first tiles, of one (occupied) band each
     long band_tiles = 0;     // bands-kernel waves (segments x g tiles x band tiles)
     long band_blocks = 0;
     size_t gh_elems = 0, xgh_elems = 0, am_part_elems = 0;  // complex elements
