@@ -1,0 +1,87 @@
+"""GPU parity of the forms the forward and the adjoint choose by grid size, at
+the sizes where one form ends and the next begins, against the oracle.
+
+Forward: below 2048 tiles (64 rows x 2 columns at nfreq 3; 3 columns at 2, 1
+from 4 on, 2 at 1) waves share a tile's bands, 8, 4 or 2 of them; from there
+on the bands may be cut into chunks; above 24576 partial sums the reduction
+takes two stages.  Adjoint: one, two or four bands per workgroup, a tile of
+its own for each of a few occupied bands, and tiles of the pairs kernel shared
+by four waves.
+
+Bars: forward 1e-12 relative per output; adjoint per entry 1e-12 relative
+plus 1e-12 of the array's largest checked entry.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2008_11326_amd import inputs as I
+from tests.gpu_helpers import assert_parity, mixed_pole_problem, say, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpp():
+    import paper_2008_11326_amd as gpp
+    return gpp
+
+
+EACH_NFREQ = [(nb, nv, ng, npw, nw) for nw in range(1, 9)
+              for nb, nv, ng, npw in ((21, 9, 130, 7), (3, 2, 70, 3))]
+
+
+@pytest.mark.parametrize("shape", EACH_NFREQ + [
+    (1, 0, 1, 1, 3), (6, 6, 65, 2, 3), (19, 18, 64, 1, 2),
+    # 1023 and 1024 tiles (8 and 4 waves per tile), 2047 and 2048 (split, long)
+    (9, 2, 700, 186, 3), (9, 2, 1024, 127, 3), (9, 2, 1472, 178, 3), (9, 2, 2048, 127, 3),
+    # finer band chunks, a ragged last one
+    (61, 3, 2048, 102, 5), (127, 70, 4090, 204, 3),
+    # 768 workgroups (one reduction stage) and 780 (two)
+    (3, 1, 3072, 64, 8), (3, 1, 3072, 65, 8),
+], ids=str)
+def test_forward(gpp, shape):
+    import torch
+    prob = mixed_pole_problem(sum(shape), I.Dims(*shape), 0.01)
+    say(f"[grid forms] forward {shape}")
+    ach, asx = gpp.sigma_fwd(**to_device(prob), nvband=prob.dims.nvband)
+    torch.cuda.synchronize()
+    ref = oracle.sigma_fwd(prob)
+    assert_parity(ach.cpu().numpy(), ref[0], ref[2], "achtemp")
+    assert_parity(asx.cpu().numpy(), ref[1], ref[3], "asxtemp")
+
+
+@pytest.mark.parametrize("shape", EACH_NFREQ + [(67, 3, 1000, 6, nw) for nw in range(1, 9)] + [
+    (64, 3, 1000, 6, 3), (65, 65, 1000, 2, 3),  # 256 and 260 one-band workgroups
+    (67, 13, 1000, 6, 3),                       # more occupied bands, few workgroups
+    (67, 21, 8000, 3, 2),                       # and many: a tile shared with an unoccupied one
+    (253, 3, 8192, 2, 1), (252, 3, 8192, 2, 3),  # 8192 and 8064 waves of the four-band form
+    (259, 13, 8100, 2, 3),
+    (16, 1, 2048, 102, 3), (64, 2, 2048, 102, 2),  # pairs tiles apart and shared
+], ids=str)
+def test_adjoint(gpp, shape):
+    import torch
+    prob = I.make_problem(I.Dims(*shape), sum(shape) + 1, 0.02)
+    nb, _, ng, npw, nw = shape
+    rng = np.random.default_rng(sum(shape))
+    ga, gs = I.make_upstream_grad(nw, rng)
+    say(f"[grid forms] adjoint {shape}")
+    t = lambda z: torch.from_numpy(np.ascontiguousarray(z)).to("cuda:0")
+    grads = gpp.sigma_bwd(**to_device(prob), nvband=prob.dims.nvband, grad_achtemp=t(ga),
+                          grad_asxtemp=t(gs))
+    torch.cuda.synchronize()
+    for name, got in zip(("aqsmtemp", "aqsntemp", "I_eps_array", "wtilde_array"), grads):
+        got = got.cpu().numpy()
+        rows, cols = got.shape
+        used = npw if name == "aqsmtemp" else cols
+        # random entries, and the first and last rows against the columns' edges
+        idx = np.stack([rng.integers(0, rows, 24), rng.integers(0, used, 24)], axis=1)
+        edge = [(r, c) for r in {0, 1 % rows, rows - 2 if rows > 1 else 0, rows - 1}
+                for c in {0, used // 2, used - 1}]
+        idx = np.concatenate([idx, np.array(edge)]).astype(np.int64)
+        ref = oracle.grad_entries(prob, ga, gs, name, idx)
+        err = np.abs(got[idx[:, 0], idx[:, 1]] - ref)
+        bad = err > 1e-12 * np.abs(ref) + 1e-12 * np.max(np.abs(ref))
+        assert not np.any(bad), (name, idx[bad][:5], err[bad][:5], ref[bad][:5])
+        if name == "aqsmtemp":
+            assert np.all(got[:, npw:] == 0)
