@@ -495,7 +495,7 @@ def main():
                      "frac": round(q["algorithmic_tflops_launch"] /
                                    FP64_VECTOR_PEAK_TFLOPS, 4),
                      "traffic": q.get("traffic"),
-                     "kernel": f"gpp::fwd_tiles<{d.nfreq},2> + two reduce_rows<{d.nfreq}> "
+                     "kernel": f"gpp::fwd_tiles<{d.nfreq}, ...> + two reduce_rows<{d.nfreq}, ...> "
                                f"(one gpp_sigma_fwd), algorithmic FLOPs",
                      "launch_ms": round(r["launch_ms"], 4)},
         "max_rel_err_vs_oracle": max_rel_err(args.workload, res),
