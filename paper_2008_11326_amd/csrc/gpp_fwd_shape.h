@@ -10,11 +10,12 @@ namespace gpp {
 // aqsntemp load serve more terms; the accumulators (columns x nfreq x 4
 // doubles) bound how many fit.  Pairs (columns, bands) for nfreq = 1..8;
 // nfreq 3 takes GPP_FWD_COLS x GPP_FWD_BANDS.  Measured on MI355X at 512
-// bands, 32768 rows, 1638 columns (best of 3 alternating rounds): nfreq 2
-// with three columns 2 % faster than with two; nfreq 5 and 6 with 2-band
-// groups 20 % and 15 % faster than 1-band ones; nfreq 1 with 2 x 2 faster
-// than 2 x 6, 3 x 4, 4 x 3 or 6 x 2; nfreq 4 with 1 x 2 faster than 1 x 3
-// or 2 x 1.
+// bands, 32768 rows, 1638 columns: nfreq 1 with 2 x 2 15.4 ms, 4 x 2 15.5, 3 x 4
+// 15.3, 2 x 4 16.5 and 3 x 2 14.1, whose longer group of the short grids' form
+// needs scratch, though (128 x 2000 x 100: 34.7 us against 27.7); nfreq 2 with
+// 3 x 2 22.6 ms, 2 x 3 23.4, 2 x 2 23.2, 3 x 1 23.6; nfreq 5 and 6 with 2-band
+// groups 20 % and 15 % faster than 1-band ones; nfreq 4 with 1 x 2 faster than
+// 1 x 3 or 2 x 1.
 #ifndef GPP_FWD_COLS
 #define GPP_FWD_COLS 2
 #endif

@@ -8,18 +8,26 @@
 
 namespace gpp {
 
-// Column tiles per block of the tile walk: blocks of Q column tiles go
-// through all g-tiles, so that the block's aqsmtemp columns (Q * cols * 16 bytes per
-// band: 2 MB at 128 two-column tiles and 512 bands, half an XCD's L2) stay
+// Column tiles per block of the tile walk: blocks of Q tiles of C columns go
+// through all g-tiles, so that the block's aqsmtemp columns (Q * C * 16 bytes
+// per band: 2 MB at 128 two-column tiles and 512 bands, half an XCD's L2) stay
 // in the L2 while the g-tiles' aqsntemp rows stream past, each row fetched
-// once per block.  Measured with band chunks of 512 on MI355X: Q = 128
-// took the HBM-side traffic of the 1024-band forward from 45.3 GB (Q = 64)
-// to 39.1 GB and its time, the 512-band one's and the 64-state batched
-// workload's down by 0.4-0.9 %; Q = 160 and 192 (2.5 and 3 MB) thrashed
-// the L2 (85 and 98 GB) and ran slower.
+// once per block.  Q is GPP_FWD_COL_BLOCK, at most twice that many columns.
+// Measured with band chunks of 512 on MI355X, nfreq 3: Q = 128 took the
+// HBM-side traffic of the 1024-band forward from 45.3 GB (Q = 64) to 39.1 GB
+// and its time, the 512-band one's and the 64-state batched workload's down by
+// 0.4-0.9 %; Q = 160 and 192 (2.5 and 3 MB) thrashed the L2 (85 and 98 GB) and
+// ran slower.  At 512 bands x 32768 rows x 1638 columns, nfreq 2 (three
+// columns), 128 and 85 tiles: 24.6 and 22.1 ms.  One-column tiles at 128 and
+// 256: 73.0 and 72.0 ms there at nfreq 7, but 40.8 and 41.3 at 900 x 17000 x
+// 900, nfreq 8.
 #ifndef GPP_FWD_COL_BLOCK
 #define GPP_FWD_COL_BLOCK 128
 #endif
+constexpr int col_block(int cols)
+{
+    return cols > 2 ? 2 * GPP_FWD_COL_BLOCK / cols : GPP_FWD_COL_BLOCK;
+}
 
 // (g-tile, column tile, band chunk) of a tile index, a bijection on
 // [0, gtiles * npt * nchunk).  Within a block of Q column tiles the walk
@@ -27,11 +35,10 @@ namespace gpp {
 // are wave-uniform and made scalar explicitly, since the divisions run on
 // the vector unit and a column index left in vector registers would turn
 // the tile's aqsmtemp loads into vector loads.
-template <typename Int>
+template <int Q, typename Int>
 __device__ __forceinline__ void tile_coords_in(Int tile, int npt, int gtiles, int nchunk, int &gt,
                                                int &pt, int &ck)
 {
-    constexpr int Q = GPP_FWD_COL_BLOCK;
     const Int per = (Int)Q * (Int)gtiles * (Int)nchunk;
     const int c = (int)(tile / per);
     Int r = tile - (Int)c * per;
@@ -46,13 +53,14 @@ __device__ __forceinline__ void tile_coords_in(Int tile, int npt, int gtiles, in
 // In 32 bits wherever a block of tiles and the tile index fit (a 64-bit
 // division costs about a hundred instructions, three of them as much as the
 // band loop of a few bands).
+template <int Q>
 __device__ __forceinline__ void tile_coords(long tile, int npt, int gtiles, int nchunk, int &gt,
                                             int &pt, int &ck)
 {
-    if (tile < (1L << 31) && (long)GPP_FWD_COL_BLOCK * gtiles * nchunk < (1L << 31))
-        tile_coords_in<uint32_t>((uint32_t)tile, npt, gtiles, nchunk, gt, pt, ck);
+    if (tile < (1L << 31) && (long)Q * gtiles * nchunk < (1L << 31))
+        tile_coords_in<Q, uint32_t>((uint32_t)tile, npt, gtiles, nchunk, gt, pt, ck);
     else
-        tile_coords_in<long>(tile, npt, gtiles, nchunk, gt, pt, ck);
+        tile_coords_in<Q, long>(tile, npt, gtiles, nchunk, gt, pt, ck);
     gt = __builtin_amdgcn_readfirstlane(gt);
     pt = __builtin_amdgcn_readfirstlane(pt);
     ck = __builtin_amdgcn_readfirstlane(ck);
