@@ -103,10 +103,11 @@ size_t gpp_sigma_fwd_workspace(const gpp_dims *dims);
  *   workspace:       device, >= gpp_sigma_fwd_workspace(dims) bytes,
  *                    16-byte aligned; contents unspecified afterwards
  *   stream:          hipStream_t or NULL
- * Three kernels run on `stream`: the tile kernel writes one partial per
- * workgroup into the workspace (above 512 bands, the band loop of each tile
- * is split into chunks of at most 512 bands, each with its own partial),
- * then two fixed-order reduction stages produce the outputs (the separate
+ * Two or three kernels run on `stream`: the tile kernel writes one partial
+ * per workgroup into the workspace (the band loop of a tile is split into
+ * chunks of at most 512 bands, each with its own partial, and finer where
+ * that evens out the last workgroups), then one fixed-order reduction stage,
+ * or two above 24576 partial sums, produces the outputs (the separate
  * reduction kernel of Sec. II-A).
  * Masked (branch B/C) Coulomb-hole terms add nothing to the sums (the
  * branch test is the execution mask of their accumulation), so an output

@@ -1,7 +1,7 @@
 // gpp_batched.hip -- persistent forward over many quasiparticle states of
 // uneven sizes in one launch (gfx950, fp64).
 //
-// The tiles of all states (each state's forward tiles: one or two G'
+// The tiles of all states (each state's forward tiles: one to three G'
 // columns x 64 G rows, G'-column fastest) are concatenated in a schedule order chosen by
 // the plan.  Two kernel forms exist: the static one below and a work-queue
 // one (batched_queue) whose waves take small chunks of the list from atomic

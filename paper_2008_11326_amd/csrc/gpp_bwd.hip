@@ -39,6 +39,15 @@
 // are added over the workgroup's four waves and written as one partial per
 // 256-row block; reduce_am sums the partials in a fixed order and zero-fills
 // columns >= ngpown.  No atomics: results are bitwise reproducible.
+//
+// What bounds it.  Large grids: the fp64 vector ALU at the clock the part
+// holds (256 bands x 16384 rows x 819 columns, nfreq 3: pairs kernel 6.8 ->
+// 6.7 ms, 0.92 of the issue slots at 1.98 GHz; bands kernel 7.5 -> 6.7 ms, 0.75
+// -> 0.87 at 2.05 GHz, since it needs x and gh only and its loads run ahead;
+// whole adjoint 14.1 -> 13.1 ms timed in turn).  Short grids: the number of
+// waves and the longest workgroup, hence the forms below (512 rows x 32 bands x
+// 64 columns: 142 us in four-band workgroups, 37.4 now; 3001 x 101 x 150, nfreq
+// 5: 634 and 344).
 #include "gpp_device.h"
 #include "gpp_fwd_tile.h"
 #include "gpp_internal.h"

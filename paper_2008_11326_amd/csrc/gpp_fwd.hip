@@ -1,11 +1,11 @@
 // gpp_fwd.hip -- forward GPP reduction on gfx950 (fp64 vector ALU, no MFMA).
 //
-// Work decomposition.  A wave owns two G' columns (one with more than three
-// frequencies) and 64 consecutive G rows g (one per lane) and walks every
+// Work decomposition.  A wave owns one to three G' columns (by the frequency
+// count) and 64 consecutive G rows g (one per lane) and walks every
 // band n sequentially, as in the band-inner loop order of Sec. III v4
 // (bands serial per thread keeps the g-fastest arrays coalesced and reads
-// wtilde/I_eps once); each aqsntemp[n][g] a lane loads serves both
-// columns.  Within a wave p and n are uniform, so aqsmtemp[n][p] and
+// wtilde/I_eps once); each aqsntemp[n][g] a lane loads serves all
+// of them.  Within a wave p and n are uniform, so aqsmtemp[n][p] and
 // wx_array[w][n] are scalar loads; the frequencies are register-blocked
 // (all NW in one pass, none of v5's recompute).
 //
@@ -17,20 +17,30 @@
 // and ends with  achtemp += vcoul/2 * e * (om P1 - wtr P2).  The branch-A
 // test is one compare against a per-(p,g) threshold that reproduces the
 // specification exactly (gpp_device.h).  r = 1/wdiffr needs no IEEE divide
-// (the v1 idea); the 2*BU*NW reciprocals of a group of BU bands and both
-// columns come from a single hardware reciprocal by batch inversion
+// (the v1 idea); the reciprocals of a group of BU bands, all columns and
+// frequencies, come from a single hardware reciprocal by batch inversion
 // (gpp_device.h: unclamped denominators, a lane test on (Im om)^2 for the
 // product's range), and the branch-A test is the execution mask around
 // each term's four fused multiply-adds, so a masked term adds nothing and
 // costs no select.  Occupied bands (n < nvband) also evaluate the
-// screened-exchange term, from batch-inverted |x - om|^2 and |x + om|^2
-// instead of a complex divide (gpp_fwd_tile.h).  Above 512 bands each
-// tile's band loop is split into chunks, each a tile of its own.
+// screened-exchange term, after the hole's sums, from one batch inversion of
+// |x - om|^2 |x + om|^2 per band instead of a complex divide
+// (gpp_fwd_tile.h).  Above 512 bands each tile's band loop is split into
+// chunks, each a tile of its own.
 //
-// Each workgroup (4 waves) writes one partial per output into the
-// workspace; two reduction kernels then sum the partials in a fixed order
-// (the separate reduction kernel of Sec. II-A), so results are bitwise
-// reproducible.
+// What bounds it.  Large grids: the fp64 vector ALU at the clock the part
+// holds under that load (1024 bands x 65536 rows x 3276 columns, nfreq 3:
+// 260.0 ms before and 250.3 ms after the loop's loads moved ahead of their
+// use, its addresses to the scalar unit and its reciprocal chain into two
+// halves; 12.6 instructions per term in 0.89-0.91 of the issue slots, 0.85
+// before).  Short grids: launches, first loads and too few waves, hence the
+// split form, in which 2, 4 or 8 waves of a 16-wave workgroup share a tile's
+// bands (512 rows x 32 bands x 64 columns, nfreq 3: 24.1 us with four waves of
+// a tile each and two reduction stages, 10.6 so).
+//
+// Each workgroup writes one partial per output into the workspace; one or two
+// reduction kernels then sum the partials in a fixed order (the separate
+// reduction kernel of Sec. II-A), so results are bitwise reproducible.
 #include "gpp_device.h"
 #include "gpp_fwd_tile.h"
 #include "gpp_internal.h"
