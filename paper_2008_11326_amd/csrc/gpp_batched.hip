@@ -264,7 +264,7 @@ batched_flat(const StateDesc *__restrict__ st, int nstates, double *__restrict__
     if (lane < 4 * NW) red[wid][lane] = 0.0;  // the tile may write only some of it
     if (local < ntile) {
         int gt, pt, ck;
-        tile_coords<col_block(C)>(local, npt, (d.ng + kWave - 1) / kWave, 1, gt, pt, ck);
+        tile_coords(local, col_block<NW, C>(d.ng), npt, (d.ng + kWave - 1) / kWave, 1, gt, pt, ck);
         RowSink<NW> sink{red[wid], lane, nullptr};
         fwd_tile_body<NW, BU, C>(d.nb, d.nv, 0, d.nb, d.ng, d.np, C * pt, gt, lane,
                                  as_global(d.aqsm), as_global(d.aqsn), as_global(d.ieps),

@@ -101,7 +101,7 @@ fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_ban
         // consecutive tiles share a g-tile (and so the same aqsntemp rows)
         const int npt = (np + C - 1) / C;  // column tiles per g-tile
         int gt, pt, ck;
-        tile_coords<col_block(C)>(tile, npt, (ng + kWave - 1) / kWave, nchunk, gt, pt, ck);
+        tile_coords(tile, col_block<NW, C>(ng), npt, (ng + kWave - 1) / kWave, nchunk, gt, pt, ck);
         int n_lo = ck * chunk_bands;
         int n_hi = nb - n_lo < chunk_bands ? nb : n_lo + chunk_bands;
         if (WAVES > kFwdWaves) {

@@ -20,13 +20,19 @@ namespace gpp {
 // ran slower.  At 512 bands x 32768 rows x 1638 columns, nfreq 2 (three
 // columns), 128 and 85 tiles: 24.6 and 22.1 ms.  One-column tiles at 128 and
 // 256: 73.0 and 72.0 ms there at nfreq 7, but 40.8 and 41.3 at 900 x 17000 x
-// 900, nfreq 8.
+// 900, nfreq 8.  With one frequency the rows stream by about twice as fast,
+// and where their pitch is a multiple of 256 KB, so that every band meets in
+// the same sets of the caches, half the tiles are better: 128 and 64 tiles 15.6
+// and 14.6 ms there, 3.90 and 3.67 at 16384 rows x 819 columns; but 17.1 and
+// 17.3 at 700 x 24000 x 2000, 1.68 and 1.69 at 300 x 12000 x 900.
 #ifndef GPP_FWD_COL_BLOCK
 #define GPP_FWD_COL_BLOCK 128
 #endif
-constexpr int col_block(int cols)
+template <int NW, int C>
+__device__ __forceinline__ int col_block(int ng)
 {
-    return cols > 2 ? 2 * GPP_FWD_COL_BLOCK / cols : GPP_FWD_COL_BLOCK;
+    if (NW == 1 && ng % 16384 == 0) return GPP_FWD_COL_BLOCK / 2;
+    return C > 2 ? 2 * GPP_FWD_COL_BLOCK / C : GPP_FWD_COL_BLOCK;
 }
 
 // (g-tile, column tile, band chunk) of a tile index, a bijection on
@@ -35,8 +41,8 @@ constexpr int col_block(int cols)
 // are wave-uniform and made scalar explicitly, since the divisions run on
 // the vector unit and a column index left in vector registers would turn
 // the tile's aqsmtemp loads into vector loads.
-template <int Q, typename Int>
-__device__ __forceinline__ void tile_coords_in(Int tile, int npt, int gtiles, int nchunk, int &gt,
+template <typename Int>
+__device__ __forceinline__ void tile_coords_in(Int tile, int Q, int npt, int gtiles, int nchunk, int &gt,
                                                int &pt, int &ck)
 {
     const Int per = (Int)Q * (Int)gtiles * (Int)nchunk;
@@ -53,14 +59,13 @@ __device__ __forceinline__ void tile_coords_in(Int tile, int npt, int gtiles, in
 // In 32 bits wherever a block of tiles and the tile index fit (a 64-bit
 // division costs about a hundred instructions, three of them as much as the
 // band loop of a few bands).
-template <int Q>
-__device__ __forceinline__ void tile_coords(long tile, int npt, int gtiles, int nchunk, int &gt,
+__device__ __forceinline__ void tile_coords(long tile, int Q, int npt, int gtiles, int nchunk, int &gt,
                                             int &pt, int &ck)
 {
     if (tile < (1L << 31) && (long)Q * gtiles * nchunk < (1L << 31))
-        tile_coords_in<Q, uint32_t>((uint32_t)tile, npt, gtiles, nchunk, gt, pt, ck);
+        tile_coords_in<uint32_t>((uint32_t)tile, Q, npt, gtiles, nchunk, gt, pt, ck);
     else
-        tile_coords_in<Q, long>(tile, npt, gtiles, nchunk, gt, pt, ck);
+        tile_coords_in<long>(tile, Q, npt, gtiles, nchunk, gt, pt, ck);
     gt = __builtin_amdgcn_readfirstlane(gt);
     pt = __builtin_amdgcn_readfirstlane(pt);
     ck = __builtin_amdgcn_readfirstlane(ck);

@@ -39,6 +39,8 @@ EACH_NFREQ = [(nb, nv, ng, npw, nw) for nw in range(1, 9)
     (61, 3, 2048, 102, 5), (127, 70, 4090, 204, 3),
     # three-column tiles over two blocks of the tile walk (85 tiles each)
     (5, 2, 320, 300, 2), (5, 1, 2048, 300, 2),
+    # one frequency, rows of a 256 KB pitch: blocks of 64 two-column tiles
+    (2, 1, 16384, 140, 1),
     # 768 workgroups (one reduction stage) and 780 (two)
     (3, 1, 3072, 64, 8), (3, 1, 3072, 65, 8),
 ], ids=str)
