@@ -48,6 +48,7 @@
 // waves and the longest workgroup, hence the forms below (512 rows x 32 bands x
 // 64 columns: 142 us in four-band workgroups, 37.4 now; 3001 x 101 x 150, nfreq
 // 5: 634 and 344).
+#include "gpp_bwd_shape.h"
 #include "gpp_device.h"
 #include "gpp_fwd_tile.h"
 #include "gpp_internal.h"
@@ -406,17 +407,15 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
 
     // the wave's bands: its shares of the occupied ones and of the groups
     const int nocc = nv < nb ? nv : nb, k = SHARE ? wid : 0;
-    const int groups = (nb - nocc + G - 1) / G;
-    const int last = nocc + groups * (k + 1) / S * G;
-    const int end = last < nb ? last : nb;
+    const int end = share_first_band(nb, nocc, G, k + 1, S);
 
     cplx Ge = cmake(0.0, 0.0), Gw = cmake(0.0, 0.0);
-    pairs_occupied<NW>(nocc * k / S, nocc * (k + 1) / S, nb, ng, as_global(aqsn),
-                       as_global(am_col), as_global(wx), ga, gs, ps, goff, Ge, Gw);
+    pairs_occupied<NW>(share_begin(nocc, k, S), share_begin(nocc, k + 1, S), nb, ng,
+                       as_global(aqsn), as_global(am_col), as_global(wx), ga, gs, ps, goff, Ge, Gw);
     cplx A2[NW], B1[NW], B2[NW], B3[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) A2[w] = B1[w] = B2[w] = B3[w] = cmake(0.0, 0.0);
-    int n = nocc + groups * k / S * G;
+    int n = share_first_band(nb, nocc, G, k, S);
     n = pairs_bands<NW, G>(n, end, nb, ng, as_global(aqsn), goff, as_global(am_col),
                            as_global(wx), ps, A2, B1, B2, B3);
     if constexpr (G > 1)
