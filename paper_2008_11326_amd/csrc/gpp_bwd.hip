@@ -29,7 +29,18 @@
 // branch A, |x - om|^2 r = 1,
 //   sum_n conj(M) K = sum_w ga_w/2 (B1_w - om A2_w),
 //   sum_n conj(M) L = sum_w ga_w/2 (B1_w - 2 (Im om)^2 B2_w - 2i Im om B3_w).
-// Occupied bands form K and L per band.
+// B1 - om A2 cancels by |om| / |x - om|, up to 500 on branch A, so from five
+// frequencies on the sums are A2 and
+//   C1_w = sum_n conj(M) (x - Re om) r,
+//   D1_w = sum_n conj(M) x r (1 - 2 (Im om)^2 r),  B3_w as above, with
+//   sum_n conj(M) K = sum_w ga_w/2 (C1_w - i Im om A2_w),
+//   sum_n conj(M) L = sum_w ga_w/2 (D1_w - 2i Im om B3_w).
+// (dI_eps at |om| / |x - om| = 450, nfreq 5 to 8, in 2^-53 of the sum of |term|:
+// up to 1000 with B1, up to 14 so; two operations per term more: whole adjoint,
+// bands x rows x columns, 128 x 8192 x 400 at nfreq 5 and 8 2.66 -> 2.78 and
+// 3.97 -> 4.19 ms, 101 x 3001 x 150 at nfreq 5 362 -> 374 us.)
+// Occupied bands, and up to four frequencies the bands left over of the
+// groups, form K and L per band.
 // bwd_bands (lane = g; a workgroup of four waves owns kBandTile bands and
 // 256 consecutive rows, 64 per wave, and walks a range of G' columns)
 // forms vcoul conj(e) Z per term, adds aqsmtemp[n][p] times it into
@@ -66,6 +77,12 @@ constexpr int kRowsPerBlock = kBwdWaves * kWave;  // g rows per workgroup (both 
 #endif
 constexpr int kPairsGroup[8] = {GPP_BWD_PAIRS_GROUP};
 constexpr int pairs_group(int nw) { return kPairsGroup[nw - 1]; }
+// Which four sums the pairs kernel keeps: A2, C1, D1, B3 from five frequencies
+// on, A2, B1, B2, B3 below (two operations per term fewer).
+constexpr bool pairs_many(int nw) { return nw >= 5; }
+static_assert(pairs_group(5) == 1 && pairs_group(6) == 1 && pairs_group(7) == 1 &&
+                  pairs_group(8) == 1,
+              "with more than four frequencies no bands are left over of the groups");
 #ifndef GPP_BWD_PAIRS_WAVES
 #define GPP_BWD_PAIRS_WAVES 4, 4, 4, 3, 3, 3, 2, 2
 #endif
@@ -247,9 +264,9 @@ __device__ __forceinline__ PairState make_pair(cplx om, cplx e, double v)
     return s;
 }
 
-// One branch-A term of the pairs kernel's band sums: A2 += cM r,
-// B1 += cM x r, B2 += cM x r^2, B3 += cM x dr r^2 (dr = x - Re om), with
-// the compare d > thr as the execution mask (a term off branch A adds
+// One branch-A term of the pairs kernel's band sums, up to four frequencies:
+// A2 += cM r, B1 += cM x r, B2 += cM x r^2, B3 += cM x dr r^2 (dr = x - Re om),
+// with the compare d > thr as the execution mask (a term off branch A adds
 // nothing, whatever its reciprocal), all 64 lanes active before and after.
 __device__ __forceinline__ void pairs_term(double d, double thr, double r, double x, double dr,
                                            cplx cm, cplx &A2, cplx &B1, cplx &B2, cplx &B3)
@@ -275,6 +292,35 @@ __device__ __forceinline__ void pairs_term(double d, double thr, double r, doubl
           [ci] "v"(cm.im)
         : "vcc");
 }
+// The same from five frequencies on: A2 += cM r, C1 += cM dr r,
+// D1 += cM x r (1 - wi2x2 r), B3 += cM x dr r^2, wi2x2 = 2 (Im om)^2.
+__device__ __forceinline__ void pairs_term_many(double d, double thr, double r, double x, double dr,
+                                                double wi2x2, cplx cm, cplx &A2, cplx &C1,
+                                                cplx &D1, cplx &B3)
+{
+    double xr, yr, t;
+    asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+        "v_mul_f64 %[xr], %[r], %[x]\n\t"
+        "v_mul_f64 %[yr], %[r], %[dr]\n\t"
+        "v_fma_f64 %[t], -%[wi2x2], %[r], 1.0\n\t"
+        "v_fma_f64 %[a2r], %[r], %[cr], %[a2r]\n\t"
+        "v_fma_f64 %[a2i], %[r], %[ci], %[a2i]\n\t"
+        "v_mul_f64 %[t], %[xr], %[t]\n\t"
+        "v_fma_f64 %[c1r], %[yr], %[cr], %[c1r]\n\t"
+        "v_fma_f64 %[c1i], %[yr], %[ci], %[c1i]\n\t"
+        "v_mul_f64 %[xr], %[xr], %[yr]\n\t"
+        "v_fma_f64 %[d1r], %[t], %[cr], %[d1r]\n\t"
+        "v_fma_f64 %[d1i], %[t], %[ci], %[d1i]\n\t"
+        "v_fma_f64 %[b3r], %[xr], %[cr], %[b3r]\n\t"
+        "v_fma_f64 %[b3i], %[xr], %[ci], %[b3i]\n\t"
+        "s_mov_b64 exec, -1"
+        : [xr] "=&v"(xr), [yr] "=&v"(yr), [t] "=&v"(t),
+          [a2r] "+v"(A2.re), [a2i] "+v"(A2.im), [c1r] "+v"(C1.re), [c1i] "+v"(C1.im),
+          [d1r] "+v"(D1.re), [d1i] "+v"(D1.im), [b3r] "+v"(B3.re), [b3i] "+v"(B3.im)
+        : [d] "v"(d), [thr] "v"(thr), [r] "v"(r), [x] "s"(x), [dr] "v"(dr), [wi2x2] "v"(wi2x2),
+          [cr] "v"(cm.re), [ci] "v"(cm.im)
+        : "vcc");
+}
 
 // The band sums of one lane over the whole groups of G unoccupied bands in
 // [n, end): one batch inversion over a group's G*NW denominators, then
@@ -283,8 +329,8 @@ __device__ __forceinline__ void pairs_term(double d, double thr, double r, doubl
 template <int NW, int G>
 __device__ __forceinline__ int pairs_bands(int n, int end, int nb, int ng, gptr<double2> aqsn,
                                            uint32_t goff, gptr<double2> am_col, gptr<double> wx,
-                                           const PairState &ps, cplx (&A2)[NW], cplx (&B1)[NW],
-                                           cplx (&B2)[NW], cplx (&B3)[NW])
+                                           const PairState &ps, cplx (&S1)[NW], cplx (&S2)[NW],
+                                           cplx (&S3)[NW], cplx (&S4)[NW])
 {
     constexpr int Kt = G * NW;
     static_assert(Kt <= 12, "a group holds at most 12 denominators");
@@ -336,8 +382,12 @@ __device__ __forceinline__ int pairs_bands(int n, int end, int nb, int ng, gptr<
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
                 const int k = u * NW + w;
-                pairs_term(d[k], ps.thr, r[k], cur.xs[k], drs[k], cM[u], A2[w], B1[w], B2[w],
-                           B3[w]);
+                if constexpr (pairs_many(NW))
+                    pairs_term_many(d[k], ps.thr, r[k], cur.xs[k], drs[k], ps.wi2x2, cM[u], S1[w],
+                                    S2[w], S3[w], S4[w]);
+                else
+                    pairs_term(d[k], ps.thr, r[k], cur.xs[k], drs[k], cM[u], S1[w], S2[w], S3[w],
+                               S4[w]);
             }
         if (--left == 0) return n;
 #pragma unroll
@@ -345,10 +395,11 @@ __device__ __forceinline__ int pairs_bands(int n, int end, int nb, int ng, gptr<
     }
 }
 
-// Occupied bands [n, end) of one lane: Ge += conj(M) Z and Gw += conj(M) W.
-// The next band's values load while this one computes.
-template <int NW>
-__device__ __forceinline__ void pairs_occupied(int n, int end, int nb, int ng, gptr<double2> aqsn,
+// Bands [n, end) of one lane, band by band (OCC: occupied ones):
+// Ge += conj(M) Z and Gw += conj(M) W.  The next band's values load while this
+// one computes.
+template <int NW, bool OCC>
+__device__ __forceinline__ void pairs_per_band(int n, int end, int nb, int ng, gptr<double2> aqsn,
                                                gptr<double2> am_col, gptr<double> wx,
                                                const double2 *__restrict__ ga,
                                                const double2 *__restrict__ gs,
@@ -363,7 +414,7 @@ __device__ __forceinline__ void pairs_occupied(int n, int end, int nb, int ng, g
         OccupiedBand<NW, 1> next;
         next.load(n + 1 < end ? n + 1 : n, nb, ng, aqsn, goff, am_col, pc, wx);
         cplx Z, W;
-        band_zw<NW, true, true>(cur.x, ga, gs, ps, Z, W);
+        band_zw<NW, OCC, true>(cur.x, ga, gs, ps, Z, W);
         const cplx cM = cmul_conj(cur.am[0], cur.an);  // conj(M) = conj(an) am
         cmac(Ge, cM, Z);
         cmac(Gw, cM, W);
@@ -410,26 +461,35 @@ bwd_pairs(int nb, int nv, int ng, int np, long nblocks, const double2 *__restric
     const int end = share_first_band(nb, nocc, G, k + 1, S);
 
     cplx Ge = cmake(0.0, 0.0), Gw = cmake(0.0, 0.0);
-    pairs_occupied<NW>(share_begin(nocc, k, S), share_begin(nocc, k + 1, S), nb, ng,
-                       as_global(aqsn), as_global(am_col), as_global(wx), ga, gs, ps, goff, Ge, Gw);
-    cplx A2[NW], B1[NW], B2[NW], B3[NW];
+    pairs_per_band<NW, true>(share_begin(nocc, k, S), share_begin(nocc, k + 1, S), nb, ng,
+                             as_global(aqsn), as_global(am_col), as_global(wx), ga, gs, ps, goff,
+                             Ge, Gw);
+    // A2, B1, B2, B3, or A2, C1, D1, B3 (pairs_many)
+    cplx S1[NW], S2[NW], S3[NW], S4[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) A2[w] = B1[w] = B2[w] = B3[w] = cmake(0.0, 0.0);
+    for (int w = 0; w < NW; ++w) S1[w] = S2[w] = S3[w] = S4[w] = cmake(0.0, 0.0);
     int n = share_first_band(nb, nocc, G, k, S);
     n = pairs_bands<NW, G>(n, end, nb, ng, as_global(aqsn), goff, as_global(am_col),
-                           as_global(wx), ps, A2, B1, B2, B3);
+                           as_global(wx), ps, S1, S2, S3, S4);
     if constexpr (G > 1)
-        pairs_bands<NW, 1>(n, end, nb, ng, as_global(aqsn), goff, as_global(am_col),
-                           as_global(wx), ps, A2, B1, B2, B3);
+        pairs_per_band<NW, false>(n, end, nb, ng, as_global(aqsn), as_global(am_col),
+                                  as_global(wx), ga, gs, ps, goff, Ge, Gw);
     // sum_n conj(M) K and sum_n conj(M) L from the band sums
     cplx SK = cmake(0.0, 0.0), SL = cmake(0.0, 0.0);
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const cplx h = half_of(ga, w);
-        const cplx k = cadd(B1[w], cmul(cmake(-ps.a, -ps.b), A2[w]));  // B1 - om A2
-        // B1 - 2 (Im om)^2 B2 - 2i (Im om) B3
-        const cplx l = cmake(fma(ps.b2, B3[w].im, fma(-ps.wi2x2, B2[w].re, B1[w].re)),
-                             fma(-ps.b2, B3[w].re, fma(-ps.wi2x2, B2[w].im, B1[w].im)));
+        cplx k, l;
+        if constexpr (pairs_many(NW)) {
+            // C1 - i (Im om) A2 and D1 - 2i (Im om) B3
+            k = cmake(fma(ps.b, S1[w].im, S2[w].re), fma(-ps.b, S1[w].re, S2[w].im));
+            l = cmake(fma(ps.b2, S4[w].im, S3[w].re), fma(-ps.b2, S4[w].re, S3[w].im));
+        } else {
+            // B1 - om A2 and B1 - 2 (Im om)^2 B2 - 2i (Im om) B3
+            k = cadd(S2[w], cmul(cmake(-ps.a, -ps.b), S1[w]));
+            l = cmake(fma(ps.b2, S4[w].im, fma(-ps.wi2x2, S3[w].re, S2[w].re)),
+                      fma(-ps.b2, S4[w].re, fma(-ps.wi2x2, S3[w].im, S2[w].im)));
+        }
         cmac(SK, h, k);
         cmac(SL, h, l);
     }
@@ -549,13 +609,27 @@ __device__ __forceinline__ void am_flush(AmCtx<BT> &a, int end)
     __syncthreads();
 }
 
+// x - a again where the first one, before the inversion, has left the
+// registers (held over it, 12 of them made the four-band kernels spill; formed
+// again, whole adjoint of 256 bands x 16384 rows x 819 columns, nfreq 3, 14.01
+// and 14.02 ms without and with it).
+__device__ __forceinline__ double subtract_again(double x, double a)
+{
+    double y;
+    asm("v_add_f64 %0, %1, -%2" : "=v"(y) : "s"(x), "v"(a));
+    return y;
+}
+
 // Fast form of a wave's columns [p_lo, p_hi): every band n0 .. n0+BT-1 is
 // unoccupied and below nb.  With r_w the masked reciprocal of |x_w - om|^2,
 //   vcoul conj(e) Z = vcoul conj(e om) sum_w gh_w (x_w - om) r_w.
-// Up to four frequencies (FACTOR) it is the sum of (x_w c1_w - c2_w) r_w with
-// the constants c1_w = gh_w vcoul conj(e om) and c2_w = om c1_w of a pair: two FMAs per term for the factor, two for the sum, and
-// per column eight products per frequency.  With more, whose constants would
-// spill, vcoul conj(e om) (S - om R) with S = sum_w gh_w (x_w r_w) and R = sum_w gh_w r_w.
+// With y_w = x_w - Re om, rounded once (x_w and Re om in separate sums would
+// cancel by |om| / |x - om|, up to 500 on branch A), it is up to four
+// frequencies (FACTOR) the sum of (y_w c1_w + c2_w) r_w with the constants
+// c1_w = gh_w vcoul conj(e om) and c2_w = -i Im om c1_w of a pair: two FMAs per
+// term for the factor, two for the sum, and per column six products per
+// frequency.  With more, whose constants would spill, vcoul conj(e om)
+// (S - i Im om R) with S = sum_w gh_w (y_w r_w) and R = sum_w gh_w r_w.
 // Either way the loop needs x and gh only, in scalar registers: x gh itself,
 // 12 complex values per column at nfreq 3 from the scalar cache, took 15
 // scalar loads with their waits per column against 4 here.  256 bands x 8192
@@ -623,10 +697,8 @@ struct BandsFast {
             if constexpr (FACTOR) {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
-                    // c2 from the rounded c1, so that x c1 - c2 cancels
-                    // against om c1 itself
                     c1[w] = cmul(gh[w], vcw);
-                    c2[w] = cmul(om, c1[w]);
+                    c2[w] = cmake(b * c1[w].im, -b * c1[w].re);
                 }
             }
 #pragma unroll
@@ -647,47 +719,51 @@ struct BandsFast {
                     // compare (all lanes are active here)
                     const int k0 = u * NW;
                     const double r0 = mask_keep(d[k0] > thr, r[k0]);
-                    const double x0 = xs[u0 * NW + k0];
+                    const double y0 = subtract_again(xs[u0 * NW + k0], a);
                     cplx vz;
                     if constexpr (FACTOR) {
-                        vz = cmake(r0 * fma(x0, c1[0].re, -c2[0].re),
-                                   r0 * fma(x0, c1[0].im, -c2[0].im));
+                        vz = cmake(r0 * fma(y0, c1[0].re, c2[0].re),
+                                   r0 * fma(y0, c1[0].im, c2[0].im));
 #pragma unroll
                         for (int w = 1; w < NW; ++w) {
-                            const double x = xs[u0 * NW + k0 + w];
-                            const cplx f = cmake(fma(x, c1[w].re, -c2[w].re),
-                                                 fma(x, c1[w].im, -c2[w].im));
+                            double y;
+                            cplx f;
                             asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+                                "v_add_f64 %[y], %[x], -%[a]\n\t"
+                                "v_fma_f64 %[fr], %[y], %[c1r], %[c2r]\n\t"
+                                "v_fma_f64 %[fi], %[y], %[c1i], %[c2i]\n\t"
                                 "v_fma_f64 %[zr], %[r], %[fr], %[zr]\n\t"
                                 "v_fma_f64 %[zi], %[r], %[fi], %[zi]\n\t"
                                 "s_mov_b64 exec, -1"
-                                : [zr] "+v"(vz.re), [zi] "+v"(vz.im)
+                                : [y] "=&v"(y), [fr] "=&v"(f.re), [fi] "=&v"(f.im),
+                                  [zr] "+v"(vz.re), [zi] "+v"(vz.im)
                                 : [d] "v"(d[k0 + w]), [thr] "v"(thr), [r] "v"(r[k0 + w]),
-                                  [fr] "v"(f.re), [fi] "v"(f.im)
+                                  [x] "s"(xs[u0 * NW + k0 + w]), [a] "v"(a), [c1r] "v"(c1[w].re),
+                                  [c1i] "v"(c1[w].im), [c2r] "v"(c2[w].re), [c2i] "v"(c2[w].im)
                                 : "vcc");
                         }
                     } else {
-                        cplx S = cscale(r0 * x0, gh[0]), R = cscale(r0, gh[0]);
+                        cplx S = cscale(r0 * y0, gh[0]), R = cscale(r0, gh[0]);
 #pragma unroll
                         for (int w = 1; w < NW; ++w) {
-                            double rx;
+                            double ry;
                             asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
-                                "v_mul_f64 %[rx], %[r], %[x]\n\t"
+                                "v_add_f64 %[ry], %[x], -%[a]\n\t"
+                                "v_mul_f64 %[ry], %[r], %[ry]\n\t"
                                 "v_fma_f64 %[rr], %[r], %[gr], %[rr]\n\t"
                                 "v_fma_f64 %[ri], %[r], %[gi], %[ri]\n\t"
-                                "v_fma_f64 %[sr], %[rx], %[gr], %[sr]\n\t"
-                                "v_fma_f64 %[si], %[rx], %[gi], %[si]\n\t"
+                                "v_fma_f64 %[sr], %[ry], %[gr], %[sr]\n\t"
+                                "v_fma_f64 %[si], %[ry], %[gi], %[si]\n\t"
                                 "s_mov_b64 exec, -1"
-                                : [rx] "=&v"(rx), [sr] "+v"(S.re), [si] "+v"(S.im),
+                                : [ry] "=&v"(ry), [sr] "+v"(S.re), [si] "+v"(S.im),
                                   [rr] "+v"(R.re), [ri] "+v"(R.im)
                                 : [d] "v"(d[k0 + w]), [thr] "v"(thr), [r] "v"(r[k0 + w]),
-                                  [x] "s"(xs[u0 * NW + k0 + w]), [gr] "s"(gh[w].re),
+                                  [x] "s"(xs[u0 * NW + k0 + w]), [a] "v"(a), [gr] "s"(gh[w].re),
                                   [gi] "s"(gh[w].im)
                                 : "vcc");
                         }
-                        // S - om R
-                        vz = cmul(vcw, cmake(fma(om.im, R.im, fma(-om.re, R.re, S.re)),
-                                             fma(-om.im, R.re, fma(-om.re, R.im, S.im))));
+                        // S - i Im om R
+                        vz = cmul(vcw, cmake(fma(b, R.im, S.re), fma(-b, R.re, S.im)));
                     }
                     cmac(acc[u0 + u], am[u0 + u], vz);
                     if constexpr (AM) am_put(amc, p, u0 + u, an[u0 + u], vz);
