@@ -249,6 +249,41 @@ struct OccupiedBand {
     }
 };
 
+// The exchange sums of exchange_bands term by term, each denominator inverted
+// by itself and branch A's term multiplied by r and rs in turn: r rs alone is
+// below the smallest double from |x| = 1e80 on.
+template <int NW, int NC>
+__device__ __forceinline__ void exchange_one_by_one(int n0, int n1, int nb, int ng,
+                                                    gptr<double2> aqsn, uint32_t goff,
+                                                    gptr<double2> aqsm, const int (&pc)[NC],
+                                                    gptr<double> wx, const cplx (&om)[NC],
+                                                    const double (&wi2)[NC],
+                                                    const double (&thr)[NC], cplx (&SX)[NC][NW])
+{
+    for (int n = n0; n < n1; ++n) {
+        OccupiedBand<NW, NC> band;
+        band.load(n, nb, ng, aqsn, goff, aqsm, pc, wx);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const cplx qm = qm_of(band.an, band.am[c]);
+            const double a = om[c].re, b = om[c].im;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const double dr = band.x[w] - a, sp = band.x[w] + a;
+                const double d = fma(dr, dr, wi2[c]), rs = rcp_nr2(fma(sp, sp, wi2[c]));
+                const double u = fma(dr, sp, wi2[c]);
+                const bool isA = d > thr[c], isB = branch_b_holds(fma(a, a, wi2[c]), d);
+                const double f = isA ? rcp_nr2(d) : (isB ? -0.5 : 0.0);
+                const double vr = f * (isA ? a * fma(-2.0, wi2[c], u) : sp);
+                const double vi = f * (isA ? b * fma(2.0 * a, a, u) : -b);
+                const double g = isA || isB ? rs : 0.0;
+                cmac(SX[c][w], qm, cmake(g * vr, g * vi));
+                __builtin_amdgcn_sched_barrier(0);  // one term's registers at a time
+            }
+        }
+    }
+}
+
 // Screened exchange of the occupied bands n0 <= n < n1 (all below nvband) of
 // one lane and NC columns: sums of ssx / (e om) in SX.  With d = x - om and
 // s = x + om, the exchange term is
@@ -260,8 +295,10 @@ struct OccupiedBand {
 // all columns and frequencies, 1/(|d|^2 |s|^2); rs is that times |d|^2.  (Both
 // are at least (Im om)^2 >= 2^-60 where the batch is used, so a product of up
 // to 8 pairs stays normal; the other lanes' wave inverts each by itself,
-// which keeps rs finite on an exact pole.)  Selects pick the branch, so a
-// value computed for another branch never reaches the sums.
+// which keeps rs finite on an exact pole.  A product that passes 2^1000 sends
+// the wave's sums to exchange_one_by_one, after the loop, so that the rare form
+// takes no registers of this one.)  Selects pick the branch, so a value
+// computed for another branch never reaches the sums.
 // The Coulomb-hole terms of these bands run in the hot loop like all others,
 // and this runs after it, when the hole's sums have left the registers.
 // Before it, 32 x 512 x 64 with two occupied bands took 11.6 us (now 10.3).
@@ -278,6 +315,7 @@ __device__ __forceinline__ void exchange_bands(int n0, int n1, int nb, int ng, g
 {
     constexpr int K = NC * NW;
     static_assert(K <= 8, "the 2^-60 lane bound keeps products of 8 pairs normal");
+    uint64_t over = 0;  // lanes whose product passed 2^1000
     OccupiedBand<NW, NC> cur;
     cur.load(n0, nb, ng, aqsn, goff, aqsm, pc, wx);
     for (int n = n0; n < n1; ++n) {
@@ -304,7 +342,8 @@ __device__ __forceinline__ void exchange_bands(int n0, int n1, int nb, int ng, g
             for (int k = 0; k < K; ++k) q[k] = fma(fma(-pr[k], q[k], 1.0), q[k], q[k]);
 #pragma unroll
             for (int k = 0; k < K; ++k) rs[k] = q[k] * d[k];
-            if (__builtin_expect(batch_misses(all, narrow) != 0, 0)) {
+            over |= batch_misses(all, 0);
+            if (__builtin_expect(narrow != 0, 0)) {
                 one_by_one<K>(d, q);
                 one_by_one<K>(ws, rs);
 #pragma unroll
@@ -332,6 +371,13 @@ __device__ __forceinline__ void exchange_bands(int n0, int n1, int nb, int ng, g
             }
         }
         cur = next;
+    }
+    if (__builtin_expect(over != 0, 0)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) SX[c][w] = cmake(0.0, 0.0);
+        exchange_one_by_one<NW, NC>(n0, n1, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr, SX);
     }
 }
 
