@@ -195,6 +195,13 @@ __device__ __forceinline__ void one_by_one(const double (&d)[K], double (&r)[K])
 #pragma unroll
     for (int k = 0; k < K; ++k) r[k] = rcp_nr2(d[k]);
 }
+// One Newton step on each reciprocal: of the batch's error, up to 2e-15, one
+// rounding is left.
+template <int K>
+__device__ __forceinline__ void refine(const double (&d)[K], double (&r)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) r[k] = fma(fma(-d[k], r[k], 1.0), r[k], r[k]);
+}
 template <int K>
 __device__ __forceinline__ void batch_reciprocal(const double (&d)[K], double (&r)[K],
                                                  bool batch_ok = true) {

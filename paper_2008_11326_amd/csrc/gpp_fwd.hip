@@ -22,10 +22,9 @@
 // (gpp_device.h: unclamped denominators, a lane test on (Im om)^2 for the
 // product's range), and the branch-A test is the execution mask around
 // each term's four fused multiply-adds, so a masked term adds nothing and
-// costs no select.  Occupied bands (n < nvband) also evaluate the
-// screened-exchange term, after the hole's sums, from one batch inversion of
-// |x - om|^2 |x + om|^2 per band instead of a complex divide
-// (gpp_fwd_tile.h).  Above 512 bands each tile's band loop is split into
+// costs no select.  Occupied bands (n < nvband) run after the others, both
+// their terms from batch inversions of |x - om|^2 |x + om|^2 instead of complex
+// divides (gpp_fwd_tile.h).  Above 512 bands each tile's band loop is split into
 // chunks, each a tile of its own.
 //
 // What bounds it.  Large grids: the fp64 vector ALU at the clock the part

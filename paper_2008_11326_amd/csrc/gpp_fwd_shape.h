@@ -98,6 +98,13 @@ inline int fwd_fine_chunks(long tiles, int bands, int cus)
     return best;
 }
 
+// Terms of an occupied band that share a batch inversion, at most: one group's
+// values must fit beside both sums' accumulators.  With 4 in place of 3, 200
+// bands x 8192 rows x 400 columns (2 occupied) at nfreq 4 took 1093 us against
+// 1051, and with 150 occupied bands at 4096 x 200, nfreq 8, 1321 against 1271; 2
+// measured as 3.
+constexpr int kOccTerms = 3;
+
 // The split form of the forward's tile kernel, for grids of fewer than
 // kSplitBelow tiles (gpp_fwd.hip).  Bands per batch-inverted group there: a
 // 16-wave workgroup holds its waves to 128 VGPRs.

@@ -5,6 +5,7 @@
 #pragma once
 
 #include "gpp_device.h"
+#include "gpp_fwd_shape.h"
 
 namespace gpp {
 
@@ -243,147 +244,177 @@ struct OccupiedBand {
                                          gptr<double> wx) {
         an = load_row_elem(aqsn + (size_t)n * ng, ng, goff);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) am[c] = cload(aqsm + pc[c] + (size_t)n * ng);
+        for (int c = 0; c < NC; ++c)
+            am[c] = Walker{(uint64_t)(aqsm + pc[c] + (size_t)n * ng)}.complex(0);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) x[w] = wx[(size_t)w * nb + n];
+        for (int w = 0; w < NW; ++w) x[w] = Walker{(uint64_t)(wx + (size_t)w * nb + n)}.real(0);
     }
 };
 
-// The exchange sums of exchange_bands term by term, each denominator inverted
-// by itself and branch A's term multiplied by r and rs in turn: r rs alone is
-// below the smallest double from |x| = 1e80 on.
-template <int NW, int NC>
-__device__ __forceinline__ void exchange_one_by_one(int n0, int n1, int nb, int ng,
-                                                    gptr<double2> aqsn, uint32_t goff,
-                                                    gptr<double2> aqsm, const int (&pc)[NC],
-                                                    gptr<double> wx, const cplx (&om)[NC],
-                                                    const double (&wi2)[NC],
-                                                    const double (&thr)[NC], cplx (&SX)[NC][NW])
+// Both sums over an occupied band's terms K0 .. K0+G-1 (term k: column k / NW,
+// frequency k % NW) of one lane: the Coulomb-hole terms over e om / 2 in HX, the
+// screened-exchange ones over e om in SX.  With d = x - om, s = x + om,
+// r = 1/|d|^2 and rs = 1/|s|^2 these are
+//   hole      A:  1/d = conj(d) r = (Re d, Im om) r
+//   exchange  A:  om/(d s) = om conj(s) rs / d,
+//             B:  -1/(2 s) = -conj(s) rs / 2
+// where om conj(s) = (fma(Re om, Re s, (Im om)^2), Im om x).  With BATCH one
+// batch inversion, of |d|^2 |s|^2, gives every r and rs of the group, each
+// refined by a Newton step of its own; `over` collects the lanes whose product
+// left the range.  Otherwise each is inverted by itself, which keeps rs finite
+// on an exact pole, and branch C is looked for.  Branch A's term is multiplied by
+// r and rs in turn: r rs alone is below the smallest double from |x| = 1e80 on.
+// The compare d > thr is the execution mask of the hole's sums and, inverted, of
+// branch B's value.
+template <int NW, int NC, int K0, int G, bool BATCH>
+__device__ __forceinline__ void occupied_terms(const OccupiedBand<NW, NC> &band,
+                                               const cplx (&om)[NC], const double (&wi2)[NC],
+                                               const double (&thr)[NC], uint64_t &over,
+                                               cplx (&HX)[NC][NW], cplx (&SX)[NC][NW])
 {
-    for (int n = n0; n < n1; ++n) {
-        OccupiedBand<NW, NC> band;
-        band.load(n, nb, ng, aqsn, goff, aqsm, pc, wx);
+    double d[G], r[G], rs[G];
+    {
+        double pr[G], ws[G], q[G], c[G];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const cplx qm = qm_of(band.an, band.am[c]);
-            const double a = om[c].re, b = om[c].im;
+        for (int k = 0; k < G; ++k) {
+            const int i = (K0 + k) / NW;
+            const double x = band.x[(K0 + k) % NW];
+            const double dr = x - om[i].re, sp = x + om[i].re;
+            d[k] = fma(dr, dr, wi2[i]);  // |x - om|^2, the branch's wdiffr
+            ws[k] = fma(sp, sp, wi2[i]);  // |x + om|^2
+            pr[k] = d[k] * ws[k];
+        }
+        if constexpr (BATCH) {
+            const double all = batch_prefix<G>(pr, c);
+            over |= batch_misses(all, 0);
+            batch_back<G>(pr, c, all, q);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const double dr = band.x[w] - a, sp = band.x[w] + a;
-                const double d = fma(dr, dr, wi2[c]), rs = rcp_nr2(fma(sp, sp, wi2[c]));
-                const double u = fma(dr, sp, wi2[c]);
-                const bool isA = d > thr[c], isB = branch_b_holds(fma(a, a, wi2[c]), d);
-                const double f = isA ? rcp_nr2(d) : (isB ? -0.5 : 0.0);
-                const double vr = f * (isA ? a * fma(-2.0, wi2[c], u) : sp);
-                const double vi = f * (isA ? b * fma(2.0 * a, a, u) : -b);
-                const double g = isA || isB ? rs : 0.0;
-                cmac(SX[c][w], qm, cmake(g * vr, g * vi));
-                __builtin_amdgcn_sched_barrier(0);  // one term's registers at a time
+            for (int k = 0; k < G; ++k) {
+                r[k] = q[k] * ws[k];
+                rs[k] = q[k] * d[k];
+            }
+            refine<G>(d, r);
+            refine<G>(ws, rs);
+        } else {
+            one_by_one<G>(d, r);
+            one_by_one<G>(ws, rs);
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                const int i = (K0 + k) / NW;
+                const double wtr = fma(om[i].re, om[i].re, wi2[i]);
+                if (!(d[k] > thr[i] || branch_b_holds(wtr, d[k]))) rs[k] = 0.0;
             }
         }
     }
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+        const int i = (K0 + k) / NW, w = (K0 + k) % NW;
+        const cplx qm = qm_of(band.an, band.am[i]);
+        const double x = band.x[w], a = om[i].re, b = om[i].im;
+        const double sp = x + a;
+        const cplx h = cmake(r[k] * (x - a), r[k] * b);  // 1/d
+        asm("v_cmpx_gt_f64_e32 vcc, %[d], %[thr]\n\t"
+            "v_fma_f64 %[xr], %[hr], %[qr], %[xr]\n\t"
+            "v_fma_f64 %[xi], %[hr], %[qi], %[xi]\n\t"
+            "v_fma_f64 %[xr], -%[hi], %[qi], %[xr]\n\t"
+            "v_fma_f64 %[xi], %[hi], %[qr], %[xi]\n\t"
+            "s_mov_b64 exec, -1"
+            : [xr] "+v"(HX[i][w].re), [xi] "+v"(HX[i][w].im)
+            : [d] "v"(d[k]), [thr] "v"(thr[i]), [hr] "v"(h.re), [hi] "v"(h.im),
+              [qr] "v"(qm.re), [qi] "v"(qm.im)
+            : "vcc");
+        cplx t = cmul(cmake(fma(a, sp, wi2[i]), b * x), h);
+        asm("v_cmpx_ngt_f64_e32 vcc, %[d], %[thr]\n\t"
+            "v_mul_f64 %[tr], -0.5, %[sp]\n\t"
+            "v_mul_f64 %[ti], 0.5, %[b]\n\t"
+            "s_mov_b64 exec, -1"
+            : [tr] "+v"(t.re), [ti] "+v"(t.im)
+            : [d] "v"(d[k]), [thr] "v"(thr[i]), [sp] "v"(sp), [b] "v"(b)
+            : "vcc");
+        cmac(SX[i][w], qm, cscale(rs[k], t));
+    }
 }
 
-// Screened exchange of the occupied bands n0 <= n < n1 (all below nvband) of
-// one lane and NC columns: sums of ssx / (e om) in SX.  With d = x - om and
-// s = x + om, the exchange term is
-//   A:  om^2 / (d s) = om^2 conj(d s) r rs,     r = 1/|d|^2, rs = 1/|s|^2
-//   B:  -om / (2 s)  = -om conj(s) rs / 2
-// where conj(d s) = (u, 2 Re om Im om) with u = fma(Re d, Re s, (Im om)^2)
-// (both factors exact to rounding even where x is near -Re om), so om
-// conj(d s) is linear in u.  One batch inversion per band gives the r rs of
-// all columns and frequencies, 1/(|d|^2 |s|^2); rs is that times |d|^2.  (Both
-// are at least (Im om)^2 >= 2^-60 where the batch is used, so a product of up
-// to 8 pairs stays normal; the other lanes' wave inverts each by itself,
-// which keeps rs finite on an exact pole.  A product that passes 2^1000 sends
-// the wave's sums to exchange_one_by_one, after the loop, so that the rare form
-// takes no registers of this one.)  Selects pick the branch, so a value
-// computed for another branch never reaches the sums.
-// The Coulomb-hole terms of these bands run in the hot loop like all others,
-// and this runs after it, when the hole's sums have left the registers.
-// Before it, 32 x 512 x 64 with two occupied bands took 11.6 us (now 10.3).
-// Both done here, column by column, with an inversion each for |d|^2 and
-// |s|^2 and the accumulators of the hot loop alive, 64 occupied bands of 128
-// at 4096 rows x 204 columns, nfreq 3, took 463 us in place of 456.
-template <int NW, int NC>
-__device__ __forceinline__ void exchange_bands(int n0, int n1, int nb, int ng, gptr<double2> aqsn,
-                                               uint32_t goff, gptr<double2> aqsm,
-                                               const int (&pc)[NC], gptr<double> wx,
-                                               const cplx (&om)[NC], const double (&wi2)[NC],
-                                               const double (&thr)[NC], uint64_t narrow,
-                                               cplx (&SX)[NC][NW])
+// Terms K0, K0 + 1, ... of a band in groups of at most G, one group's registers
+// at a time.
+template <int NW, int NC, int K0, int G, bool BATCH>
+__device__ __forceinline__ void occupied_groups(const OccupiedBand<NW, NC> &band,
+                                                const cplx (&om)[NC], const double (&wi2)[NC],
+                                                const double (&thr)[NC], uint64_t &over,
+                                                cplx (&HX)[NC][NW], cplx (&SX)[NC][NW])
 {
-    constexpr int K = NC * NW;
-    static_assert(K <= 8, "the 2^-60 lane bound keeps products of 8 pairs normal");
-    uint64_t over = 0;  // lanes whose product passed 2^1000
+    constexpr int left = NC * NW - K0;
+    occupied_terms<NW, NC, K0, (left < G ? left : G), BATCH>(band, om, wi2, thr, over, HX, SX);
+    if constexpr (left > G) {
+        __builtin_amdgcn_sched_barrier(0);
+        occupied_groups<NW, NC, K0 + G, G, BATCH>(band, om, wi2, thr, over, HX, SX);
+    }
+}
+
+// The sums of one form; returns the lanes whose batch left its range.
+template <int NW, int NC, int G, bool BATCH>
+__device__ __forceinline__ uint64_t occupied_sums(int n0, int n1, int nb, int ng,
+                                                  gptr<double2> aqsn, uint32_t goff,
+                                                  gptr<double2> aqsm, const int (&pc)[NC],
+                                                  gptr<double> wx, const cplx (&om)[NC],
+                                                  const double (&wi2)[NC], const double (&thr)[NC],
+                                                  cplx (&HX)[NC][NW], cplx (&SX)[NC][NW])
+{
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) HX[c][w] = SX[c][w] = cmake(0.0, 0.0);
+    uint64_t over = 0;
     OccupiedBand<NW, NC> cur;
     cur.load(n0, nb, ng, aqsn, goff, aqsm, pc, wx);
     for (int n = n0; n < n1; ++n) {
         OccupiedBand<NW, NC> next;  // loads while this band computes
         next.load(n + 1 < n1 ? n + 1 : n, nb, ng, aqsn, goff, aqsm, pc, wx);
-        double d[K], q[K], rs[K];
-        {
-            double pr[K], ws[K], c[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const double x = cur.x[k % NW], a = om[k / NW].re;
-                const double dr = x - a, sp = x + a;
-                d[k] = fma(dr, dr, wi2[k / NW]);  // |x - om|^2, the branch's wdiffr
-                ws[k] = fma(sp, sp, wi2[k / NW]);  // |x + om|^2
-                pr[k] = d[k] * ws[k];
-            }
-            const double all = batch_prefix<K>(pr, c);
-            batch_back<K>(pr, c, all, q);
-            // one Newton step each takes the roundings of the batch's chain
-            // back out: asxtemp is off by 3.6e-16 of its value at 2048 rows x
-            // 102 columns, nfreq 5, without it by 4.5e-16 (time there 44.4
-            // and 44.6 us)
-#pragma unroll
-            for (int k = 0; k < K; ++k) q[k] = fma(fma(-pr[k], q[k], 1.0), q[k], q[k]);
-#pragma unroll
-            for (int k = 0; k < K; ++k) rs[k] = q[k] * d[k];
-            over |= batch_misses(all, 0);
-            if (__builtin_expect(narrow != 0, 0)) {
-                one_by_one<K>(d, q);
-                one_by_one<K>(ws, rs);
-#pragma unroll
-                for (int k = 0; k < K; ++k) q[k] *= rs[k];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const cplx qm = qm_of(cur.an, cur.am[c]);
-            const double a = om[c].re, b = om[c].im;
-            const double wtr = fma(a, a, wi2[c]);
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const int k = c * NW + w;
-                const double x = cur.x[w];
-                const double dr = x - a, sp = x + a;
-                const double u = fma(dr, sp, wi2[c]);
-                const bool isA = d[k] > thr[c];
-                const bool isB = branch_b_holds(wtr, d[k]);
-                // om conj(d s) = (a u - 2 a b^2, b u + 2 a^2 b); conj(s) = (sp, -b)
-                const double vr = isA ? a * fma(-2.0, wi2[c], u) : sp;
-                const double vi = isA ? b * fma(2.0 * a, a, u) : -b;
-                const double f = isA ? q[k] : (isB ? -0.5 * rs[k] : 0.0);
-                cmac(SX[c][w], qm, cmake(f * vr, f * vi));
-            }
-        }
+        occupied_groups<NW, NC, 0, G, BATCH>(cur, om, wi2, thr, over, HX, SX);
         cur = next;
     }
-    if (__builtin_expect(over != 0, 0)) {
+    return over;
+}
+
+// Both sums over the occupied bands n0 <= n < n1 (all below nvband).  The batch
+// needs denominators of at least 2^-60 (a product of G <= 8 pairs then stays
+// normal) and waves where no lane's threshold lets branch C occur; `narrow`
+// waves, those with a nearly vanishing om, and those whose batch overflowed take
+// the sums term by term, in a loop of their own (a branch inside the common one
+// costs it 12 to 100 spilled registers).
+// One loop for both sums because every value but the last products is common:
+// 150 occupied bands of 200, 4096 rows x 200 columns, nfreq 1, 2, 3, 4 and 8, took
+// 303, 504, 696, 768 and 1528 us with the hole's terms in the hot loop and their
+// reciprocals from its batch, 230, 419, 584, 671 and 1271 so; all of om real,
+// nfreq 3 and 8, 1004 and 2295 against 681 and 1545.
+template <int NW, int NC>
+__device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng, gptr<double2> aqsn,
+                                               uint32_t goff, gptr<double2> aqsm,
+                                               const int (&pc)[NC], gptr<double> wx,
+                                               const cplx (&om)[NC], const double (&wi2)[NC],
+                                               const double (&thr)[NC], uint64_t narrow,
+                                               cplx (&HX)[NC][NW], cplx (&SX)[NC][NW])
+{
+    constexpr int K = NC * NW;
+    constexpr int groups = (K + kOccTerms - 1) / kOccTerms, G = (K + groups - 1) / groups;
+    static_assert(G <= 8, "the 2^-60 lane bound keeps products of 8 pairs normal");
+    bool below = false;
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-#pragma unroll
-            for (int w = 0; w < NW; ++w) SX[c][w] = cmake(0.0, 0.0);
-        exchange_one_by_one<NW, NC>(n0, n1, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr, SX);
-    }
+    for (int c = 0; c < NC; ++c)  // d <= thr off branch A, and rounding is monotone
+        below = below || !branch_b_holds(fma(om[c].re, om[c].re, wi2[c]), thr[c]);
+    uint64_t alone = narrow | __builtin_amdgcn_ballot_w64(below);
+    if (alone == 0)
+        alone = occupied_sums<NW, NC, G, true>(n0, n1, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr,
+                                               HX, SX);
+    if (__builtin_expect(alone != 0, 0))
+        occupied_sums<NW, NC, 1, false>(n0, n1, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr, HX,
+                                        SX);
 }
 
 // Where a tile's sums go.  hole() takes the lanes' Coulomb-hole parts (2 NW
-// values per lane), exchange() the screened-exchange ones; either may be
-// called or not, at most once.
+// values per lane) of the unoccupied bands, occupied() those of the occupied
+// ones and their screened-exchange parts; either may be called or not, at most
+// once, hole() first.
 //
 // A row of 4 NW wave totals in LDS, achtemp re, im, asxtemp re, im per
 // frequency, so that no total stays in registers over the band loop.  With
@@ -402,8 +433,11 @@ struct RowSink {
     __device__ __forceinline__ void hole(const double (&v)[2 * NW]) const {
         wave_totals<2 * NW>(v, lane, [&](int i, double t) { row[i + (i & ~1)] = t; });
     }
-    __device__ __forceinline__ void exchange(const double (&v)[2 * NW]) const {
-        wave_totals<2 * NW>(v, lane, [&](int i, double t) { row[i + (i & ~1) + 2] = t; });
+    // each total is added by the lane that wrote hole()'s
+    __device__ __forceinline__ void occupied(const double (&v)[2 * NW],
+                                             const double (&x)[2 * NW]) const {
+        wave_totals<2 * NW>(v, lane, [&](int i, double t) { row[i + (i & ~1)] += t; });
+        wave_totals<2 * NW>(x, lane, [&](int i, double t) { row[i + (i & ~1) + 2] = t; });
     }
 };
 // Running sums of a persistent wave, in scalar registers.
@@ -416,7 +450,11 @@ struct RunningSink {
         for (int w = 0; w < NW; ++w) ach[w] = asx[w] = cmake(0.0, 0.0);
     }
     __device__ __forceinline__ void hole(const double (&v)[2 * NW]) { add(ach, v); }
-    __device__ __forceinline__ void exchange(const double (&v)[2 * NW]) { add(asx, v); }
+    __device__ __forceinline__ void occupied(const double (&v)[2 * NW],
+                                             const double (&x)[2 * NW]) {
+        add(ach, v);
+        add(asx, x);
+    }
     __device__ __forceinline__ void add(cplx (&to)[NW], const double (&v)[2 * NW]) {
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
@@ -478,72 +516,78 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
         }
     }
 
-    // Coulomb hole of all bands, whole groups, then band by band
-    cplx P1[NC][NW], P2[NC][NW];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
-    BandGroup<NW, BU> first;
-    first.load_first(n_lo, nb, ng, aqsn, goff, wx);
-    const int n = ch_bands<NW, BU, NC>(n_lo, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr,
-                                       narrow, first, P1, P2);
-    if constexpr (BU > 1) {
-        if (n < n_hi) {
-            BandGroup<NW, 1> rest;
-            rest.load_first(n, nb, ng, aqsn, goff, wx);
-            ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow,
-                                rest, P1, P2);
-        }
-    }
-
-    double v2[2 * NW];
-#pragma unroll
-    for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        if constexpr (Sink::kKeep > 0) {
-            ev[c] = cmake(sink.fetch(3 * c), sink.fetch(3 * c + 1));
-            om[c] = cmake(a[c], sink.fetch(3 * c + 2));
-        }
-        const double wtr = fma(a[c], a[c], wi2[c]);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            // S = om P1 - wtr P2
-            cplx S = cmul(om[c], P1[c][w]);
-            S.re = fma(-wtr, P2[c][w].re, S.re);
-            S.im = fma(-wtr, P2[c][w].im, S.im);
-            const cplx t = cscale(0.5, cmul(ev[c], S));
-            v2[2 * w] += t.re;
-            v2[2 * w + 1] += t.im;
-        }
-    }
-    sink.hole(v2);
-
-    // occupied bands: their screened exchange, after the hole so that neither
-    // holds the other's sums in registers
+    // occupied bands come last, so that neither part holds the other's sums in
+    // registers (first, 32 x 512 x 64 with two of them took 1 us more)
     const int occ_hi = nv < n_hi ? nv : n_hi;
-    if (occ_hi > n_lo) {
-        cplx SX[NC][NW];
+    if (occ_hi < n_hi) {
+        // Coulomb hole of the unoccupied bands, whole groups, then band by band
+        cplx P1[NC][NW], P2[NC][NW];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) SX[c][w] = cmake(0.0, 0.0);
-        exchange_bands<NW, NC>(n_lo, occ_hi, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr, narrow,
-                               SX);
+            for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
+        int n = occ_hi > n_lo ? occ_hi : n_lo;
+        BandGroup<NW, BU> first;
+        first.load_first(n, nb, ng, aqsn, goff, wx);
+        n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow,
+                                 first, P1, P2);
+        if constexpr (BU > 1) {
+            if (n < n_hi) {
+                BandGroup<NW, 1> rest;
+                rest.load_first(n, nb, ng, aqsn, goff, wx);
+                ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow,
+                                    rest, P1, P2);
+            }
+        }
+        if constexpr (Sink::kKeep > 0) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                ev[c] = cmake(sink.fetch(3 * c), sink.fetch(3 * c + 1));
+                om[c] = cmake(a[c], sink.fetch(3 * c + 2));
+            }
+        }
+        double v2[2 * NW];
 #pragma unroll
         for (int k = 0; k < 2 * NW; ++k) v2[k] = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const cplx evom = cmul(ev[c], om[c]);
+            const double wtr = fma(a[c], a[c], wi2[c]);
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
-                const cplx t = cmul(evom, SX[c][w]);
+                // S = om P1 - wtr P2
+                cplx S = cmul(om[c], P1[c][w]);
+                S.re = fma(-wtr, P2[c][w].re, S.re);
+                S.im = fma(-wtr, P2[c][w].im, S.im);
+                const cplx t = cscale(0.5, cmul(ev[c], S));
                 v2[2 * w] += t.re;
                 v2[2 * w + 1] += t.im;
             }
         }
-        sink.exchange(v2);
+        sink.hole(v2);
+    }
+
+    if (occ_hi > n_lo) {
+        cplx HX[NC][NW], SX[NC][NW];
+        occupied_bands<NW, NC>(n_lo, occ_hi, nb, ng, aqsn, goff, aqsm, pc, wx, om, wi2, thr, narrow,
+                               HX, SX);
+        double v2[2 * NW], x2[2 * NW];
+#pragma unroll
+        for (int k = 0; k < 2 * NW; ++k) v2[k] = x2[k] = 0.0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if constexpr (Sink::kKeep > 0)
+                ev[c] = cmake(sink.fetch(3 * c), sink.fetch(3 * c + 1));
+            const cplx evom = cmul(ev[c], om[c]);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const cplx h = cmul(evom, HX[c][w]), x = cmul(evom, SX[c][w]);
+                v2[2 * w] = fma(0.5, h.re, v2[2 * w]);
+                v2[2 * w + 1] = fma(0.5, h.im, v2[2 * w + 1]);
+                x2[2 * w] += x.re;
+                x2[2 * w + 1] += x.im;
+            }
+        }
+        sink.occupied(v2, x2);
     }
 }
 

@@ -43,3 +43,34 @@ def test_exchange_far_from_the_poles(gpp, nw, imag, scale):
     bar = 40 + nb * ng * npw
     say(f"[fwd accuracy] exchange x ~ {scale:g} nfreq {nw}: {worst:.1f} u, bar {bar}")
     assert worst <= bar
+
+
+@pytest.mark.parametrize("nw", range(1, 9))
+@pytest.mark.parametrize("shape,draws", [((1, 64, 4), 40), ((8, 64, 4), 40), ((8, 4096, 160), 12)])
+def test_reciprocals_of_occupied_bands(gpp, nw, shape, draws):
+    """At x = 0 a Coulomb-hole term is om / (0 - om) = -1, every other factor
+    here being 1 and every other term 0, formed as om (conj(0 - om) r) with r
+    the reciprocal of |om|^2: apart from the roundings of two products its error
+    is that of the reciprocal.  Bar: with r good to one rounding u, the real
+    part, a sum of two products of one sign, is off by at most 4 u (r, the
+    factor conj(0 - om) r, one product and the sum), the imaginary part, whose
+    products are at most 1/2 and cancel, by at most u: 4.2 u together.  (A
+    reciprocal from a batch alone is off by up to 20 u.)"""
+    nb, ng, npw = shape
+    rng = np.random.default_rng(nw + nb + ng)
+    prob = I.make_problem(I.Dims(nb, nb, ng, npw, nw), 1)
+    prob.aqsmtemp[:] = 1.0
+    worst = 0.0
+    for _ in range(draws):
+        w, n, p, g = (rng.integers(k) for k in (nw, nb, npw, ng))
+        prob.wtilde_array[:] = rng.uniform(0.6, 2, (npw, ng)) + 1j * rng.uniform(-1, 1, (npw, ng))
+        prob.wx_array[:] = rng.uniform(-2, -0.1, (nw, nb))
+        prob.wx_array[w, n] = 0.0
+        for a, at, v in ((prob.aqsntemp, n, 1.0), (prob.I_eps_array, (p, g), 1.0),
+                         (prob.vcoul, g, 2.0)):
+            a[:] = 0.0
+            a[at] = v
+        ach, _ = gpp.sigma_fwd(**to_device(prob), nvband=nb)
+        worst = max(worst, abs(complex(ach[w].item()) + 1.0))
+    say(f"[fwd accuracy] reciprocals {shape} nfreq {nw}: {worst / U:.1f} u, bar 4.2")
+    assert worst <= 4.2 * U
