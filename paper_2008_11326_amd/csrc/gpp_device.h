@@ -202,6 +202,18 @@ __device__ __forceinline__ void refine(const double (&d)[K], double (&r)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) r[k] = fma(fma(-d[k], r[k], 1.0), r[k], r[k]);
 }
+// The same one after the other, with one register pair for all of them.
+template <int K>
+__device__ __forceinline__ void refine_in_turn(const double (&d)[K], double (&r)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        double e;
+        asm("v_fma_f64 %[e], -%[d], %[r], 1.0\n\t"
+            "v_fma_f64 %[r], %[e], %[r], %[r]"
+            : [e] "=&v"(e), [r] "+v"(r[k])
+            : [d] "v"(d[k]));
+    }
+}
 template <int K>
 __device__ __forceinline__ void batch_reciprocal(const double (&d)[K], double (&r)[K],
                                                  bool batch_ok = true) {

@@ -4,6 +4,8 @@
 // gpp_fwd.hip for the derivation.
 #pragma once
 
+#include <type_traits>
+
 #include "gpp_device.h"
 #include "gpp_fwd_shape.h"
 
@@ -137,10 +139,12 @@ struct BandGroup {
 // Coulomb-hole sums of NC columns over the whole groups of BU bands in
 // [n, n_hi), the first of them loaded in `cur`; returns the first
 // band left over.  The BU*NW*NC denominators of a group share one batch
-// inversion; they go in unclamped: every one is at least (Im om)^2, and where
-// a lane has a column with (Im om)^2 below kMinUnclampedWi2 (the wave mask
-// `narrow`) the wave inverts one by one; a masked term's reciprocal (possibly
-// infinite or NaN there) never reaches the sums (ch_term).
+// inversion; they go in unclamped: every one is at least (Im om)^2.  Where
+// a lane has a column with (Im om)^2 below kMinUnclampedWi2 the wave takes the
+// NARROW form, whose denominators are at least kLimitTwo, which changes no term
+// that ch_term keeps (thr is at least that), and whose reciprocals get a Newton
+// step each: as good as one by one (200 bands x 8192 rows x 400 columns, all om
+// real, nfreq 1, 3, 5 and 8: XXTIMES).
 // Loads run ahead of their use, so that no wait sits in front of a group's
 // arithmetic: the frequencies of the next group are asked for together with
 // this group's aqsmtemp values, which are needed only after the reciprocals;
@@ -154,12 +158,12 @@ struct BandGroup {
 // wave-terms per second; a register-only loop of the same instructions
 // reaches 4.3e10 at the part's power limit), 256 states of 32-128 bands
 // 10.7 -> 10.2 ms; of that the running addresses 2.0 and 2.6 %.
-template <int NW, int BU, int NC>
+template <int NW, int BU, int NC, bool NARROW>
 __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<double2> aqsn,
                                         uint32_t goff, gptr<double2> aqsm, const int (&pc)[NC],
                                         gptr<double> wx, const double (&a)[NC],
                                         const double (&wi2)[NC], const double (&thr)[NC],
-                                        uint64_t narrow, BandGroup<NW, BU> &cur,
+                                        BandGroup<NW, BU> &cur,
                                         cplx (&P1)[NC][NW], cplx (&P2)[NC][NW])
 {
     constexpr int KB = BU * NW;  // terms of one column
@@ -205,12 +209,14 @@ __device__ __forceinline__ int ch_bands(int n, int n_hi, int nb, int ng, gptr<do
             for (int k = 0; k < KB; ++k) {
                 const double dr = xs[k] - a[c];
                 d[c * KB + k] = fma(dr, dr, wi2[c]);
+                if constexpr (NARROW) d[c * KB + k] = fmax(d[c * KB + k], kLimitTwo);
             }
         }
         double c[K];
         const double all = batch_prefix<K>(d, c);
         batch_back<K>(d, c, all, r);
-        if (__builtin_expect(batch_misses(all, narrow) != 0, 0)) one_by_one<K>(d, r);
+        if (__builtin_expect(batch_misses(all, 0) != 0, 0)) one_by_one<K>(d, r);
+        if constexpr (NARROW) refine_in_turn<K>(d, r);
         cplx qm[NC][BU];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -526,19 +532,24 @@ __device__ __forceinline__ void fwd_tile_body(int nb, int nv, int n_lo, int n_hi
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int w = 0; w < NW; ++w) P1[c][w] = P2[c][w] = cmake(0.0, 0.0);
-        int n = occ_hi > n_lo ? occ_hi : n_lo;
-        BandGroup<NW, BU> first;
-        first.load_first(n, nb, ng, aqsn, goff, wx);
-        n = ch_bands<NW, BU, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow,
-                                 first, P1, P2);
-        if constexpr (BU > 1) {
-            if (n < n_hi) {
-                BandGroup<NW, 1> rest;
-                rest.load_first(n, nb, ng, aqsn, goff, wx);
-                ch_bands<NW, 1, NC>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2, thr, narrow,
-                                    rest, P1, P2);
+        const int n0 = occ_hi > n_lo ? occ_hi : n_lo;
+        const auto hole = [&](auto narrow_form) {
+            constexpr bool NARROW = decltype(narrow_form)::value;
+            BandGroup<NW, BU> first;
+            first.load_first(n0, nb, ng, aqsn, goff, wx);
+            const int n = ch_bands<NW, BU, NC, NARROW>(n0, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a,
+                                                       wi2, thr, first, P1, P2);
+            if constexpr (BU > 1) {
+                if (n < n_hi) {
+                    BandGroup<NW, 1> rest;
+                    rest.load_first(n, nb, ng, aqsn, goff, wx);
+                    ch_bands<NW, 1, NC, NARROW>(n, n_hi, nb, ng, aqsn, goff, aqsm, pc, wx, a, wi2,
+                                                thr, rest, P1, P2);
+                }
             }
-        }
+        };
+        if (__builtin_expect(narrow != 0, 0)) hole(std::true_type());
+        else hole(std::false_type());
         if constexpr (Sink::kKeep > 0) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) {

@@ -74,3 +74,33 @@ def test_reciprocals_of_occupied_bands(gpp, nw, shape, draws):
         worst = max(worst, abs(complex(ach[w].item()) + 1.0))
     say(f"[fwd accuracy] reciprocals {shape} nfreq {nw}: {worst / U:.1f} u, bar 4.2")
     assert worst <= 4.2 * U
+
+
+@pytest.mark.parametrize("nw", range(1, 9))
+@pytest.mark.parametrize("shape,draws", [((8, 64, 4), 40), ((9, 4096, 160), 12)])
+def test_reciprocals_of_real_poles(gpp, nw, shape, draws):
+    """The same for unoccupied bands where every om is real, a fifth of them
+    on a frequency of some band.  The term is there -(|om|^2 r), P1 = 0: one
+    rounding of r and one of the product."""
+    nb, ng, npw = shape
+    rng = np.random.default_rng(nw + nb + ng)
+    prob = I.make_problem(I.Dims(nb, 0, ng, npw, nw), 1)
+    prob.aqsmtemp[:] = 1.0
+    worst = 0.0
+    for _ in range(draws):
+        w, n, p, g = (rng.integers(k) for k in (nw, nb, npw, ng))
+        prob.wx_array[:] = rng.uniform(-2, 2, (nw, nb))
+        prob.wx_array[w, n] = 0.0
+        om = rng.uniform(0.6, 2, (npw, ng))
+        on = rng.random(om.shape) < 0.2
+        om[on] = rng.choice(np.abs(prob.wx_array.ravel()), size=int(on.sum()))
+        om[p, g] = rng.uniform(0.6, 2)
+        prob.wtilde_array[:] = om
+        for a, at, v in ((prob.aqsntemp, n, 1.0), (prob.I_eps_array, (p, g), 1.0),
+                         (prob.vcoul, g, 2.0)):
+            a[:] = 0.0
+            a[at] = v
+        ach, _ = gpp.sigma_fwd(**to_device(prob), nvband=0)
+        worst = max(worst, abs(complex(ach[w].item()) + 1.0))
+    say(f"[fwd accuracy] real poles {shape} nfreq {nw}: {worst / U:.1f} u, bar 2")
+    assert worst <= 2 * U
