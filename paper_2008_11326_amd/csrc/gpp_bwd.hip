@@ -170,15 +170,17 @@ struct PairState {
 };
 
 // One band of one lane with frequencies x (wave-uniform): its Z = conj(om) K
-// [+ KS] and, with WANT_W, W = L [+ LS]; OCC adds the exchange parts.  Those,
-// ssx = e sigma and d ssx/d om = e delta, with d = x - om, s = x + om and
-// D = d s = x^2 - om^2, are
-//   A:  sigma = om^2 / D,       delta = 2 om x^2 / D^2
-//   B:  sigma = -om / (2 s),    delta = -x / (2 s^2)
-// evaluated without a divide as in the forward: 1/D = conj(D) r rs and
-// 1/s = conj(s) rs with r = 1/|d|^2, rs = 1/|s|^2, where conj(D) =
-// (fma(Re d, Re s, (Im om)^2), 2 Re om Im om) and om conj(s) =
-// (fma(Re om, Re s, (Im om)^2), Im om x); selects pick the branch's value.
+// [+ KS] and, with WANT_W, W = L [+ LS]; OCC adds the exchange parts.  With
+// d = x - om, s = x + om, u = conj(1/d) and y = conj(1/s) those are, from ssx =
+// e sigma and d ssx/d om = e delta,
+//   A:  conj(sigma) = conj(om)^2 u y,   conj(delta) = 2 conj(om) (x u y)^2
+//   B:  conj(sigma) = -conj(om) y / 2,  conj(delta) = -x y^2 / 2
+// and so, with m = conj(om) u on branch A, -1/2 on B and l = 2 x u on A, 1 on B,
+//   conj(sigma) = conj(om) m y,         conj(delta) = x l m y^2
+// without a divide: u = d r and y = s rs, where r = 1/|d|^2 (0 off branch A) and
+// rs = 1/|s|^2 (0 on branch C).  Selecting m and l in place of sigma and delta:
+// 100 occupied bands of 128, 4096 rows x 200 columns, nfreq 1, 3 and 8, 614 -> 560,
+// 1353 -> 1191 and 3305 -> 2876 us for the whole adjoint.
 // The reciprocals come one by one: delta takes their squares, and those of a
 // batch inversion (one Newton step, shared error) raised the dwtilde error of
 // a problem with few bands from 3.8e-16 to 1.7e-15.
@@ -188,54 +190,40 @@ __device__ __forceinline__ void band_zw(const double (&x)[NW], const double2 *__
                                         cplx &Z, cplx &W)
 {
     const double a = ps.a, b = ps.b, wi2 = ps.wi2;
-    double d[NW], r[NW], ws[NW], rs[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const double dr = x[w] - a, sp = x[w] + a;
-        d[w] = fma(dr, dr, wi2);
-        ws[w] = fma(sp, sp, wi2);
-    }
-    one_by_one<NW>(d, r);
-    if (OCC) one_by_one<NW>(ws, rs);
     cplx K = cmake(0.0, 0.0), L = cmake(0.0, 0.0), KS = K, LS = K;
-    const double ab2 = 2.0 * a * b;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const double dr = x[w] - a, sp = x[w] + a;
-        const bool isA = d[w] > ps.thr;
-        const double rm = isA ? r[w] : 0.0;
-        const cplx uu = cmake(dr * rm, -b * rm);  // conj(1/(x - om))
+        const double d = fma(dr, dr, wi2), r = rcp_nr2(d);
+        const bool isA = d > ps.thr;
+        const double rm = isA ? r : 0.0;
+        const cplx u = cmake(dr * rm, -b * rm);
         const cplx gh = half_of(ga, w);
-        cmac(K, gh, uu);
-        if (WANT_W) cmac(L, cscale(x[w], gh), cmul(uu, uu));
+        cmac(K, gh, u);
+        if (WANT_W) cmac(L, cscale(x[w], gh), cmul(u, u));
         if constexpr (OCC) {
-            const bool isB = branch_b_holds(ps.wtr, d[w]);
-            const double q = rm * rs[w];
-            const cplx cd = cmake(fma(dr, sp, wi2), ab2);  // conj(D)
-            const cplx om2 = cmake(fma(a, a, -wi2), ab2);
-            const cplx sa = cscale(q, cmul(om2, cd));
-            const double h = -0.5 * rs[w];
-            const cplx sb = cmake(fma(a, sp, wi2) * h, (b * x[w]) * h);
-            const cplx sigma = cmake(isA ? sa.re : (isB ? sb.re : 0.0),
-                                     isA ? sa.im : (isB ? sb.im : 0.0));
-            cmac(KS, cload(gs + w), cmake(sigma.re, -sigma.im));
+            const double rs = rcp_nr2(fma(sp, sp, wi2));
+            const double rsm = isA || branch_b_holds(ps.wtr, d) ? rs : 0.0;
+            const cplx y = cmake(sp * rsm, b * rsm);
+            cplx m = cmul(cmake(a, -b), u);
+            m.re = isA ? m.re : -0.5;
+            const cplx my = cmul(m, y), g = cload(gs + w);
+            cmac(KS, g, my);
             if constexpr (WANT_W) {
-                const cplx da = cscale(2.0 * x[w] * x[w] * q * q, cmul(ps.om, cmul(cd, cd)));
-                // conj(s)^2 = (sp^2 - b^2, -2 sp b)
-                const double hh = h * rs[w] * x[w];
-                const cplx db = cmake(fma(sp, sp, -wi2) * hh, -2.0 * sp * b * hh);
-                const cplx delta = cmake(isA ? da.re : (isB ? db.re : 0.0),
-                                         isA ? da.im : (isB ? db.im : 0.0));
-                cmac(LS, cload(gs + w), cmake(delta.re, -delta.im));
+                cplx l = cscale(2.0 * x[w], u);
+                l.re = isA ? l.re : 1.0;
+                cmac(LS, cscale(x[w], g), cmul(cmul(my, y), l));
             }
+            // one term at a time: six and more at once take 40 registers more
+            if constexpr (NW > 5 && WANT_W) __builtin_amdgcn_sched_barrier(0);
         }
+    }
+    if constexpr (OCC) {
+        K = cadd(K, KS);
+        L = cadd(L, LS);
     }
     Z = cmul(cmake(a, -b), K);
     W = L;
-    if constexpr (OCC) {
-        Z = cadd(Z, KS);
-        W = cadd(W, LS);
-    }
 }
 
 __device__ __forceinline__ PairState make_pair(cplx om, cplx e, double v)
