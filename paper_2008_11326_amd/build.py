@@ -12,6 +12,7 @@ link into paper_2008_11326_amd/libgpp.so.  Packed-fp32 instructions are
 disabled for all device code.  build() also compiles the native side of the
 Python binding (host code against torch's headers) into _binding.so.
 """
+import hashlib
 import os
 import subprocess
 import sys
@@ -45,10 +46,26 @@ FLAGS = [
 EXTRA_FLAGS = {src: ["-mllvm", "-disable-machine-sink"]
                for src in ("gpp_fwd.hip", "gpp_batched.hip", "gpp_bwd.hip")}
 
+# What the batched plan's tuning candidates are compiled from.
+TUNED = ["gpp_batched.hip", "gpp_fwd_tile.h", "gpp_fwd_shape.h", "gpp_device.h", "gpp_internal.h",
+         "gpp_plan.hip"]
+
+
+def kernels_id(defines=()) -> str:
+    """Names the kernels a tuned choice was timed with (gpp_plan.hip)."""
+    h = hashlib.sha256(repr((FLAGS[:-2], sorted(EXTRA_FLAGS.items()), list(defines))).encode())
+    for f in TUNED:
+        with open(os.path.join(CSRC, f), "rb") as src:
+            h.update(src.read())
+    return h.hexdigest()[:8]
+
 
 def _compile(src: str, verbose: bool, objdir: str = OBJDIR, defines=()) -> str:
     obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, *EXTRA_FLAGS.get(src, []), *[f"-D{d}" for d in defines], "-c", os.path.join(CSRC, src), "-o", obj]
+    if src == "gpp_plan.hip":
+        defines = [*defines, f'GPP_KERNELS_ID="{kernels_id(defines)}"']
+    cmd = [HIPCC, *FLAGS, *EXTRA_FLAGS.get(src, []), *[f"-D{d}" for d in defines], "-c",
+           os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -11,7 +11,7 @@
 // on this device.  On the first gpp_sigma_batched call, if no cached choice
 // exists, every candidate is timed once on the caller's inputs and the
 // fastest is kept and written to the cache (JSON, keyed by architecture,
-// kind and a hash of the sizes).  Afterwards each call uploads the
+// kind, the build's kernels and a hash of the sizes).  Afterwards each call uploads the
 // descriptor table only if an input pointer changed and replays a graph of
 // [persistent kernel -> per-state reduction] captured on a private stream.
 #include <errno.h>
@@ -59,6 +59,12 @@ long flat_workgroups(const gpp::Dims32 &d)
 #define GPP_QUEUE_CHUNK_TILES 2
 #endif
 constexpr int kQueueChunkTiles = GPP_QUEUE_CHUNK_TILES;
+// What the candidates' times depend on besides the sizes: the build passes a
+// hash of the kernels' sources, so that a choice timed with other kernels does
+// not decide for these.
+#ifndef GPP_KERNELS_ID
+#define GPP_KERNELS_ID "0"
+#endif
 // Workspace layout: [0, 256) the queue counters, then the partial rows.
 constexpr size_t kPartialsOffset = 256;
 
@@ -653,9 +659,9 @@ gpp_status gpp_plan_create(int32_t nstates, const gpp_dims *dims_host, gpp_plan 
     uint64_t h = fnv1a(&pl->nw, sizeof pl->nw);
     for (const auto &d : pl->dims) h = fnv1a(&d, sizeof d, h);
     char key[160];
-    snprintf(key, sizeof key, "gfx950:batched:nw=%d:cols=%d:s=%d:n=%d:cus=%d:h=%016llx", pl->nw,
-             gpp::bat_cols(pl->nw), gpp::kSchedCount, nstates, prop.multiProcessorCount,
-             (unsigned long long)h);
+    snprintf(key, sizeof key, "gfx950:batched:k=%s:nw=%d:cols=%d:s=%d:n=%d:cus=%d:h=%016llx",
+             GPP_KERNELS_ID, pl->nw, gpp::bat_cols(pl->nw), gpp::kSchedCount, nstates,
+             prop.multiProcessorCount, (unsigned long long)h);
     pl->key = key;
 
     const size_t sbytes = sizeof(gpp::StateDesc) * (nstates + 1);
