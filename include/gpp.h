@@ -260,9 +260,9 @@ gpp_status gpp_plan_get_info(const gpp_plan *plan, gpp_plan_info *info);
  *   workspace:        device, >= gpp_plan_workspace(plan) bytes, 256-byte
  *                     aligned
  * First call (tuning): unless the cache holds a choice for these sizes on
- * this architecture with these kernels (a hash of their sources), each candidate (tile variant x state order x
- * tile-to-wave schedule) runs
- * twice on the caller's inputs, timed with events (the call synchronises
+ * this architecture with these kernels (a hash of their sources), each
+ * candidate (tile variant x state order x tile-to-wave schedule) runs twice on
+ * the caller's inputs, timed with events (the call synchronises
  * `stream` then), and the fastest is kept and saved to the cache file
  * $GPP_TUNE_CACHE (default $XDG_CACHE_HOME/gpp/tune.json, else
  * ~/.cache/gpp/tune.json; unreadable or corrupt files are ignored).

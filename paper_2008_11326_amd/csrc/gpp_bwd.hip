@@ -38,7 +38,7 @@
 // (dI_eps at |om| / |x - om| = 450, nfreq 5 to 8, in 2^-53 of the sum of |term|:
 // up to 1000 with B1, up to 14 so; two operations per term more: whole adjoint,
 // bands x rows x columns, 128 x 8192 x 400 at nfreq 5 and 8 2.66 -> 2.78 and
-// 3.97 -> 4.19 ms, 101 x 3001 x 150 at nfreq 5 362 -> 374 us.)
+// 3.97 -> 4.19 ms.)
 // Occupied bands, and up to four frequencies the bands left over of the
 // groups, form K and L per band.
 // bwd_bands (lane = g; a workgroup of four waves owns kBandTile bands and
@@ -55,10 +55,10 @@
 // holds (256 bands x 16384 rows x 819 columns, nfreq 3: pairs kernel 6.8 ->
 // 6.7 ms, 0.92 of the issue slots at 1.98 GHz; bands kernel 7.5 -> 6.7 ms, 0.75
 // -> 0.87 at 2.05 GHz, since it needs x and gh only and its loads run ahead;
-// whole adjoint 14.1 -> 13.1 ms timed in turn).  Short grids: the number of
-// waves and the longest workgroup, hence the forms below (512 rows x 32 bands x
-// 64 columns: 142 us in four-band workgroups, 37.4 now; 3001 x 101 x 150, nfreq
-// 5: 634 and 344).
+// whole adjoint timed in turn 14.00 -> 13.36 ms on one box, 14.95 -> 13.50 on
+// another).  Short grids: the number of waves and the longest workgroup, hence
+// the forms below (512 rows x 32 bands x 64 columns: 142 us in four-band
+// workgroups, 37 now; 3001 x 101 x 150, nfreq 5: 631 and 351).
 #include "gpp_bwd_shape.h"
 #include "gpp_device.h"
 #include "gpp_fwd_tile.h"

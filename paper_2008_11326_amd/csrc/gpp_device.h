@@ -120,8 +120,9 @@ __device__ __forceinline__ double rcp_nr2(double d) {
 
 // Newton steps after the hardware estimate for the batch product.  The
 // estimate is good to 2^-24.4; one step leaves a relative error below
-// 2.2e-15 (2^-48.7, measured over normal inputs with exponents -720..1000,
-// the range a batch product can take), which is shared by the K reciprocals
+// 2.2e-15 (2^-48.7, measured over normal inputs with exponents -720..1000, the
+// range of a product of 12 denominators of at least 2^-60 or of 6 pairs of
+// them), which is shared by the K reciprocals
 // of the batch.  That is far inside the 1e-12 bar on every output, and saves
 // two fused multiply-adds per batch.
 #ifndef GPP_BATCH_NEWTON
@@ -146,14 +147,14 @@ __device__ __forceinline__ double rcp_batch(double d) {
 // r[k] = R c[k-1] and R <- R d[k].  Two halves cost the same 3(K-1)
 // multiplies as one run over all K, with half the serial chain.  Each r[k]
 // carries the error of R plus at most 2K roundings.  The batch path needs
-// every d[k] >= 2^-60 (so that no product of up to 12 leaves the normal
-// range at the bottom; callers pass batch_ok = false for a lane without that
-// bound) and a total product below 2^1000 (an overflowed prefix stays
-// infinite, so this also covers the prefixes).  batch_prefix forms the prefix
-// products and returns the total, batch_back the r[k]; where a lane of the
-// wave fails one of the bounds (batch_misses, one scalar test), every lane
-// inverts one by one instead (one_by_one); a zero there gives an infinite or
-// NaN reciprocal, which callers mask.
+// every d[k] >= 2^-60, or 2^-120 with at most 6 of them (so that no product
+// leaves the normal range at the bottom; callers keep lanes without that bound
+// out of it, or pass batch_ok = false) and a total product below 2^1000 (an
+// overflowed prefix stays infinite, so this also covers the prefixes).
+// batch_prefix forms the prefix products and returns the total, batch_back the
+// r[k]; where a lane of the wave fails one of the bounds (batch_misses, one
+// scalar test), every lane inverts one by one instead (one_by_one); a zero there
+// gives an infinite or NaN reciprocal, which callers mask.
 template <int K>
 __device__ __forceinline__ double batch_prefix(const double (&d)[K], double (&c)[K]) {
     static_assert(K <= 12, "the 2^-60 lane bound keeps products of at most 12 factors normal");
@@ -356,6 +357,13 @@ __device__ __forceinline__ void clear_row(double *row, int lane)
     wave_lds_sync();
 }
 
+// A wave-uniform value moved into scalar registers (the value of lane 0).
+__device__ __forceinline__ double to_uniform(double t) {
+    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(t));
+    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(t));
+    return __hiloint2double(hi, lo);
+}
+
 // Element at byte offset `off` of a complex row of `len` elements whose
 // base is wave-uniform: a raw buffer load with the row in a scalar buffer
 // descriptor (gfx9 descriptor word 3 = 0x00020000) and the offset in a
@@ -365,16 +373,6 @@ __device__ __forceinline__ cplx load_row_elem(gptr<double2> row, int len, uint32
         (void *)(const double2 *)row, (short)0, len * (int)sizeof(double2), 0x00020000);
     const double2 v = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
     return {v.x, v.y};
-}
-
-// Mark a pointer read from memory as a global-memory pointer, so accesses
-// through it compile to global/scalar loads instead of flat ones (pointers
-// passed as kernel arguments get this from address-space inference).
-// A wave-uniform value moved into scalar registers (the value of lane 0).
-__device__ __forceinline__ double to_uniform(double t) {
-    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(t));
-    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(t));
-    return __hiloint2double(hi, lo);
 }
 
 // The same for the row `row_off` bytes further on (a scalar register) than

@@ -37,11 +37,13 @@ constexpr bool fwd_shapes_fit()
 }
 static_assert(fwd_shapes_fit(), "a forward tile's batch inversion holds at most 12 denominators");
 // Minimum waves per SIMD (a VGPR cap) of the forward tile kernels for
-// nfreq = 1..8, measured at 512 bands, 32768 rows, 1638 columns (best of 3
-// alternating rounds): nfreq 4 capped at 96 VGPRs (5 waves) 1.5 % faster
-// than at 103 (4); nfreq 7 and 8 capped at 128 (4 waves; 2 and 24 bytes of
-// spills) 9.5 % and 5.1 % faster than at 130 and 144 (3).  nfreq 1 capped
-// for 6 waves and nfreq 6 for 4 ran 0.9 % and 16 % slower.
+// nfreq = 1..8.  nfreq 2 capped at 168 VGPRs (3 waves; 8 of them spilled, outside
+// the hot loop) against 176 (2 waves): 23.0 and 24.3 ms at 512 bands x 32768 rows
+// x 1638 columns, 2.77 and 2.86 at 300 x 12000 x 900.  nfreq 4 capped at 96 (5
+// waves; 12 spilled) against 100 (4): equal there, 5.24 and 5.32 ms at 300 x 12000
+// x 900.  At 3 (154), 7 (120) and 8 (128) the cap is what the compiler takes
+// without it (times equal to 1 %); it keeps a change from crossing the line.
+// nfreq 1 capped for 6 waves and nfreq 6 for 4 ran 0.9 % and 16 % slower.
 #ifndef GPP_FWD_MIN_WAVES
 #define GPP_FWD_MIN_WAVES 1, 3, 3, 5, 1, 1, 4, 4
 #endif

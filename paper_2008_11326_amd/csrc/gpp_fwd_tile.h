@@ -384,8 +384,8 @@ __device__ __forceinline__ uint64_t occupied_sums(int n0, int n1, int nb, int ng
 }
 
 // Both sums over the occupied bands n0 <= n < n1 (all below nvband).  The batch
-// needs denominators of at least 2^-60 (a product of G <= 8 pairs then stays
-// normal) and waves where no lane's threshold lets branch C occur; `narrow`
+// needs denominators of at least 2^-60 (a product of G <= 6 pairs is then in its
+// range) and waves where no lane's threshold lets branch C occur; `narrow`
 // waves, those with a nearly vanishing om, and those whose batch overflowed take
 // the sums term by term, in a loop of their own (a branch inside the common one
 // costs it 12 to 100 spilled registers).
@@ -404,7 +404,7 @@ __device__ __forceinline__ void occupied_bands(int n0, int n1, int nb, int ng, g
 {
     constexpr int K = NC * NW;
     constexpr int groups = (K + kOccTerms - 1) / kOccTerms, G = (K + groups - 1) / groups;
-    static_assert(G <= 8, "the 2^-60 lane bound keeps products of 8 pairs normal");
+    static_assert(G <= 6, "the 2^-60 lane bound keeps products of 6 pairs in the batch's range");
     bool below = false;
 #pragma unroll
     for (int c = 0; c < NC; ++c)  // d <= thr off branch A, and rounding is monotone
