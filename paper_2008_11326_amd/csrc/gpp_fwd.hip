@@ -256,10 +256,16 @@ FwdGeometry fwd_geometry(const Dims32 &d)
     geo.red_blocks = one ? 0 : geo.nblocks < kRedBlocks ? geo.nblocks : kRedBlocks;
     geo.red_chunk = one ? 0 : (geo.nblocks + geo.red_blocks - 1) / geo.red_blocks;
     // sized for the long form and its first stage: 2^3 waves per tile and 16
-    // per workgroup make at most twice its rows, and then no first stage
+    // per workgroup make at most twice its rows, and then no first stage.
+    // Where finer band chunks may be chosen, at least for the most rows they
+    // make at any size, so that a smaller call never needs more than a larger
+    // one and one buffer serves every state of a program.
     const size_t row = 4 * sizeof(double) * d.nw;
     const long stage_rows = long_rows < kRedBlocks ? long_rows : kRedBlocks;
-    geo.workspace_bytes = (size_t)(long_rows + stage_rows) * row;
+    long rows = long_rows + stage_rows;
+    if (fwd_most_tiles(gtiles, d.np, d.nb) >= kSplitBelow && rows < kFineRows + kRedBlocks)
+        rows = kFineRows + kRedBlocks;
+    geo.workspace_bytes = (size_t)rows * row;
     return geo;
 }
 

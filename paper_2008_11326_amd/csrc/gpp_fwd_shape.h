@@ -107,6 +107,16 @@ inline int fwd_fine_chunks(long tiles, int bands, int cus)
 // measured as 3.
 constexpr int kOccTerms = 3;
 
+// The most partial rows a grid with finer chunks makes (16895 tiles in two, at
+// 486 bands and more), and the most tiles a call has at any frequency count (one
+// column each).
+constexpr long kFineRows = 8448;
+inline long fwd_most_tiles(long gtiles, int np, int nb)
+{
+    const int chunks = GPP_FWD_CHUNK_BANDS > 0 ? (nb - 1) / GPP_FWD_CHUNK_BANDS + 1 : 1;
+    return gtiles * np * chunks;
+}
+
 // The split form of the forward's tile kernel, for grids of fewer than
 // kSplitBelow tiles (gpp_fwd.hip).  Bands per batch-inverted group there: a
 // 16-wave workgroup holds its waves to 128 VGPRs.

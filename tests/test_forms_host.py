@@ -4,6 +4,7 @@ a threshold cannot take a kernel out of the tests unseen.  A small C++ shim call
 the library's own geometry functions (no device call)."""
 import ctypes as C
 import os
+import random
 import subprocess
 
 import pytest
@@ -24,6 +25,7 @@ extern "C" void forms(int nb, int nv, int ng, int np, int nw, int *out)
     out[2] = b.share_pairs;
     out[3] = b.tile_bands;
     out[4] = b.single;
+    out[5] = (int)(f.nblocks + f.red_blocks);
 }
 """
 
@@ -42,9 +44,9 @@ def form(tmp_path_factory):
     shim = C.CDLL(lib)
 
     def of(shape):
-        out = (C.c_int * 5)()
+        out = (C.c_int * 6)()
         shim.forms(*shape, out)
-        return dict(zip(("waves", "nchunk", "share", "tile", "single"), out))
+        return dict(zip(("waves", "nchunk", "share", "tile", "single", "rows"), out))
 
     return of
 
@@ -70,3 +72,32 @@ def test_small_shapes_take_the_short_forms(form):
         assert {f["waves"] for f in small} == {16}
         assert {f["share"] for f in small} == {1}
         assert {f["tile"] for f in small} == {1, 2}
+
+
+def need(shape):
+    return int(_lib.load().gpp_sigma_fwd_workspace(C.byref(_lib.dims_struct(*shape))))
+
+
+def random_shape(rng):
+    nw, nb = rng.randint(1, 8), int(2 ** rng.uniform(0, 11))
+    ng = int(2 ** rng.uniform(0, 17))
+    return nb, 0, ng, max(1, min(ng, int(2 ** rng.uniform(0, 12)))), nw
+
+
+def test_forward_workspace_holds_every_row(form):
+    rng = random.Random(3)
+    for _ in range(20000):
+        shape = random_shape(rng)
+        assert form(shape)["rows"] * 32 * shape[4] <= need(shape), shape
+
+
+def test_forward_workspace_of_a_larger_call_serves_a_smaller_one():
+    """A program that keeps one buffer for states of several sizes sizes it for
+    the largest: no call with every size at most as large may need more."""
+    rng = random.Random(4)
+    for _ in range(100000):
+        nb, nv, ng, npw, nw = small = random_shape(rng)
+        grow = lambda n: int(n * rng.choice((1, 1, 1.05, 1.5, 2.5)))
+        ng2 = grow(ng)
+        large = (grow(nb), nv, ng2, max(npw, min(ng2, grow(npw))), min(8, nw + rng.randint(0, 2)))
+        assert need(small) <= need(large), (small, large)
